@@ -301,8 +301,8 @@ def main():
         peak = (PEAK_FP32_TFLOPS if (dom == "k_ctg_main" and args.ctg_precision != "fp64")
                 else PEAK_FP64_TFLOPS)
         runit = "TFLOP/s"
-    # the map-reduce stage runs k_ctg_pm under a period-split tile
-    kname = "k_ctg_pm" if (dom == "k_ctg_main" and prob.dims["ctg_split"]) else dom
+    # the map-reduce stage runs k_ctg_rows under a period-split tile
+    kname = "k_ctg_rows" if (dom == "k_ctg_main" and prob.dims["ctg_split"]) else dom
     roof = dict(bound=bound, kernel=kname, achieved=achieved, peak=peak, unit=runit,
                 frac=achieved / peak, traffic=stored_traffic(kname, args.config, prob.tile()),
                 per_launch=f"{amount:.4g} {unit} algorithmic, mean {kms[dom] * 1e3:.2f} us/launch")

@@ -93,15 +93,13 @@ enum { QG_CTG_ALL_NONBRIDGE = 0, QG_CTG_LIST = 1 };
  * accumulates them); the sum goes into the QG_T_CTG_MEAN slot and
  * QG_T_CTG_MAX is 0. */
 #define QG_FLAG_CTG_SUM 0x8u
-/* Bound-based skip in the contingency map-reduce.  Default: with every
- * contingency scored and blocks of 4 to 64 / (periods per wavefront) branch
- * tiles, a half row (4 branches, one period, 64 contingencies) is passed
- * over when |F_tl| + max|LODF_lk| max|F_tk| proves every post-outage flow
- * within its test radius, the factors' maximum taken as stored (FP64, FP32
- * or BF16) and with margins that cover the rounding of the exact test of
- * that precision, so the results are bitwise those of testing every
- * element.  With this flag every element is tested (a reference for that
- * claim). */
+/* Bound-based skip in the contingency map-reduce.  Default: a row (one
+ * branch, one period, 64 scored contingencies) is passed over when
+ * |F_tl| + max|LODF_lk| max|F_tk| proves every post-outage flow within its
+ * test radius, the factors' maximum taken as stored (FP64, FP32 or BF16) and
+ * with margins that cover the rounding of the exact test of that precision,
+ * so the results are bitwise those of testing every element.  With this flag
+ * every element is tested (a reference for that claim). */
 #define QG_FLAG_CTG_NO_SKIP 0x10u
 
 /* Grid description: host arrays, all FP64 per unit (100 MVA base) unless
@@ -193,7 +191,9 @@ typedef struct {
   double final_score;        /* -L at eps = 0, beta = 1, rho_scale = rhof */
   double terms[QG_NTERMS];   /* score-point terms at the end */
   /* mean duration per launch when profile = 1, in stream order: k_forward,
-   * k_ctg_main, k_ctg_zred, k_ctg_asm, k_adjoint, k_final (slots 6, 7 unused) */
+   * k_ctg_main, k_ctg_zred, k_ctg_asm, k_adjoint, k_final (slots 6, 7 unused);
+   * under a period-split tile k_ctg_rows runs in k_ctg_main's place and does
+   * k_ctg_zred's work, whose slot then shows only the events' distance */
   double kernel_ms[QG_NKERNELS];
   int64_t kernel_calls[QG_NKERNELS];
   /* device time of the steps, from HIP events on the solve's stream around
@@ -324,19 +324,17 @@ qg_status qg_solve(qg_problem* prob, double* d_x, double* d_m, double* d_v,
 /*
  * Batched solve of independent scenarios (problems built separately, of any
  * sizes; the scenario batching of the many-problem workload): the same
- * schedule and Adam constants for all, n_steps steps each.  A step is six
- * launches for the whole batch, one per stage of the single-problem step
+ * schedule and Adam constants for all, n_steps steps each.  A step is five
+ * launches for the whole batch, one per kernel of the single-problem step
  * (Section II-C to II-G; Alg. 3), each covering every scenario's blocks;
- * the contingency map-reduce (eqs. (rank_correct), (sfr_pen)-(zctg)) is one
- * persistent launch whose blocks take (scenario, branch block, contingency
- * block, period chunk) work items from a counter until none is left.  Steps
- * are replayed from one HIP graph per 16 steps.  Every scenario gets the
+ * the contingency map-reduce (eqs. (rank_correct), (sfr_pen)-(zctg)) finishes
+ * the penalties too.  Steps are replayed from one HIP graph per 16 steps.  Every scenario gets the
  * points of its own qg_solve steps, bit for bit.
  *   Arrays of n entries (n <= QG_BATCH_MAX): problems, x, m, v, workspaces
  *   (caller-owned, as for qg_solve) and reports.
  *   d_batch: caller-owned device buffer of at least qg_batch_bytes bytes,
- *   256-byte aligned (every scenario's kernel arguments, the block tables of
- *   the six launches and the work counter); overwritten by the call.
+ *   256-byte aligned (every scenario's kernel arguments and the block tables
+ *   of the launches); overwritten by the call.
  *   Every problem with contingencies needs a period-split tile of 4
  *   wavefronts of 4 periods (qg_set_ctg_tile_split(prob, 4, 4, lt); the
  *   branch tiles per block lt chosen per problem), screening off, and the
@@ -381,11 +379,12 @@ qg_status qg_set_ctg_tile(qg_problem* prob, int32_t bl, int32_t wl, int32_t tc);
 
 /*
  * Branch tiles (of wl * bl branches; of 8 branches for a period-split tile)
- * that one block of the contingency map-reduce covers, lt in [1, 64] (at
- * least 2 for a period-split tile), or 0 for the default (doubling from 1,
- * or 2, while at least 2048 blocks remain, at most 8).  More tiles per block
- * spread each block's fixed costs and shrink the per-(period, contingency)
- * partial sums; fewer leave more blocks.  qg_set_ctg_tile resets it to the
+ * that one block of the contingency map-reduce covers (a wavefront of one,
+ * for a period-split tile), lt in [1, 64] (at least 2 for a period-split
+ * tile), or 0 for the default (doubling from 1, or 2, while at least 2048
+ * blocks remain, at most 8; a period-split tile at its default takes as many
+ * wavefronts per block as keep every block resident).  More tiles spread the
+ * fixed costs; fewer leave more blocks or wavefronts.  qg_set_ctg_tile resets it to the
  * default; qg_set_ctg_tile_split sets it (0: the default).
  * Results depend on it only through the order of floating-point sums.  A
  * step graph cached by qg_solve is re-captured after a change.  Errors: ARG.
@@ -394,12 +393,12 @@ qg_status qg_set_ctg_ltiles(qg_problem* prob, int32_t lt);
 
 /*
  * Period-split tile of the contingency map-reduce (the default form): a
- * block of wl wavefronts (1..8) covers lt consecutive tiles of 8 branches (lt
- * in [2, 64], or 0 for the default of qg_set_ctg_ltiles) and 64
- * contingencies, and its wavefronts split the periods, tcw (1..8) each, so a
- * block spans wl * tcw periods.  A wavefront's per-(period, contingency) sums
- * stay with it over the block's whole branch range (no sum over wavefronts);
- * with wl * tcw >= T each outage factor is read once per evaluation.
+ * block covers one period and 64 contingencies over every branch, its
+ * wavefronts split the branches in slices of at least lt tiles of 8 (lt in
+ * [2, 64], or 0 for the default of qg_set_ctg_ltiles; whole 64-branch groups,
+ * at most 16 slices).  wl (1..8) and tcw (1..8) describe a period chunk of wl *
+ * tcw periods and enter the default lt and the tile a batched solve asks for;
+ * they do not change the results.
  * Results depend on the tile only through the order of floating-point sums.
  * qg_set_ctg_tile returns to the branch-stacked form.  A step graph cached by
  * qg_solve is re-captured after a change.  Errors: ARG.

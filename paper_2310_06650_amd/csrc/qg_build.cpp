@@ -128,7 +128,7 @@ ConstLayout const_layout(const Problem& p) {
       (size_t)p.Lp * p.Kp * lodf_elem_bytes(lodf_kind_of(p.flags)),  // lodf (FP64/FP32/BF16)
       T * (size_t)p.Lp * D,                       // cload
       (size_t)p.Lp * D,                           // rsum
-      (size_t)(p.Lp / 4) * (p.Kp / 64) * D};      // lmaxh
+      (size_t)p.Lp * (p.Kp / 64) * D};            // lmax
   ConstLayout c;
   size_t o = 0;
   for (int i = 0; i < kNConst; ++i) {
@@ -160,7 +160,8 @@ WorkLayout work_layout(const Problem& p) {
       T * N * D, T * N * D,                             // lamp, lamq
       4 * T * G * D,                                    // gdev
       (size_t)p.nLb_max * T * p.Kp * D, (size_t)p.nLb_max * T * p.Kp * D,
-      (size_t)p.nKb_max * T * p.Lp * D, (size_t)p.nKb_max * T * p.Lp * D,
+      (size_t)p.nKb_max * T * p.Lp * 2 * D,             // rpart and qpart, or rq
+      T * (size_t)(p.Lp / 64) * p.nKb_max * 8,          // hot
       T * p.Kp * D, T * p.Kp * D,                       // smean, zval
       (size_t)p.Lp * p.Tp * D,                          // gfT
       T * p.Lp * D,                                     // qtot
@@ -176,10 +177,7 @@ WorkLayout work_layout(const Problem& p) {
       T * G * D, T * G * D,                             // lamg, lamqg
       T * (size_t)p.G16 * D,                            // isfk
       T * p.Lp * D,                                     // thr
-      T * (size_t)p.nKb_max * p.nLb_max,                // zflag
-      T * (size_t)(p.Lp / 8) * rflag_stride(p.nKb_max),   // rflag
-      kSchedStride * D,                                 // snext
-      ((size_t)(p.Lp / 8 + 1) * T + 8) * 16 * D};       // fh
+      kSchedStride * D};                                // snext
   WorkLayout w;
   const int n = (int)(sizeof(cnt) / sizeof(cnt[0]));
   size_t o = 0;
@@ -255,6 +253,27 @@ void apply_ctg_tile(Problem* p, const CtgTile& t) {
   p->tile = t;
   const int span = t.split ? 8 * t.lt : t.bl * t.wl * t.lt;
   p->nLb = (p->Lp + span - 1) / span;
+}
+
+int ctg_slices(const Problem& p, int nkb) {
+  if (!p.tile.split) return 0;
+  const int ng = p.Lp / 64;
+  int most;  // 64-branch groups of a slice
+  if (p.tile.lt != default_ctg_lt(p, p.tile)) {
+    most = (p.tile.lt + 7) / 8;
+  } else {
+    // the most wavefronts per block with which every block is resident at
+    // once (28 wavefronts of k_ctg_rows fit a CU), but 8 at least: a block's
+    // wavefronts wait for each other twice, so where the blocks come in
+    // several rounds smaller blocks that overlap do better.  us of the
+    // map-reduce with 16 / 11 / 8 slices: 162 blocks of 14 groups 7.5 (14
+    // slices) / - / 8.7 (7), 456 of 44 16.6 / 13.3 / 13.8, 589 of 23 15.4 /
+    // 13.3 (12) / 12.7, 1824 of 44 49 / 42 / 36.
+    const int per_cu = (nkb * p.T + 255) / 256;
+    const int wl = std::max(8, std::min(kCtgSlices, 28 / per_cu));
+    most = (ng + wl - 1) / wl;
+  }
+  return std::min(kCtgSlices, (ng + most - 1) / most);
 }
 
 int ctg_tc_cap(int wl) {
@@ -653,9 +672,9 @@ qg_status build_arena(const qg_grid_desc* d, const qg_build_opts* o, Problem* p,
         out[k] = (row[d->br_from[bk]] - row[d->br_to[bk]]) / denom[k];
       }
     });
-    // largest |factor| of every 4-branch group over every 64-contingency
-    // block (NaN entries left out), of the factors as stored (FP32 or BF16
-    // rounding included): the bound of the map-reduce's skip test
+    // largest |factor| of every branch over every 64-contingency block (NaN
+    // entries left out), of the factors as stored (FP32 or BF16 rounding
+    // included): the bound of the map-reduce's row test
     {
       double* lm = reinterpret_cast<double*>(img.data() + cl.off[46]);
       const int nkb = Kp / 64;
@@ -670,15 +689,15 @@ qg_status build_arena(const qg_grid_desc* d, const qg_build_opts* o, Problem* p,
         return v;
       };
       parallel_for(Lp / 4, [&](int q) {
-        for (int kb = 0; kb < nkb; ++kb) {
-          double m = 0.0;
-          for (int l = 4 * q; l < 4 * q + 4; ++l)
+        for (int l = 4 * q; l < 4 * q + 4; ++l)
+          for (int kb = 0; kb < nkb; ++kb) {
+            double m = 0.0;
             for (int k = 64 * kb; k < 64 * kb + 64; ++k) {
               const double v = std::fabs(stored(lo[(size_t)l * Kp + k]));
               if (v > m) m = v;  // false for NaN
             }
-          lm[(size_t)q * nkb + kb] = m;
-        }
+            lm[(size_t)kb * Lp + l] = m;
+          }
       });
     }
     if (kind == kLodfF32) {
@@ -759,7 +778,7 @@ void rebase_pointers(Problem* p, void* arena) {
   dp.lodf_kind = lodf_kind_of(p->flags);
   dp.ctg_sum = (p->flags & QG_FLAG_CTG_SUM) ? 1 : 0;
   dp.lodf = dp.lodf_kind == kLodfF64 ? D(43) : nullptr;
-  dp.lmaxh = !(p->flags & QG_FLAG_CTG_NO_SKIP) ? D(46) : nullptr;
+  dp.lmax = !(p->flags & QG_FLAG_CTG_NO_SKIP) ? D(46) : nullptr;
   dp.lodf32 = dp.lodf_kind == kLodfF32 ? reinterpret_cast<const float*>(base + cl.off[43]) : nullptr;
   dp.lodf16 =
       dp.lodf_kind == kLodfBF16 ? reinterpret_cast<const uint16_t*>(base + cl.off[43]) : nullptr;
@@ -777,35 +796,35 @@ DevWork carve_workspace(const Problem* p, void* ws) {
   w.sched = D(2);
   w.epP = D(3); w.epQ = D(4); w.bco = D(5); w.q2 = D(6);
   w.F = D(7); w.Fk = D(8); w.lamp = D(9); w.lamq = D(10); w.gdev = D(11);
-  w.zpart = D(12); w.spart = D(13); w.rpart = D(14); w.qpart = D(15);
+  w.zpart = D(12); w.spart = D(13); w.rpart = w.rq = D(14);
+  w.qpart = w.rpart + (size_t)p->nKb_max * p->T * p->Lp;
+  w.hot = reinterpret_cast<uint64_t*>(base + wl.off[15]);
   w.smean = D(16); w.zval = D(17); w.gfT = D(18); w.qtot = D(19); w.gpdc = D(20);
   w.epGV = D(21); w.epGT = D(22); w.tpart = D(23); w.terms = D(24);
   w.drs = D(25); w.zmaxp = D(26); w.zargp = D(27); w.zsump = D(28); w.kstar = D(29);
   w.smaxp = D(30);
   w.lamg = D(31); w.lamqg = D(32); w.isfk = D(33); w.thr = D(34);
-  w.zflag = base + wl.off[35];
-  w.rflag = base + wl.off[36];
-  w.snext = D(37);
-  w.fh = D(38);
+  w.snext = D(35);
   return w;
 }
 
 // Screening buffer: act_k, act_slot, top, sel [Kp] int32; sev [Kp] double;
-// key [Kp] uint64; then the gathered outage factors [Lp][cap padded to 64]
-// in the problem's factor storage.  Each part 256-byte aligned.
+// key [Kp] uint64; the gathered outage factors [Lp][cap padded to 64] in the
+// problem's factor storage; their largest magnitudes [cap padded / 64][Lp].  Each part 256-byte aligned.
 namespace {
 struct ScreenLayout {
-  size_t off[7];
+  size_t off[8];
   size_t total;
 };
 ScreenLayout screen_layout(const Problem& p, int cap) {
   const size_t Kp = (size_t)p.Kp;
   const size_t ka = (size_t)round_up(cap, kCtgLanes);
-  const size_t cnt[7] = {Kp * 4, Kp * 4, Kp * 4, Kp * 4, Kp * 8, Kp * 8,
-                         (size_t)p.Lp * ka * lodf_elem_bytes(lodf_kind_of(p.flags))};
+  const size_t cnt[8] = {Kp * 4, Kp * 4, Kp * 4, Kp * 4, Kp * 8, Kp * 8,
+                         (size_t)p.Lp * ka * lodf_elem_bytes(lodf_kind_of(p.flags)),
+                         ka / kCtgLanes * p.Lp * 8};
   ScreenLayout sl;
   size_t o = 0;
-  for (int i = 0; i < 7; ++i) {
+  for (int i = 0; i < 8; ++i) {
     sl.off[i] = o;
     o += (size_t)round_up((int64_t)cnt[i], kAlign);
   }
@@ -826,6 +845,7 @@ void carve_screen(const Problem& p, void* buf, int cap, Screen* sc) {
   sc->sev = reinterpret_cast<double*>(b + sl.off[4]);
   sc->key = reinterpret_cast<uint64_t*>(b + sl.off[5]);
   sc->lodf_act = b + sl.off[6];
+  sc->lmax_act = reinterpret_cast<double*>(b + sl.off[7]);
   sc->bytes = sl.total;
 }
 

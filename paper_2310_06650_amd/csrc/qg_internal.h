@@ -16,6 +16,7 @@ constexpr int kBlock = 256;        // threads per block of the streaming kernels
 constexpr int kCtgLanes = 64;      // contingencies per wavefront in the map-reduce
 constexpr int kParams = 16;        // doubles in the per-step parameter block
 constexpr int kCtgMaxTc = 8;            // periods per block of the contingency kernel
+constexpr int kCtgSlices = 16;          // most branch slices (wavefronts) of a k_ctg_rows block
 constexpr int kCtgLdsBytes = 64 * 1024; // LDS budget of one contingency block
 constexpr int kAdjStepsPerBlock = 32;   // MFMA k-steps per block of the adjoint product
 constexpr int kSchedCap = 2048;         // solve steps per uploaded schedule table
@@ -73,8 +74,8 @@ struct DevProblem {
   const float* lodf32;   //           the same in FP32 (QG_FLAG_CTG_FP32)
   const uint16_t* lodf16;  //         the same in BF16 (QG_FLAG_CTG_BF16)
   int lodf_kind;         // 0 FP64, 1 FP32, 2 BF16 (one of the three pointers is set)
-  const double* lmaxh;   // [Lp/4][Kp/64] max |lodf| (as stored) of each 4-branch group and
-                         // 64-contingency block, NaN left out (null with QG_FLAG_CTG_NO_SKIP)
+  const double* lmax;    // [Kp/64][Lp] max |lodf| (as stored) of each branch over
+                         // 64 contingencies, NaN left out (null with QG_FLAG_CTG_NO_SKIP)
   int ctg_sum;           // 1: per-period sum over contingencies instead of max + mean
   // prices
   double c_p, c_q, c_s, c_ang, ang_max, c_rsv, rho, vload;
@@ -86,10 +87,6 @@ struct DevWork {
   int64_t* step;       // [1] index of the current step in the schedule table
   double* sched;       // [kSchedCap][kSchedStride] per-step eps, beta, rho_s, alpha[6], bc1, bc2
   double* snext;       // [kSchedStride] the schedule row of the next scheduled evaluation
-  double* fh;          // [Lp/8 + 1][T][16] (+ 8 rows): per 8-branch tile and period, F and
-                       // the test radii thr of branches 0-3, then of branches 4-7 (the
-                       // same values as F, thr); the spare tile and rows absorb the
-                       // map-reduce's prefetch
   double* epP; double* epQ;      // [T][2L] branch flows at bus-sorted endpoint slots
   double* bco;         // [9][T][L] per-branch reverse coefficients
   double* q2;          // [T][Lp]  max(q_fr^2, q_to^2)
@@ -98,7 +95,10 @@ struct DevWork {
   double* lamp; double* lamq;    // [T][N] balance multipliers
   double* gdev;        // [4][T][G] device-only partials of p, q, r, u
   double* zpart; double* spart;  // [nLb][T][Kp]
-  double* rpart; double* qpart;  // [nKb][T][Lp]
+  double* rpart; double* qpart;  // [nKb][T][Lp] (branch-stacked tile)
+  double* rq;          // [T][Lp][nKb_max][2] R and Q per contingency block (period-split
+                       // tile; the memory of rpart and qpart), stored where flagged:
+  uint64_t* hot;       // [T][Lp/64][nKb_max] flags of 64 branches per contingency block
   double* smean;       // [T][Kp]
   double* zval;        // [T][Kp]
   double* gfT;         // [Lp][Tp] dL/dF, transposed
@@ -115,14 +115,8 @@ struct DevWork {
   double* smaxp;       // [T][nLc]  per-chunk dL/dF of the worst contingency's own branch
   double* lamg; double* lamqg;   // [T][G] balance multipliers at each generator's bus
   double* isfk;        // [T][G16]  ISF[br(k*_t)][bus(j)] - rowsum/N of the period's worst outage
-  double* thr;         // [T][Lp]  test radius of the outage flows (k_ctg_pm)
-  // which partials were stored (the rest are all zero and not written):
-  uint8_t* zflag;      // [T][nKb_max][nLb_max] z/S partials of (t, k-block, l-block)
-  uint8_t* rflag;      // [T][Lp/8][rflag_stride] R/Q partials of (t, 8 branches, k-block)
+  double* thr;         // [T][Lp]  test radius of the outage flows
 };
-
-// Row stride of DevWork::rflag: k-blocks rounded up to 16 (16-byte loads).
-inline int rflag_stride(int nKb_max) { return (nKb_max + 15) / 16 * 16; }
 
 // Offsets of the term partial sums inside DevWork::tpart.
 struct TermOffsets {
@@ -135,8 +129,8 @@ struct CtgTile {
   int wl;   // wavefronts per block, stacked along branches
   int tc;   // periods per block (the period range is split over grid.z)
   int lt;   // consecutive tiles of wl * bl branches per block (split: of 8
-            // branches, shared by the block's wavefronts)
-  int split = 0;  // 1: period-split blocks (bl = 8, tc periods per wavefront)
+            // branches per wavefront, see ctg_slices)
+  int split = 0;  // 1: period-split blocks, one period each (k_ctg_rows)
 };
 
 // Homotopy source of one evaluation.
@@ -174,6 +168,7 @@ struct Screen {
   double* sev = nullptr;     // [Kp] severities of the last refresh
   uint64_t* key = nullptr;   // [Kp] draw keys of the last refresh
   void* lodf_act = nullptr;  // [Lp][Ka] outage factors of the slots, NaN past n_act
+  double* lmax_act = nullptr;  // [Ka/64][Lp] largest |factor| of a branch over 64 slots
   size_t bytes = 0;          // bytes of the buffer in use
 };
 // Bytes of a screening buffer for up to cap scored contingencies, and the
@@ -267,6 +262,8 @@ int default_ctg_tc(const Problem& p, int wl);
 int default_ctg_lt(const Problem& p, const CtgTile& t);  // tiles per block for tile t
 void apply_ctg_tile(Problem* p, const CtgTile& t);        // set the tile and the l-block count
 CtgTile default_ctg_tile(const Problem& p);               // the tile a new problem starts with
+// branch slices of a period-split block over nkb contingency blocks (0: branch-stacked)
+int ctg_slices(const Problem& p, int nkb);
 int ctg_tc_cap(int wl);  // most periods per block the LDS budget allows
 
 // Kernel launchers (qg_kernels.hip).  A step is kStages kernels.
@@ -286,22 +283,20 @@ int launch_set_step(const Problem* p, const DevWork& w, int64_t value, void* str
 // Batched step of independent problems: kStages launches for all of them.
 // The caller's batch buffer holds every problem's kernel arguments and, per
 // stage, a table of the launch's blocks (problem index << 22 | block of that
-// problem); stage 1, the contingency map-reduce, is a persistent launch that
-// takes its blocks' work items from a counter reset by stage 0.
+// problem).
 struct BatchPlan {
   int n = 0;
-  int nblk[kStages] = {};      // blocks (stage 1: work items) of each batched launch
+  int nblk[kStages] = {};      // blocks of each batched launch
   size_t off_args = 0;         // byte offsets into the batch buffer
   size_t off_tab[kStages] = {};
-  size_t off_ctr = 0;
   size_t bytes = 0;            // size of the batch buffer
   int lodf_kind = 0;
-  int pm_grid = 0;             // blocks of the persistent map-reduce
-  bool skip = false;           // the map-reduce takes the skip test (FP64 factors)
+  int nsl = 0;                 // most branch slices of a problem (map-reduce LDS)
 };
 constexpr int kBatchLocBits = 22;                  // block index bits of a table entry
-constexpr int kBatchWl = 4;                        // wavefronts per map-reduce block
-constexpr int kBatchTcw = 4;                       // periods per map-reduce wavefront
+constexpr int kBatchWl = 4;        // the tile a batch asks of its problems: wavefronts
+constexpr int kBatchTcw = 4;       // and periods per wavefront
+constexpr int kBatchRowWaves = 8;  // wavefronts per block of the batched map-reduce
 // Sizes, validation and (image != nullptr) the host image of a batch buffer
 // for problems whose steps take x[i], m[i], v[i] and workspaces ws[i]; 0 or
 // a message in *err.

@@ -4,10 +4,10 @@
 //   k_forward       per-(t, branch) AC flows and penalties          (Section II-B Ex. 1, 4; II-G)
 //                   + base-case DC flows on FP64 MFMA:                 (eqs. (Yb_solve)-(p_flow))
 //                     F_t = ISF[:, gen] p_t - ISF load_t - mean_t ISF 1 (uniform slack)
-//   k_ctg_main      per-(t, l, k) outage flows F_l + LODF_lk F_k, their (eqs. (rank_correct),
-//                     penalties and partial reductions                   (sfr_pen)-(zctg), (2nd_lin_sys))
-//                     (k_ctg_pm: the same stage with period-split blocks)
-//   k_ctg_zred      per-(t, k) penalties z_tk, per-chunk worst and sum
+//   k_ctg_rows      per-(t, l, k) outage flows F_l + LODF_lk F_k, their (eqs. (rank_correct),
+//                     penalties and reductions, per-(t, k) penalties z_tk, (sfr_pen)-(zctg), (2nd_lin_sys))
+//                     per-chunk worst and sum (branch-stacked tile: k_ctg_main
+//                     and k_ctg_zred instead)
 //   k_ctg_asm       per-(t, l) dL/dF and dL/dqmax2 (mean + worst-contingency weights)
 //                   + per-(t, bus) power balance from bus-sorted endpoint flows
 //                     (LDS-staged segmented sums)                      (Ex. 4)
@@ -57,9 +57,9 @@ struct EvalArgs {
   int fuse_adam;
   int nb_br, nb_bus, bus_chunks, nb_gen, nsplit;
   int nLb, nKb, nKc, nLc, tc, lt;
-  // partials stored sparsely with flags (the period-split map-reduce);
-  // strides of w.zflag (k-blocks, l-blocks per row) and w.rflag (k-blocks)
-  int sparse, zfk, zfs, rfs;
+  // period-split tile: branch slices of a map-reduce block (0: branch-stacked
+  // tile) and the contingency-block stride of w.rq and w.hot
+  int nsl, rqs;
   TermOffsets toff;
   // contingencies scored this step (Alg. 2): slot s of the map-reduce holds
   // contingency act_k[s] (the identity when act_k is null), na slots in use,
@@ -69,6 +69,8 @@ struct EvalArgs {
   const int* act_slot;
   int na, kst;
   const void* lodf_sel;
+  // [nKb][Lp] largest |factor| of a branch over 64 slots (null: test every row)
+  const double* lmax;
 };
 
 // ---------------------------------------------------------------------------
@@ -86,14 +88,14 @@ __device__ __forceinline__ double soft_relu_d(double e, double eps) {
   return m / sqrt(m * m + eps * eps);
 }
 
-// 1/sqrt(x) for x > 0: the hardware estimate refined by two Newton steps on
-// y^-2 = x (y <- y + y (1 - x y^2) / 2), which restores FP64 accuracy.
+// 1/sqrt(x) for x > 0: the hardware estimate (about 2^-23) refined by one
+// third-order step on y^-2 = x: with r = 1 - x y^2, y (1 + r/2 + 3 r^2 / 8) is
+// off by 5 r^3 / 16, far below FP64 rounding.  Three instructions fewer than two
+// Newton steps, and a shorter chain.
 __device__ __forceinline__ double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double r = fma(-x * y, y, 1.0);
-  y = fma(0.5 * y, r, y);
-  r = fma(-x * y, y, 1.0);
-  return fma(0.5 * y, r, y);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double r = fma(-x * y, y, 1.0);
+  return fma(y * r, fma(0.375, r, 0.5), y);
 }
 
 // sigma(e) = sqrt(max(e,0)^2 + eps^2) and d sigma/de = max(e,0)/sigma (0 where
@@ -225,12 +227,6 @@ __device__ __forceinline__ float fma_uniform_c(float a, float b, float c) {
   return d;
 }
 
-// Branch-tiled copy of F and thr (w.fh): per 8-branch tile and period one
-// 128-byte row of two 64-byte halves, [F0..F3 thr0..thr3][F4..F7 thr4..thr7],
-// so that one 16-dword scalar load brings the F and thr of four branches.
-__device__ __forceinline__ constexpr int fh_col_f(int g) { return (g >> 2) * 8 + (g & 3); }
-__device__ __forceinline__ constexpr int fh_col_h(int g) { return (g >> 2) * 8 + 4 + (g & 3); }
-
 // ---- FP32 counterparts for the reduced-precision contingency map-reduce
 
 // 1/sqrt(x) for x > 0 in FP32: the hardware estimate and one Newton step.
@@ -248,23 +244,6 @@ __device__ __forceinline__ double readlane_any(double v, int lane) { return read
 template <typename R>
 __device__ __forceinline__ R writelane_any(R v, R x, int lane) {
   return (int)(threadIdx.x & 63) == lane ? x : v;
-}
-
-// The same with v_writelane (one per 32-bit half), for lanes known at compile
-// time after unrolling (an immediate lane select, which also leaves the one
-// scalar operand the instruction may read to x): the select form would keep
-// one lane mask per constant live in SGPRs.
-__device__ __forceinline__ unsigned writelane_u32(unsigned v, unsigned x, int lane) {
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "i"(lane));
-  return v;
-}
-__device__ __forceinline__ double writelane_set(double v, double x, int lane) {
-  const unsigned lo = writelane_u32((unsigned)__double2loint(v), (unsigned)__double2loint(x), lane);
-  const unsigned hi = writelane_u32((unsigned)__double2hiint(v), (unsigned)__double2hiint(x), lane);
-  return __hiloint2double((int)hi, (int)lo);
-}
-__device__ __forceinline__ float writelane_set(float v, float x, int lane) {
-  return __uint_as_float(writelane_u32(__float_as_uint(v), __float_as_uint(x), lane));
 }
 
 template <int CTRL>
@@ -285,27 +264,6 @@ __device__ __forceinline__ float pair_sum(float a, float b) {
   v += dpp_f32<0x141>(v);
   v += dpp_f32<0x140>(v);
   return v;
-}
-
-// Raw buffer resource over `bytes` bytes from `base` (gfx9 word 3): the
-// address of a buffer access is base + the lane's 32-bit offset (VGPR) + a
-// wavefront-uniform offset (SGPR), so a loop that advances the uniform offset
-// needs no per-lane address arithmetic.  Loads past the end return 0 and
-// stores past it are dropped.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ double lodf_buf(__amdgpu_buffer_rsrc_t r, const double*, unsigned v,
-                                           unsigned s) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
-}
-__device__ __forceinline__ float lodf_buf(__amdgpu_buffer_rsrc_t r, const float*, unsigned v,
-                                          unsigned s) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
-}
-__device__ __forceinline__ float lodf_buf(__amdgpu_buffer_rsrc_t r, const uint16_t*, unsigned v,
-                                          unsigned s) {
-  return __uint_as_float((unsigned)__builtin_amdgcn_raw_buffer_load_b16(r, v, s, 0) << 16);
 }
 
 // Outage factor of the stored kind, widened to the arithmetic type.
@@ -645,7 +603,6 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     const double A = p.ctg_smax2[l] * (1.0 - 0x1p-40) - qm2;
     const double thr = A > 0.0 ? sqrt(A) * (1.0 - 0x1p-50) : -1.0;
     w.thr[(size_t)t * p.Lp + l] = thr;
-    w.fh[((size_t)(l >> 3) * T + t) * 16 + fh_col_h(l & 7)] = thr;
     const size_t TL = (size_t)T * L, e = (size_t)t * L + l;
     w.bco[0 * TL + e] = cs;
     w.bco[1 * TL + e] = sn;
@@ -808,7 +765,6 @@ __device__ void reserve_pad_block(const EvalArgs& a, const StepParams& sp, int t
   for (int l = p.L + tid; l < p.Lp; l += kBlock) {
     w.q2[(size_t)t * p.Lp + l] = 0.0;
     w.thr[(size_t)t * p.Lp + l] = -1.0;
-    w.fh[((size_t)(l >> 3) * p.T + t) * 16 + fh_col_h(l & 7)] = -1.0;
   }
   for (int k = p.K + tid; k < p.Kp; k += kBlock) w.Fk[(size_t)t * p.Kp + k] = 0.0;
 }
@@ -846,7 +802,6 @@ __device__ void flow_slab(const EvalArgs& a, int blk, double* smem) {
   const int n0 = slab * 16;
   double* F = w.F;
   double* Fk = w.Fk;
-  double* FH = w.fh;
   const int* kof = p.kof;
   const double* cload = p.cload;
   auto aload = [=](int k, int row) -> double {
@@ -858,7 +813,6 @@ __device__ void flow_slab(const EvalArgs& a, int blk, double* smem) {
     if (t < T) {
       const double f = v - cload[(size_t)t * Lp + col];
       F[(size_t)t * Lp + col] = f;
-      FH[((size_t)(col >> 3) * T + t) * 16 + fh_col_f(col & 7)] = f;
       const int k = kof[col];
       if (k >= 0) Fk[(size_t)t * Kp + k] = f;
     }
@@ -1124,430 +1078,134 @@ __global__ __launch_bounds__(512) void k_ctg_main(EvalArgs a, const LT* __restri
   }
 }
 
-// Skip test of the period-split map-reduce (FP64 factors, every contingency
-// scored).  For a half row h (branches 4h..4h+3 of an 8-branch tile) of one
-// period, |P_tlk| = |F_tl + LODF_lk F_tk| <= |F_tl| + Lm Fm, where Lm is the
-// largest |LODF| of the 4 branches over the wave's 64 contingencies (a
-// per-grid table) and Fm the largest |F_tk| of the wave's lanes and periods.
-// When |F_tl| (1 + 2^-40) + Lm Fm <= thr_tl (1 - 2^-40) holds in floating
-// point for each of the 4 branches, no element of the half row passes the
-// test |fl(P)| > thr_tl: the margins cover the rounding of the bound, of its
-// comparison and of fl(P) (a few units of 2^-53), so the half row is skipped.
-// NaN in F or thr makes the comparison false (the half row is tested).  Lane
-// e of the wavefront decides half row (period tw + i, tile t0 + j) with
-// j = e / (2 TCW), i = (e / 2) % TCW, h = e % 2; periods past the wave's last
-// are skipped (their verdicts are dropped anyway).  Returns the ballot.
+// Row-compacted form of the same map-reduce (the period-split tile, default).
 //
-// FP32 arithmetic (FP32 or BF16 factors) tests fl(P^2 + qmax2) > s_ctg^2 in
-// FP32 on FP32 roundings of F, qmax2 and s_ctg^2, and Lm is the largest
-// stored factor.  There |fl(P)| <= (Lm Fm + |F|)(1 + u)^2 and the test's
-// left side is at most ((Lm Fm + |F|)^2 + qmax2)(1 + u)^5 (u = 2^-24), so a
-// half row is skipped when (Lm Fm + |F|)^2 (1 + 2^-18) + qmax2 (1 + 2^-18)
-// <= s_ctg^2 (1 - 2^-18), computed in FP64, for each of its branches.
-template <int TCW, bool F64>
-__device__ __forceinline__ uint64_t ctg_cold_mask(const double* __restrict__ fh,
-                                                  const double* __restrict__ lmaxh, int T,
-                                                  int tw, int ntw, int tile0, int ntile, int kb,
-                                                  int nkb, double fkm,
-                                                  const double* __restrict__ q2,
-                                                  const double* __restrict__ smax2, int Lp) {
-  constexpr int CT = 32 / TCW;  // tiles per mask
-  const int e = threadIdx.x & 63;
-  const int j = e / (2 * TCW), i = (e >> 1) % TCW, h = e & 1;
-  bool cold = false;
-  if (j < CT && j < ntile) {
-    if (i >= ntw) {
-      cold = true;
-    } else {
-      const int tile = tile0 + j;
-      const double* r = fh + ((size_t)tile * T + tw + i) * 16 + 8 * h;
-      const double lm = lmaxh[(size_t)(2 * tile + h) * nkb + kb];
-      double f[4], t[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f[g] = r[g];
-        t[g] = r[4 + g];
-      }
-      cold = true;
-      if constexpr (F64) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const double s = fabs(f[g]) * (1.0 + 0x1p-40) - t[g] * (1.0 - 0x1p-40);
-          cold = cold && fma(lm, fkm, s) <= 0.0;
-        }
-      } else {
-        const int l = tile * 8 + 4 * h;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const double b = fma(lm, fkm, fabs(f[g]));
-          const double lhs = (b * b + q2[(size_t)(tw + i) * Lp + l + g]) * (1.0 + 0x1p-18);
-          cold = cold && lhs <= smax2[l + g] * (1.0 - 0x1p-18);
-        }
-      }
-    }
-  }
-  return __builtin_amdgcn_ballot_w64(cold);
+// One block covers one period and 64 contingencies (a lane each) over every
+// branch, so z_tk and S_tk are complete at its end and the block finishes
+// them itself (ctg_finish_z); the branches are split into a.nsl slices, one
+// wavefront each, whose z and S are added in slice order.  A slice takes the
+// 64-branch groups s, s + nsl, ...  For a group every lane first decides one
+// branch l by a bound: |P_tlk| = |F_tl + LODF_lk F_tk| <= |F_tl| + Lm Fm, with
+// Lm the largest |LODF_lk| of the row over the block's 64 contingencies (a
+// per-grid table, a.lmax) and Fm the largest |F_tk| of its lanes.  When
+// |F_tl| (1 + 2^-40) + Lm Fm <= thr_tl (1 - 2^-40) holds in floating point, no
+// element of the row passes the test |fl(P)| > thr_tl: the margins cover the
+// rounding of the bound, of its comparison and of fl(P) (a few units of
+// 2^-53).  NaN in F or thr makes the comparison false (the row is tested).
+// Only the rows that the ballot leaves are loaded and tested, four at a time,
+// and only rows with a flagged lane evaluate the penalty, two at a time:
+// their sums over the lanes (R = sum dP, Q = sum dq) share one reduction
+// tree.  R and Q of such rows are stored per contingency block, with one
+// 64-bit word of row flags per group; the readers consult the word first.
+// Neither the pairing of rows nor the bound changes any sum's order, so
+// testing every row (lmax null) gives bitwise the same results, as does a
+// block of fewer wavefronts than slices.
+//
+// FP64 tests |P| > thr_tl with thr_tl from k_forward, a radius a little below
+// sqrt(s_ctg^2 - qmax2_tl), so that every element the exact test
+// P^2 + qmax2 > s_ctg^2 accepts passes it; the exact test is applied again
+// when the row is evaluated.  FP32 arithmetic (FP32 or BF16 factors) tests
+// fl(P^2 + qmax2) > s_ctg^2 in FP32 on FP32 roundings of F, qmax2 and s_ctg^2,
+// and Lm is the largest stored factor.  There |fl(P)| <= (Lm Fm + |F|)(1 + u)^2
+// and the test's left side is at most ((Lm Fm + |F|)^2 + qmax2)(1 + u)^5 (u =
+// 2^-24), so a row is passed over when (Lm Fm + |F|)^2 (1 + 2^-18) + qmax2 (1 +
+// 2^-18) <= s_ctg^2 (1 - 2^-18), computed in FP64.  FP32 sums of z and S are
+// flushed to FP64 at every multiple of eight branches.
+//
+// What it measured, against a tile of eight branches and four periods per
+// wavefront whose half rows (four branches) were skipped together and whose
+// z and S went through memory to a reduction kernel (us in the step,
+// map-reduce + reduction before, this kernel now): 2000 buses x 48 periods
+// 55.6 + 10.0 -> 36, 617 x 18 9.4 + 4.8 -> 7.4, twelve grids of 100-1000 buses in a
+// batch 262 + 17 -> 48.  There 2.1 % of the rows at 2000 buses are hot, and most
+// of them in all 64 lanes (the branch is overloaded before the outage); 3.8 %
+// remain after the bound (13 % of half rows did).  At 2000 buses the vector
+// instructions bound it (they issue in about three quarters of the SIMD cycles,
+// half of them for the hot rows); at 617 buses its chain of four memory round
+// trips does.  Slower: the slices' hot rows spread evenly over the wavefronts
+// after the test (two more barriers and a lookup: 48 us, 10 us at 617 buses),
+// one list of undecided rows for four groups with F and thr by scalar loads
+// (44 us), R and Q staged in LDS (44 us).
+
+// A hot row (one with a flagged lane): the lane's post-outage flow and factor,
+// the branch (-1: none), its qmax2 and rating.
+template <typename R>
+struct HotRow {
+  R P, lod, q2, smx, smx2;
+  int l;
+};
+
+// Penalty above its floor and derivatives of the row's element in this lane,
+// 0 where the exact test fails (NaN factors, flows inside the rating).  FP64:
+// dP and dq per unit of kt and kt / 2, which are applied to the sums.
+__device__ __forceinline__ bool hot_eval(const HotRow<float>& h, float eps, float eps2, float kt,
+                                         float& z, float& dP, float& dq) {
+  const float s2 = fma(h.P, h.P, h.q2);
+  const bool m = s2 > h.smx2;
+  z = ctg_overload(h.P, m ? s2 : 1.0f, h.smx, eps, eps2, kt, dP, dq);
+  z = m ? z : 0.0f;
+  dP = m ? dP : 0.0f;
+  dq = m ? dq : 0.0f;
+  return m;
+}
+__device__ __forceinline__ bool hot_eval(const HotRow<double>& h, double eps, double eps2, double,
+                                         double& z, double& dP, double& dq) {
+  const double s2 = fma(h.P, h.P, h.q2);
+  const bool m = s2 > h.smx2;
+  const double rs = rsqrt_nr(m ? s2 : 1.0);
+  const double em = fmax(fma(s2, rs, -h.smx), 0.0);
+  const double w2 = fma(em, em, eps2);
+  // w2 = 0 only when eps = 0 and s sits exactly on the rating
+  const bool pos = m && w2 > 0.0;
+  const double rw = rsqrt_nr(pos ? w2 : 1.0);
+  z = pos ? fma(w2, rw, -eps) : 0.0;
+  dq = pos ? em * rw * rs : 0.0;
+  dP = pos ? dq * h.P : 0.0;
+  return m;
 }
 
-// Period-split form of the same map-reduce.  The wavefronts of a block share
-// one range of lt * 8 branches and split the periods: wavefront w owns the
-// periods [t0 + w TCW, t0 + (w + 1) TCW), so z_tk and S_tk of its lanes need
-// no sum over wavefronts and stay with the wavefront (in its own LDS slice)
-// over the whole branch range, and with wl * TCW >= T every outage factor is
-// read from memory once per evaluation (the block's wavefronts read the same
-// tile, served by the L1 cache).  Per period the eight tests of a tile are
-// combined before one branch; a period with a flagged lane takes the
-// per-branch path of k_ctg_main.  A group of 64 z/S partials or of 8 R/Q
-// partials is stored only when not all zero, with a byte flag per group
-// (w.zflag, w.rflag) that the readers consult first.
-//
-// FP64: the test is |P| > thr_tl with thr_tl from k_forward, a radius a
-// little below sqrt(s_ctg^2 - qmax2_tl), so that every element the exact
-// test P^2 + qmax2 > s_ctg^2 accepts passes it (one FMA and one compare per
-// element); the exact test is applied again on the per-branch path.  F_tl
-// and thr_tl reach SGPRs by scalar loads issued one period ahead.  FP32
-// arithmetic keeps the exact test with F and qmax2 moved to SGPRs by
-// v_readlane from a per-tile lane load (lane e: period e / 8, branch e % 8).
-//
-// The batched launch (k_ctg_pm_b) runs the same block code for each work
-// item; it is written out in both kernels rather than shared through an
-// inlined function, which made the compiler spill about three times as many
-// SGPRs and the map-reduce 1.5x slower.  Batched and single steps are checked
-// to agree bit for bit.
-template <int TCW, typename LT, bool SKIP>
-__global__ __launch_bounds__(512) void k_ctg_pm(EvalArgs a, const LT* __restrict__ lodf) {
-  typedef typename std::conditional<std::is_same<LT, double>::value, double, float>::type R;
-  constexpr bool kF64 = std::is_same<R, double>::value;
-  const DevProblem& p = a.p;
-  const DevWork& w = a.w;
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int WL = blockDim.x >> 6;
-  const int lb = blockIdx.x, kb = blockIdx.y;
-  const int T = p.T, Lp = p.Lp, Kp = p.Kp;
-  const int tw = (blockIdx.z * WL + wv) * TCW;  // first period of the wavefront
-  const int ntw = min(TCW, T - tw);
-  if (ntw <= 0) return;  // no barrier follows
-  const int k = kb * 64 + lane;  // slot of the lane
-  const int kc = a.act_k ? a.act_k[k] : k;
-  // z and S of the wavefront's (period, lane) pairs live in its own slice
-  // of LDS: only the per-branch path and the final store touch them
-  extern __shared__ double dyn[];
-  double* zsh = dyn + (size_t)wv * TCW * 128;
-  double* ssh = zsh + TCW * 64;
-  R fk[TCW];
-#pragma unroll
-  for (int i = 0; i < TCW; ++i) {
-    fk[i] = i < ntw ? (R)w.Fk[(size_t)(tw + i) * Kp + kc] : R(0);
-    zsh[i * 64 + lane] = 0.0;
-    ssh[i * 64 + lane] = 0.0;
-  }
-  const cdouble* Sc = as_const(p.ctg_smax2);
-  const cdouble* Mc = as_const(p.ctg_smax);
-  const cdouble* Dc = as_const(p.dt);
-  const cdouble* Qc = as_const(w.q2);
-  const cdouble* FH = as_const(w.fh);
-  const double beta = w.params[PB_BETA];
-  const R eps = (R)w.params[PB_EPS];
-  const R eps2 = eps * eps;
-  const int ei = lane >> 3, eg = lane & 7;
-  const int l0 = lb * a.lt * 8;
-  const int l1 = min(Lp, l0 + a.lt * 8);
-  // The factor loads of the tile loop go through a buffer resource over
-  // the block's rows: the lane's fixed 32-bit byte offset (its slot k) plus
-  // a uniform row offset that advances with the tile, so the loop needs no
-  // per-lane address arithmetic.
-  unsigned rowb = (unsigned)a.kst * (unsigned)sizeof(LT);  // bytes per factor row
-  const __amdgpu_buffer_rsrc_t lrs =
-      buf_rsrc(lodf + (size_t)l0 * a.kst, (unsigned)(l1 - l0) * rowb);
-  const unsigned koff = (unsigned)k * (unsigned)sizeof(LT);
-  // R/Q flags of the lane's period (lane e < ntw: period tw + e), bit i for
-  // tile i of the block, stored after the loop
-  uint64_t fbits = 0;
-  // SKIP: half rows proved free of overloads are skipped (ctg_cold_mask),
-  // with FP64 factors, every contingency scored and a block of at most
-  // 64 / TCW tiles (two masks of 32 / TCW tiles cover them; the host
-  // launches the SKIP form only then, and a block outside it tests
-  // everything); the F and thr of a tested half row are loaded when it is
-  // reached.  Otherwise they are prefetched one half row ahead.
-  // Bit ((ti mod CT) TCW + i) 2 + h of mask ti / CT (CT = 32 / TCW): half
-  // row h of period tw + i of tile ti skipped.
-  uint64_t coldm = 0, coldm1 = 0;
-  if constexpr (SKIP) {
-    constexpr int CT = 32 / TCW;  // tiles per mask
-    const int ntile = (l1 - l0) >> 3;
-    if (p.lmaxh != nullptr && a.act_k == nullptr && ntile <= 2 * CT) {
-      double fkm = 0.0;  // largest |F_tk| of the wave's lanes and periods
-#pragma unroll
-      for (int i = 0; i < TCW; ++i) fkm = fmax(fkm, fabs(fk[i]));
-      fkm = wave_max(fkm);
-      coldm = ctg_cold_mask<TCW, kF64>(w.fh, p.lmaxh, T, tw, ntw, l0 >> 3, ntile, kb, Kp >> 6,
-                                       fkm, w.q2, p.ctg_smax2, Lp);
-      if (ntile > CT)
-        coldm1 = ctg_cold_mask<TCW, kF64>(w.fh, p.lmaxh, T, tw, ntw, (l0 >> 3) + CT, ntile - CT,
-                                          kb, Kp >> 6, fkm, w.q2, p.ctg_smax2, Lp);
-    }
-  }
-  // F and thr of the next half row (four branches of one period) to be
-  // tested, from the branch-tiled copy, so that every prefetch is a fixed
-  // offset from the tile's row of period tw
-  double Fn[4], Hn[4];
-  if constexpr (kF64 && !SKIP) {
-    const cdouble* r = FH + ((size_t)(l0 >> 3) * T + tw) * 16;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      Fn[g] = r[g];
-      Hn[g] = r[4 + g];
-    }
-  }
-  const uint32_t live = (1u << ntw) - 1u;  // the wave's periods among the TCW tested
-  unsigned lso = 0;  // uniform offset of the tile's factor rows
-  int ti = 0;        // tile index in the block
-  // rows of the branch-tiled copy: period tw of the tile, of the next tile
-  const cdouble* cur = FH + ((size_t)(l0 >> 3) * T + tw) * 16;
-  unsigned fstep = (unsigned)T * 16u;
-  for (int lbase = l0; lbase < l1; lbase += 8, lso += 8 * rowb, ++ti, cur += fstep) {
-    // the strides are taken as changing in every tile, so that nothing
-    // derived from them is hoisted out of the loop (such values took SGPRs
-    // that were then spilled, and reloading them costs vector instructions)
-    asm volatile("" : "+s"(rowb), "+s"(fstep));
-    const cdouble* nxt = cur + fstep;
-    // the tile's half rows that are tested (bit 2 i + h); a tile without
-    // any is passed over, and only the factor rows of tested halves are loaded
-    const uint32_t need =
-        ~(uint32_t)((ti < 32 / TCW ? coldm : coldm1) >> ((ti % (32 / TCW)) * TCW * 2)) &
-        ((1u << (2 * TCW)) - 1u);
-    if (need == 0) continue;
-    R lod[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      lod[j] = (need & (j < 4 ? 0x5555u : 0xAAAAu)) ? lodf_buf(lrs, lodf, koff, lso + j * rowb) : R(0);
-    R fv = R(0), qv = R(0), smx2[8];
-    if constexpr (!kF64) {
-      if (ei < ntw) {
-        const size_t e = (size_t)(tw + ei) * Lp + lbase + eg;
-        fv = (R)w.F[e];
-        qv = (R)w.q2[e];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) smx2[j] = (R)Sc[lbase + j];
-    }
-    // The test of every (period, branch, lane) of the tile, without a
-    // branch: all TCW periods are tested (the rows past the wave's last
-    // period are spare rows of the array, and their verdicts are dropped
-    // with the mask), and each period's verdict is one bit of hotm.
-    uint32_t hotm = 0;
-#pragma unroll
-    for (int i = 0; i < TCW; ++i) {
-      uint64_t hot = 0;
-      if constexpr (SKIP && kF64) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if ((need >> (2 * i + h)) & 1u) {
-            double Fr[4], Hr[4];
-            const cdouble* q = cur + 16 * i + 8 * h;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              Fr[g] = q[g];
-              Hr[g] = q[4 + g];
-            }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              const double P = fma_uniform_c(lod[4 * h + g], fk[i], Fr[g]);
-              hot |= __builtin_amdgcn_ballot_w64(fabs(P) > Hr[g]);
-            }
-          }
-        }
-      } else if constexpr (kF64) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          double Fr[4], Hr[4];
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            Fr[g] = Fn[g];
-            Hr[g] = Hn[g];
-          }
-          // prefetch: the other half of this period's row, else the next
-          // period of this tile, else period tw of the next tile (rows past
-          // the tile or the last tile are spare rows)
-          const cdouble* q = h == 0 ? cur + 16 * i + 8 : (i + 1 < TCW) ? cur + 16 * (i + 1) : nxt;
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            Fn[g] = q[g];
-            Hn[g] = q[4 + g];
-          }
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const double P = fma_uniform_c(lod[4 * h + g], fk[i], Fr[g]);
-            hot |= __builtin_amdgcn_ballot_w64(fabs(P) > Hr[g]);
-          }
-        }
-      } else {
-        // FP32 arithmetic; with SKIP only the half rows that are tested
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if ((need >> (2 * i + h)) & 1u) {
-#pragma unroll
-            for (int gg = 0; gg < 4; ++gg) {
-              const int g = 4 * h + gg;
-              const R Fr = readlane_any(fv, i * 8 + g);
-              const R P = fma_uniform_c(lod[g], fk[i], Fr);
-              const R s2 = fma_uniform_c(P, P, readlane_any(qv, i * 8 + g));
-              hot |= __builtin_amdgcn_ballot_w64(s2 > smx2[g]);
-            }
-          }
-        }
-      }
-      hotm |= (hot != 0 ? 1u : 0u) << i;
-    }
-    hotm &= live;
-    // a wave with fewer than TCW periods prefetched a spare row for the
-    // next tile: load its first period's row again
-    if constexpr (kF64 && !SKIP) {
-      if (ntw < TCW) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          Fn[g] = nxt[g];
-          Hn[g] = nxt[4 + g];
-        }
-      }
-    }
-    if (hotm) {
-      // R and Q of (period tw + e / 8, branch lbase + e % 8) gather in lane e
-      R racc = R(0), qacc = R(0);
-      // the overloaded periods of the tile: the per-branch path, with F,
-      // qmax2 and the ratings loaded again
-#pragma unroll
-      for (int i = 0; i < TCW; ++i) {
-        if ((hotm >> i) & 1u) {
-          const R kt = (R)(Dc[tw + i] * p.c_s * beta);
-          R Fr[8], Qr[8], Sr[8];
-#pragma unroll
-          for (int g = 0; g < 8; ++g) {
-            if constexpr (kF64) {
-              Fr[g] = cur[16 * i + fh_col_f(g)];
-              Qr[g] = Qc[(size_t)(tw + i) * Lp + lbase + g];
-              Sr[g] = Sc[lbase + g];
-            } else {
-              Fr[g] = readlane_any(fv, i * 8 + g);
-              Qr[g] = readlane_any(qv, i * 8 + g);
-              Sr[g] = smx2[g];
-            }
-          }
-          R zt = R(0), st = R(0);
-#pragma unroll
-          for (int g = 0; g < 8; ++g) {
-            // a skipped half row holds no overload (and its factors were
-            // not loaded)
-            if (((need >> (2 * i + (g >> 2))) & 1u) == 0) continue;
-            // the flow formed again (the same fused operation, so the same
-            // value as in the test)
-            const R P = fma_uniform_c(lod[g], fk[i], Fr[g]);
-            const R s2 = fma_uniform_c(P, P, Qr[g]);
-            if (__builtin_amdgcn_ballot_w64(s2 > Sr[g])) {
-              R dP = R(0), dq = R(0);
-              if (s2 > Sr[g]) {
-                zt += ctg_overload(P, s2, (R)Mc[lbase + g], eps, eps2, kt, dP, dq);
-                st = fma(lod[g], dP, st);
-              }
-              const R r = pair_sum(dP, dq);  // lane 0: sum of dP, lane 32: of dq
-              racc = writelane_set(racc, readlane_any(r, 0), i * 8 + g);
-              qacc = writelane_set(qacc, readlane_any(r, 32), i * 8 + g);
-            }
-          }
-          zsh[i * 64 + lane] += (double)zt;
-          ssh[i * 64 + lane] += (double)st;
-        }
-      }
-      // per (period, 8 branches): stored only when not all zero, and flagged
-      const uint64_t b = __builtin_amdgcn_ballot_w64(racc != R(0) || qacc != R(0));
-      if (lane < ntw && ((b >> (8 * lane)) & 0xFF) != 0) fbits |= (uint64_t)1 << ti;
-      if (b != 0 && lane < ntw * 8 && ((b >> (lane & ~7)) & 0xFF) != 0) {
-        const size_t o = ((size_t)kb * T + tw + ei) * Lp + lbase + eg;
-        w.rpart[o] = (double)racc;
-        w.qpart[o] = (double)qacc;
-      }
-    }
-  }
-  if (lane < ntw) {
-    uint8_t* f = w.rflag + ((size_t)(tw + lane) * (Lp / 8) + (l0 >> 3)) * a.rfs + kb;
-    for (int i = 0; i < ti; ++i) f[(size_t)i * a.rfs] = (uint8_t)((fbits >> i) & 1u);
-  }
-#pragma unroll
-  for (int i = 0; i < TCW; ++i) {
-    if (i < ntw) {
-      // stored only when not all zero, and flagged
-      const double z = zsh[i * 64 + lane], s2 = ssh[i * 64 + lane];
-      const bool nz = __builtin_amdgcn_ballot_w64(z != 0.0 || s2 != 0.0) != 0;
-      if (lane == 0) w.zflag[((size_t)(tw + i) * a.zfk + kb) * a.zfs + lb] = (uint8_t)nz;
-      if (nz) {
-        const size_t o = ((size_t)lb * T + tw + i) * Kp + k;
-        w.zpart[o] = z;
-        w.spart[o] = s2;
-      }
-    }
-  }
+// Wavefront totals of two rows' dP and dq at once: lanes 0..15 return the sum
+// of pa, lanes 16..31 of pb, 32..47 of qa, 48..63 of qb, each summed over the
+// 64 lanes by pair_sum's tree.
+__device__ __forceinline__ double quad_sum(double pa, double qa, double pb, double qb) {
+  double v = swap_add<16>(swap_add<32>(pa, qa), swap_add<32>(pb, qb));
+  v += dpp_f64_row<0xB1>(v);
+  v += dpp_f64_row<0x4E>(v);
+  v += dpp_f64_row<0x141>(v);
+  v += dpp_f64_row<0x140>(v);
+  return v;
+}
+__device__ __forceinline__ float quad_sum(float pa, float qa, float pb, float qb) {
+  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(pa), __float_as_uint(qa), false,
+                                                  false);
+  const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(pb), __float_as_uint(qb), false,
+                                                  false);
+  const float a = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  const float b = __uint_as_float(y[0]) + __uint_as_float(y[1]);
+  const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  float v = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+  v += dpp_f32<0xB1>(v);
+  v += dpp_f32<0x4E>(v);
+  v += dpp_f32<0x141>(v);
+  v += dpp_f32<0x140>(v);
+  return v;
 }
 
-
-// ---------------------------------------------------------------------------
-// K4: per-(t, k) penalties z_tk (the l-block partials plus the floor
-// (L-1) eps), the mean outage-correction derivative, and per 64-contingency
-// chunk the worst penalty (smallest index on ties) and the sum.  One 64-thread
-// block per (chunk, t); all partial loads of a lane are in flight together.
-
-// flagged l-block partials loaded together by the sparse reduction
-constexpr int kZredBatch = 32;
-
-template <bool SPARSE>
-__device__ __forceinline__ void ctg_zred_body(const EvalArgs& a, int kc, int t) {
+// z_tk of the block's 64 slots from their sums over the branches (plus the
+// floor (L-1) eps), and the chunk's worst penalty (smallest index on ties)
+// and sum; one wavefront, lane = slot.
+__device__ __forceinline__ void ctg_finish_z(const EvalArgs& a, int kc, int t, double kt,
+                                             double eps, double zs) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
-  const int lane = threadIdx.x;
-  const int T = p.T, L = p.L, K = p.K, Kp = p.Kp;
-  const double eps = w.params[PB_EPS], beta = w.params[PB_BETA];
-  const double kt = p.dt[t] * p.c_s * beta;
-  const int s = kc * 64 + lane;  // slot
-  const size_t o = (size_t)t * Kp + s;
-  const size_t stride = (size_t)T * Kp;
-  // the l-block partials in l-block order; after the period-split
-  // map-reduce only the flagged ones (the others are all zero), up to 32 of
-  // each in flight
-  double zs = 0.0, ss = 0.0;
-  if constexpr (!SPARSE) {
-    zs = strided_sum<16>(w.zpart + o, a.nLb, stride);
-    ss = strided_sum<16>(w.spart + o, a.nLb, stride);
-  }
-  const uint8_t* zf = w.zflag + ((size_t)t * a.zfk + kc) * a.zfs;
-  for (int b0 = 0; SPARSE && b0 < a.nLb; b0 += 64) {
-    uint64_t m = __builtin_amdgcn_ballot_w64(b0 + lane < a.nLb && zf[b0 + lane] != 0);
-    while (m) {
-      int idx[kZredBatch];
-#pragma unroll
-      for (int u = 0; u < kZredBatch; ++u) {
-        idx[u] = m ? b0 + __builtin_ctzll(m) : -1;
-        m &= m - 1;
-      }
-      double vz[kZredBatch], vs[kZredBatch];
-#pragma unroll
-      for (int u = 0; u < kZredBatch; ++u) {
-        vz[u] = idx[u] >= 0 ? w.zpart[o + (size_t)idx[u] * stride] : 0.0;
-        vs[u] = idx[u] >= 0 ? w.spart[o + (size_t)idx[u] * stride] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < kZredBatch; ++u) {
-        zs += vz[u];
-        ss += vs[u];
-      }
-    }
-  }
+  const int lane = threadIdx.x & 63, s = kc * 64 + lane;
   double z = -DBL_MAX, zsum = 0.0;
   int idx = INT_MAX;
   if (s < a.na) {
     const int k = a.act_k ? a.act_k[s] : s;
-    z = kt * ((double)(L - 1) * eps + zs);
-    w.zval[(size_t)t * Kp + k] = z;
-    w.smean[o] = p.ctg_sum ? ss : ss / (double)K;
+    z = kt * ((double)(p.L - 1) * eps + zs);
+    w.zval[(size_t)t * p.Kp + k] = z;
     idx = k;
     zsum = z;
   }
@@ -1561,9 +1219,191 @@ __device__ __forceinline__ void ctg_zred_body(const EvalArgs& a, int kc, int t) 
   }
 }
 
-template <bool SPARSE>
+// The mean outage-correction derivative of the block's slots.
+__device__ __forceinline__ void ctg_finish_s(const EvalArgs& a, int kc, int t, double ss) {
+  const int s = kc * 64 + (threadIdx.x & 63);
+  if (s < a.na)
+    a.w.smean[(size_t)t * a.p.Kp + s] = a.p.ctg_sum ? ss : ss / (double)a.p.K;
+}
+
+// LT: storage type of the outage factors; lds: a.nsl x 128 doubles.
+template <typename LT>
+__device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* lds) {
+  typedef typename std::conditional<std::is_same<LT, double>::value, double, float>::type R;
+  constexpr bool kF64 = std::is_same<R, double>::value;
+  const DevProblem& p = a.p;
+  const DevWork& w = a.w;
+  const LT* __restrict__ lodf = static_cast<const LT*>(a.lodf_sel);
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int T = p.T, L = p.L, Lp = p.Lp, ng = Lp >> 6;
+  const int kb = b / T, t = b - kb * T;
+  const unsigned k = (unsigned)(kb * 64 + lane);  // slot of the lane
+  const double* __restrict__ Ft = w.F + (size_t)t * Lp;
+  const double* __restrict__ Ht = (kF64 ? w.thr : w.q2) + (size_t)t * Lp;  // thr, or qmax2
+  const double* __restrict__ lmax = a.lmax ? a.lmax + (size_t)kb * Lp : nullptr;
+  // F, thr and the largest factor of a lane's branch in the first group, in
+  // flight with the outaged branches' flows; later groups' one group ahead
+  double Fn = 0.0, Hn = 0.0, Mn = 0.0;
+  auto prefetch = [&](int g) {
+    if (g < ng) {
+      const int l = g * 64 + lane;
+      Fn = Ft[l];
+      Hn = Ht[l];
+      if (lmax) Mn = lmax[l];
+    }
+  };
+  prefetch(wv);
+  const R fk = (R)w.Fk[(size_t)t * p.Kp + (a.act_k ? a.act_k[k] : (int)k)];
+  const double deps = w.params[PB_EPS];
+  const double dkt = p.dt[t] * p.c_s * w.params[PB_BETA];
+  const R eps = (R)deps, eps2 = eps * eps, kt = (R)dkt;
+  const double fkm = wave_max(fabs((double)fk));
+  // lane 0 stores R and lane 32 Q of a pair's first row, lanes 16 and 48
+  // those of the second
+  double* __restrict__ rq = w.rq + ((size_t)t * Lp * a.rqs + kb) * 2 + (lane >> 5);
+  const double rqk = !kF64 ? 1.0 : lane < 32 ? dkt : 0.5 * dkt;
+  for (int s = wv; s < a.nsl; s += nw) {
+    double zacc = 0.0, sacc = 0.0;
+    R zt = R(0), st = R(0);  // FP32 only: sums of the current eight branches
+    int tile = -1;
+    HotRow<R> pend;
+    pend.l = -1;
+    auto add = [&](const HotRow<R>& h, bool m, R z, R dP) {
+      if constexpr (kF64) {
+        zacc += z;
+        sacc = m ? fma(h.lod, dP, sacc) : sacc;
+      } else {
+        if ((h.l >> 3) != tile) {
+          zacc += (double)zt;
+          sacc += (double)st;
+          zt = st = R(0);
+          tile = h.l >> 3;
+        }
+        zt += z;
+        st = m ? fma(h.lod, dP, st) : st;
+      }
+    };
+    auto flush = [&](const HotRow<R>& h0, const HotRow<R>& h1) {
+      R z, p0, q0, p1 = R(0), q1 = R(0);
+      const bool m0 = hot_eval(h0, eps, eps2, kt, z, p0, q0);
+      add(h0, m0, z, p0);
+      if (h1.l >= 0) {
+        const bool m1 = hot_eval(h1, eps, eps2, kt, z, p1, q1);
+        add(h1, m1, z, p1);
+      }
+      const R v = quad_sum(p0, q0, p1, q1);
+      const int row = (lane & 16) ? h1.l : h0.l;
+      if ((lane & 15) == 0 && row >= 0) rq[(size_t)row * a.rqs * 2] = (double)v * rqk;
+    };
+    if (s != wv) prefetch(s);
+    for (int g = s; g < ng; g += a.nsl) {
+      const int l = g * 64 + lane;
+      const double F = Fn, H = Hn, M = Mn;
+      const double smx = p.ctg_smax[l];
+      double q2 = H;
+      if constexpr (kF64) q2 = w.q2[(size_t)t * Lp + l];
+      prefetch(g + a.nsl);
+      bool cold = false;
+      if (lmax) {
+        if constexpr (kF64) {
+          const double e = fabs(F) * (1.0 + 0x1p-40) - H * (1.0 - 0x1p-40);
+          cold = fma(M, fkm, e) <= 0.0;
+        } else {
+          const double e = fma(M, fkm, fabs(F));
+          cold = (e * e + q2) * (1.0 + 0x1p-18) <= smx * smx * (1.0 - 0x1p-18);
+        }
+      }
+      uint64_t und = __builtin_amdgcn_ballot_w64(l < L && !cold), hot = 0;
+      while (und) {
+        constexpr int U = 4;
+        int r[U];
+        R lod[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          r[u] = und ? __builtin_ctzll(und) : -1;
+          und &= und - 1;  // 0 stays 0
+          if (r[u] >= 0) lod[u] = lodf_load(lodf + (size_t)(g * 64 + r[u]) * a.kst, k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (r[u] < 0) break;
+          HotRow<R> h;
+          h.P = fma(lod[u], fk, (R)readlane_f64(F, r[u]));
+          bool over;
+          if constexpr (kF64) {
+            over = fabs(h.P) > readlane_f64(H, r[u]);
+          } else {
+            const double m = readlane_f64(smx, r[u]);
+            h.q2 = (R)readlane_f64(H, r[u]);
+            h.smx2 = (R)(m * m);
+            over = fma(h.P, h.P, h.q2) > h.smx2;
+          }
+          if (__builtin_amdgcn_ballot_w64(over) == 0) continue;
+          hot |= (uint64_t)1 << r[u];
+          const double m = readlane_f64(smx, r[u]);
+          h.smx = (R)m;
+          if constexpr (kF64) {
+            h.q2 = readlane_f64(q2, r[u]);
+            h.smx2 = m * m;
+          }
+          h.lod = lod[u];
+          h.l = g * 64 + r[u];
+          if (pend.l < 0) {
+            pend = h;
+          } else {
+            flush(pend, h);
+            pend.l = -1;
+          }
+        }
+      }
+      if (lane == 0) w.hot[((size_t)t * ng + g) * a.rqs + kb] = hot;
+    }
+    if (pend.l >= 0) {
+      HotRow<R> none;
+      none.l = -1;
+      flush(pend, none);
+    }
+    lds[s * 128 + lane] = zacc + (double)zt;
+    lds[s * 128 + 64 + lane] = sacc + (double)st;
+  }
+  __syncthreads();
+  // z by the first wavefront, S by the second (or the first again)
+  for (int half = wv; half < 2; half += nw) {
+    double v = 0.0;
+    for (int s = 0; s < a.nsl; ++s) v += lds[s * 128 + half * 64 + lane];
+    if (half == 0)
+      ctg_finish_z(a, kb, t, dkt, deps, v);
+    else
+      ctg_finish_s(a, kb, t, kF64 ? v * dkt : v);
+  }
+}
+
+// Blocks (contingency block, period), XCD-grouped: the periods of one
+// contingency block read the same factor rows through one L2.
+template <typename LT>
+__global__ __launch_bounds__(1024) void k_ctg_rows(EvalArgs a) {
+  extern __shared__ double dyn[];
+  ctg_rows_body<LT>(a, xcd_group(blockIdx.x, gridDim.x), dyn);
+}
+
+// ---------------------------------------------------------------------------
+// K4 (branch-stacked tile only): per-(t, k) penalties z_tk from the l-block
+// partials, the mean outage-correction derivative, and per 64-contingency
+// chunk the worst penalty and the sum.  One 64-thread block per (chunk, t).
+
 __global__ __launch_bounds__(64) void k_ctg_zred(EvalArgs a) {
-  ctg_zred_body<SPARSE>(a, blockIdx.x, blockIdx.y);
+  const DevProblem& p = a.p;
+  const DevWork& w = a.w;
+  const int kc = blockIdx.x, t = blockIdx.y;
+  const double kt = p.dt[t] * p.c_s * w.params[PB_BETA];
+  const size_t o = (size_t)t * p.Kp + kc * 64 + threadIdx.x;
+  const size_t stride = (size_t)p.T * p.Kp;
+  // the l-block partials in l-block order, 16 of each in flight
+  const double zs = strided_sum<16>(w.zpart + o, a.nLb, stride);
+  const double ss = strided_sum<16>(w.spart + o, a.nLb, stride);
+  ctg_finish_s(a, kc, t, ss);
+  ctg_finish_z(a, kc, t, kt, w.params[PB_EPS], zs);
 }
 
 // ---------------------------------------------------------------------------
@@ -1574,7 +1414,66 @@ __global__ __launch_bounds__(64) void k_ctg_zred(EvalArgs a) {
 // outage-correction term S* = sum_l LODF_lk* dP_tlk* belongs to dL/dF at the
 // outaged branch and is applied in k_final as a rank-1 term (per-chunk sums).
 
-template <bool SPARSE>
+// OR of a 64-bit word over the 64 lanes of a wavefront, in every lane.
+__device__ __forceinline__ uint64_t wave_or(uint64_t v) {
+  unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+#define QG_OR_STEP(CTRL)                                                        \
+  lo |= (unsigned)__builtin_amdgcn_mov_dpp((int)lo, CTRL, 0xF, 0xF, false);     \
+  hi |= (unsigned)__builtin_amdgcn_mov_dpp((int)hi, CTRL, 0xF, 0xF, false);
+  QG_OR_STEP(0xB1)   // quad_perm [1,0,3,2]
+  QG_OR_STEP(0x4E)   // quad_perm [2,3,0,1]
+  QG_OR_STEP(0x141)  // row_half_mirror
+  QG_OR_STEP(0x140)  // row_mirror
+#undef QG_OR_STEP
+  uint64_t r = 0;
+  for (int row = 0; row < 64; row += 16)
+    r |= ((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)hi, row) << 32) |
+         (unsigned)__builtin_amdgcn_readlane((int)lo, row);
+  return r;
+}
+
+// R and Q of the wavefront's 64 branches (lane = branch l of period t) from
+// the map-reduce's per-contingency-block sums.  Few branches hold any, and
+// those that do mostly hold one in every block, so each is summed across the
+// lanes (lane = contingency block, one 16-byte load each), four branches'
+// loads in flight together.
+__device__ __forceinline__ void gather_rq(const EvalArgs& a, int t, int g, double& r, double& q) {
+  const DevProblem& p = a.p;
+  const int lane = threadIdx.x & 63;
+  const int ng = p.Lp >> 6;
+  for (int c0 = 0; c0 < a.nKb; c0 += 64) {
+    const bool in = c0 + lane < a.nKb;
+    const uint64_t word =
+        in ? a.w.hot[((size_t)t * ng + g) * a.rqs + c0 + lane] : (uint64_t)0;
+    uint64_t any = wave_or(word);
+    const double2* src = reinterpret_cast<const double2*>(a.w.rq) +
+                         ((size_t)t * p.Lp + g * 64) * a.rqs + c0 + lane;
+    while (any) {
+      constexpr int U = 4;
+      int row[U];
+      double2 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        row[u] = any ? __builtin_ctzll(any) : -1;
+        any &= any - 1;  // 0 stays 0
+        v[u] = double2{0.0, 0.0};
+        if (row[u] >= 0 && ((word >> row[u]) & 1)) v[u] = src[(size_t)row[u] * a.rqs];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (row[u] < 0) break;
+        const double s = pair_sum(v[u].x, v[u].y);
+        const double rs = readlane_f64(s, 0), qs = readlane_f64(s, 32);
+        if (lane == row[u]) {
+          r += rs;
+          q += qs;
+        }
+      }
+    }
+  }
+}
+
+template <bool SPLIT>
 __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
@@ -1600,8 +1499,7 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
     // per-chunk worst penalties and sums: chunk c0 + u in lane u (vector
     // loads, issued first), combined by wavefront reductions (the argmax is
     // a total order, the sum has a fixed order); then the k-block partials
-    // of R and Q in k-block order, 16 of each in flight together.  Without
-    // contingencies the partials were never written.
+    // of R and Q.  Without contingencies the partials were never written.
     const int lane = tid & 63;
     double zmax = -DBL_MAX, zsum = 0.0;
     int kstar = INT_MAX;
@@ -1613,27 +1511,14 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
       ci = (int)w.zargp[ob + lane];
       cs = w.zsump[ob + lane];
     }
-    // after the period-split map-reduce only the flagged k-block partials
-    // were stored (the others are zero): the flags of the branch's group of
-    // 8 first, 16 k-blocks per load
-    const size_t st = (size_t)T * Lp;
-    const uint8_t* rf = w.rflag + ((size_t)t * (Lp / 8) + l / 8) * a.rfs;
-    for (int c0 = 0; c0 < a.nKb; c0 += 16) {
-      uint4 f4 = make_uint4(~0u, ~0u, ~0u, ~0u);
-      if constexpr (SPARSE)
-        f4 = hasl ? *reinterpret_cast<const uint4*>(rf + c0) : make_uint4(0u, 0u, 0u, 0u);
-      const uint32_t fw[4] = {f4.x, f4.y, f4.z, f4.w};
-      double vr[16], vq[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const bool ib = hasl && c0 + u < a.nKb && ((fw[u >> 2] >> (8 * (u & 3))) & 0xFFu) != 0;
-        vr[u] = ib ? w.rpart[o + (size_t)(c0 + u) * st] : 0.0;
-        vq[u] = ib ? w.qpart[o + (size_t)(c0 + u) * st] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        r += vr[u];
-        q += vq[u];
+    if constexpr (SPLIT) {
+      const int g = lc * (kBlock / 64) + (tid >> 6);
+      if (g < (Lp >> 6)) gather_rq(a, t, __builtin_amdgcn_readfirstlane(g), r, q);
+    } else {
+      const size_t st = (size_t)T * Lp;
+      if (hasl) {
+        r = strided_sum<16>(w.rpart + o, a.nKb, st);
+        q = strided_sum<16>(w.qpart + o, a.nKb, st);
       }
     }
     for (int c0 = 0; c0 < a.nKc; c0 += 64) {
@@ -1697,7 +1582,7 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
 // kernel resolved them; nsl slices per period); then nLc T blocks of flow
 // adjoints of (period, 256-branch chunk); then the nb_bus power-balance
 // blocks, which only need the forward flows.
-template <bool SPARSE>
+template <bool SPLIT>
 __device__ __forceinline__ void ctg_asm_body(const EvalArgs& a, int b, int nblocks,
                                              double* smem) {
   const int T = a.p.T, nasm = a.nLc * T;
@@ -1719,16 +1604,16 @@ __device__ __forceinline__ void ctg_asm_body(const EvalArgs& a, int b, int nbloc
     // XCD-grouped: the blocks of consecutive periods store the transposed
     // flow adjoints gfT[l][t] of the same branches through one L2
     const int g = xcd_group(b - nper, nasm);
-    ctg_assemble<SPARSE>(a, g / a.nLc, g % a.nLc, smem);
+    ctg_assemble<SPLIT>(a, g / a.nLc, g % a.nLc, smem);
   } else {
     bus_balance(a, b - nper - nasm, smem);
   }
 }
 
-template <bool SPARSE>
+template <bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_ctg_asm(EvalArgs a) {
   __shared__ double smem[2 * kSegChunk + 16];
-  ctg_asm_body<SPARSE>(a, blockIdx.x, gridDim.x, smem);
+  ctg_asm_body<SPLIT>(a, blockIdx.x, gridDim.x, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -2032,49 +1917,16 @@ void launch_ctg_main(int bl, dim3 grid, dim3 block, hipStream_t s, const EvalArg
   }
 }
 
-// The map-reduce takes the skip test (ctg_cold_mask) with every contingency
-// scored and blocks of 4 to 64 / TCW branch tiles: with fewer tiles per
-// block the mask's cost is not recovered.
-constexpr int kSkipMinTiles = 4;
-inline bool ctg_skip(const EvalArgs& a, int tcw) {
-  return a.p.lmaxh != nullptr && a.act_k == nullptr && a.lt >= kSkipMinTiles && a.lt <= 64 / tcw;
-}
-
-template <int TCW, typename LT>
-void launch_ctg_pm_t(dim3 grid, dim3 block, hipStream_t s, const EvalArgs& a, const LT* lodf) {
-  // z and S of every (wavefront, period, lane)
-  const size_t lds = (size_t)(block.x / 64) * TCW * 128 * sizeof(double);
-  if (ctg_skip(a, TCW)) {
-    hipLaunchKernelGGL((k_ctg_pm<TCW, LT, true>), grid, block, lds, s, a, lodf);
-    return;
-  }
-  hipLaunchKernelGGL((k_ctg_pm<TCW, LT, false>), grid, block, lds, s, a, lodf);
-}
-
-template <typename LT>
-void launch_ctg_pm(int tcw, dim3 grid, dim3 block, hipStream_t s, const EvalArgs& a,
-                   const LT* lodf) {
-  switch (tcw) {
-    case 1: launch_ctg_pm_t<1>(grid, block, s, a, lodf); break;
-    case 2: launch_ctg_pm_t<2>(grid, block, s, a, lodf); break;
-    case 3: launch_ctg_pm_t<3>(grid, block, s, a, lodf); break;
-    case 4: launch_ctg_pm_t<4>(grid, block, s, a, lodf); break;
-    case 5: launch_ctg_pm_t<5>(grid, block, s, a, lodf); break;
-    case 6: launch_ctg_pm_t<6>(grid, block, s, a, lodf); break;
-    case 7: launch_ctg_pm_t<7>(grid, block, s, a, lodf); break;
-    default: launch_ctg_pm_t<8>(grid, block, s, a, lodf); break;
-  }
-}
-
 template <typename LT>
 void launch_ctg(const Problem* pr, hipStream_t s, const EvalArgs& a, const LT* lodf) {
   const CtgTile& t = pr->tile;
-  const int span = t.split ? t.wl * t.tc : t.tc;
-  const dim3 grid(pr->nLb, a.nKb, (pr->T + span - 1) / span), block(64 * t.wl);
-  if (t.split)
-    launch_ctg_pm(t.tc, grid, block, s, a, lodf);
-  else
-    launch_ctg_main(t.bl, grid, block, s, a, lodf);
+  if (t.split) {
+    hipLaunchKernelGGL(k_ctg_rows<LT>, dim3(a.nKb * pr->T), dim3(64 * a.nsl),
+                       (size_t)a.nsl * 128 * sizeof(double), s, a);
+    return;
+  }
+  launch_ctg_main(t.bl, dim3(pr->nLb, a.nKb, (pr->T + t.tc - 1) / t.tc), dim3(64 * t.wl), s, a,
+                  lodf);
 }
 
 static EvalArgs make_args(const Problem* pr, const DevWork& w, const double* x, double* grad,
@@ -2101,10 +1953,7 @@ static EvalArgs make_args(const Problem* pr, const DevWork& w, const double* x, 
   a.nLc = pr->nLc;
   a.tc = pr->tile.tc;
   a.lt = pr->tile.lt;
-  a.sparse = pr->tile.split;
-  a.zfk = pr->nKb_max;
-  a.zfs = pr->nLb_max;
-  a.rfs = rflag_stride(pr->nKb_max);
+  a.rqs = pr->nKb_max;
   a.toff = pr->toff;
   const Screen& sc = pr->scr;
   if (mode.screened) {
@@ -2114,6 +1963,7 @@ static EvalArgs make_args(const Problem* pr, const DevWork& w, const double* x, 
     a.kst = sc.Ka;
     a.nKb = a.nKc = sc.Ka / kCtgLanes;
     a.lodf_sel = sc.lodf_act;
+    a.lmax = pr->dp.lmax ? sc.lmax_act : nullptr;
   } else {
     a.act_k = nullptr;
     a.act_slot = nullptr;
@@ -2122,7 +1972,9 @@ static EvalArgs make_args(const Problem* pr, const DevWork& w, const double* x, 
     const DevProblem& dp = pr->dp;
     a.lodf_sel = dp.lodf_kind == kLodfF64 ? (const void*)dp.lodf
                  : dp.lodf_kind == kLodfF32 ? (const void*)dp.lodf32 : (const void*)dp.lodf16;
+    a.lmax = dp.lmax;
   }
+  a.nsl = ctg_slices(*pr, a.nKb);
   return a;
 }
 
@@ -2151,15 +2003,11 @@ static void launch_stage(const Problem* pr, const EvalArgs& a, int stage, hipStr
       }
       break;
     case 2:
-      if (pr->K > 0) {
-        if (a.sparse)
-          hipLaunchKernelGGL(k_ctg_zred<true>, dim3(a.nKc, pr->T), dim3(64), 0, s, a);
-        else
-          hipLaunchKernelGGL(k_ctg_zred<false>, dim3(a.nKc, pr->T), dim3(64), 0, s, a);
-      }
+      if (pr->K > 0 && a.nsl == 0)  // k_ctg_rows finishes z itself
+        hipLaunchKernelGGL(k_ctg_zred, dim3(a.nKc, pr->T), dim3(64), 0, s, a);
       break;
     case 3:
-      if (a.sparse)
+      if (a.nsl > 0)
         hipLaunchKernelGGL(k_ctg_asm<true>, dim3(asm_blocks(pr)), dim3(kBlock), 0,
                            s, a);
       else
@@ -2193,7 +2041,7 @@ int launch_eval(const Problem* pr, const DevWork& w, const double* x, double* gr
 }
 
 // ---------------------------------------------------------------------------
-// Batched step: the same six stages for many independent problems, one launch
+// Batched step: the same stages for many independent problems, one launch
 // per stage.  A block finds its problem and its block of that problem in the
 // stage's table (one scalar load); the kernel arguments of every problem sit
 // in the batch buffer.  Each problem's blocks do exactly what they do in a
@@ -2208,324 +2056,23 @@ __device__ __forceinline__ void batch_entry(const uint32_t* __restrict__ tab, ui
 }
 
 __global__ __launch_bounds__(kBlock) void k_forward_b(const EvalArgs* __restrict__ args,
-                                                      const uint32_t* __restrict__ tab, int* ctr) {
+                                                      const uint32_t* __restrict__ tab) {
   __shared__ double smem[kFwdLds];
-  // the work counter of this step's map-reduce (the previous step's has
-  // finished: the launches are ordered)
-  if (blockIdx.x == 0 && threadIdx.x == 0) *ctr = 0;
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
   forward_body(args[s], b, smem);
 }
 
-// Persistent contingency map-reduce: every block takes work items (one
-// period-split block of one problem: l-block, k-block, period chunk) from the
-// counter until none is left, and runs k_ctg_pm's block code on each (a
-// wavefront without periods skips it, as every wavefront must reach the
-// barriers of the loop).  Items are ordered by decreasing work, so the
-// last ones to be taken are short.  Tiles: 4 wavefronts of 4 periods (the
-// problem's tile), its branch tiles per block free.
-template <typename LT, bool SKIP>
-__global__ __launch_bounds__(kBatchWl * 64) void k_ctg_pm_b(const EvalArgs* __restrict__ args,
-                                                            const uint32_t* __restrict__ items,
-                                                            int nitems, int* ctr) {
+// Batched row-compacted map-reduce: blocks of kBatchRowWaves wavefronts, each
+// taking the slices of its (period, contingency block) in turn; the sums are
+// added in slice order, as in a launch of the problem's own.
+template <typename LT>
+__global__ __launch_bounds__(kBatchRowWaves * 64) void k_ctg_rows_b(const EvalArgs* __restrict__ args,
+                                                             const uint32_t* __restrict__ tab) {
   extern __shared__ double dyn[];
-  __shared__ int next;
-  for (;;) {
-    if (threadIdx.x == 0) next = atomicAdd(ctr, 1);
-    __syncthreads();
-    const int it = next;
-    __syncthreads();  // every wave has read the item before it is replaced
-    if (it >= nitems) break;
-    int s, loc;
-    batch_entry(items, (uint32_t)it, s, loc);
-    const EvalArgs& a = args[s];
-    const int nLb = a.nLb, nKb = a.nKb;
-    const int lb = loc % nLb, kb = (loc / nLb) % nKb, bz = loc / (nLb * nKb);
-    constexpr int TCW = kBatchTcw;
-    const int WL = kBatchWl;
-    const LT* __restrict__ lodf = static_cast<const LT*>(a.lodf_sel);
-    {
-      typedef typename std::conditional<std::is_same<LT, double>::value, double, float>::type R;
-      constexpr bool kF64 = std::is_same<R, double>::value;
-      const DevProblem& p = a.p;
-      const DevWork& w = a.w;
-      const int lane = threadIdx.x & 63;
-      const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-      const int T = p.T, Lp = p.Lp, Kp = p.Kp;
-      const int tw = (bz * WL + wv) * TCW;  // first period of the wavefront
-      const int ntw = min(TCW, T - tw);
-      if (ntw > 0) {
-      const int k = kb * 64 + lane;  // slot of the lane
-      const int kc = a.act_k ? a.act_k[k] : k;
-      // z and S of the wavefront's (period, lane) pairs live in its own slice
-      // of LDS: only the per-branch path and the final store touch them
-      double* zsh = dyn + (size_t)wv * TCW * 128;
-      double* ssh = zsh + TCW * 64;
-      R fk[TCW];
-    #pragma unroll
-      for (int i = 0; i < TCW; ++i) {
-        fk[i] = i < ntw ? (R)w.Fk[(size_t)(tw + i) * Kp + kc] : R(0);
-        zsh[i * 64 + lane] = 0.0;
-        ssh[i * 64 + lane] = 0.0;
-      }
-      const cdouble* Sc = as_const(p.ctg_smax2);
-      const cdouble* Mc = as_const(p.ctg_smax);
-      const cdouble* Dc = as_const(p.dt);
-      const cdouble* Qc = as_const(w.q2);
-      const cdouble* FH = as_const(w.fh);
-      const double beta = w.params[PB_BETA];
-      const R eps = (R)w.params[PB_EPS];
-      const R eps2 = eps * eps;
-      const int ei = lane >> 3, eg = lane & 7;
-      const int l0 = lb * a.lt * 8;
-      const int l1 = min(Lp, l0 + a.lt * 8);
-      // The factor loads of the tile loop go through a buffer resource over
-      // the block's rows: the lane's fixed 32-bit byte offset (its slot k) plus
-      // a uniform row offset that advances with the tile, so the loop needs no
-      // per-lane address arithmetic.
-      unsigned rowb = (unsigned)a.kst * (unsigned)sizeof(LT);  // bytes per factor row
-      const __amdgpu_buffer_rsrc_t lrs =
-          buf_rsrc(lodf + (size_t)l0 * a.kst, (unsigned)(l1 - l0) * rowb);
-      const unsigned koff = (unsigned)k * (unsigned)sizeof(LT);
-      // R/Q flags of the lane's period (lane e < ntw: period tw + e), bit i for
-      // tile i of the block, stored after the loop
-      uint64_t fbits = 0;
-      // SKIP: half rows proved free of overloads are skipped (ctg_cold_mask),
-      // with FP64 factors, every contingency scored and a block of at most
-      // 64 / TCW tiles (two masks of 32 / TCW tiles cover them; the host
-      // launches the SKIP form only then, and a block outside it tests
-      // everything); the F and thr of a tested half row are loaded when it is
-      // reached.  Otherwise they are prefetched one half row ahead.
-      // Bit ((ti mod CT) TCW + i) 2 + h of mask ti / CT (CT = 32 / TCW): half
-      // row h of period tw + i of tile ti skipped.
-      uint64_t coldm = 0, coldm1 = 0;
-      if constexpr (SKIP) {
-        constexpr int CT = 32 / TCW;  // tiles per mask
-        const int ntile = (l1 - l0) >> 3;
-        if (p.lmaxh != nullptr && a.act_k == nullptr && ntile <= 2 * CT) {
-          double fkm = 0.0;  // largest |F_tk| of the wave's lanes and periods
-    #pragma unroll
-          for (int i = 0; i < TCW; ++i) fkm = fmax(fkm, fabs(fk[i]));
-          fkm = wave_max(fkm);
-          coldm = ctg_cold_mask<TCW, kF64>(w.fh, p.lmaxh, T, tw, ntw, l0 >> 3, ntile, kb, Kp >> 6,
-                                           fkm, w.q2, p.ctg_smax2, Lp);
-          if (ntile > CT)
-            coldm1 = ctg_cold_mask<TCW, kF64>(w.fh, p.lmaxh, T, tw, ntw, (l0 >> 3) + CT, ntile - CT,
-                                              kb, Kp >> 6, fkm, w.q2, p.ctg_smax2, Lp);
-        }
-      }
-      // F and thr of the next half row (four branches of one period) to be
-      // tested, from the branch-tiled copy, so that every prefetch is a fixed
-      // offset from the tile's row of period tw
-      double Fn[4], Hn[4];
-      if constexpr (kF64 && !SKIP) {
-        const cdouble* r = FH + ((size_t)(l0 >> 3) * T + tw) * 16;
-    #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          Fn[g] = r[g];
-          Hn[g] = r[4 + g];
-        }
-      }
-      const uint32_t live = (1u << ntw) - 1u;  // the wave's periods among the TCW tested
-      unsigned lso = 0;  // uniform offset of the tile's factor rows
-      int ti = 0;        // tile index in the block
-      // rows of the branch-tiled copy: period tw of the tile, of the next tile
-      const cdouble* cur = FH + ((size_t)(l0 >> 3) * T + tw) * 16;
-      unsigned fstep = (unsigned)T * 16u;
-      for (int lbase = l0; lbase < l1; lbase += 8, lso += 8 * rowb, ++ti, cur += fstep) {
-        // the strides are taken as changing in every tile, so that nothing
-        // derived from them is hoisted out of the loop (such values took SGPRs
-        // that were then spilled, and reloading them costs vector instructions)
-        asm volatile("" : "+s"(rowb), "+s"(fstep));
-        const cdouble* nxt = cur + fstep;
-        // the tile's half rows that are tested (bit 2 i + h); a tile without
-        // any is passed over, and only the factor rows of tested halves are loaded
-        const uint32_t need =
-            ~(uint32_t)((ti < 32 / TCW ? coldm : coldm1) >> ((ti % (32 / TCW)) * TCW * 2)) &
-            ((1u << (2 * TCW)) - 1u);
-        if (need == 0) continue;
-        R lod[8];
-    #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          lod[j] = (need & (j < 4 ? 0x5555u : 0xAAAAu)) ? lodf_buf(lrs, lodf, koff, lso + j * rowb) : R(0);
-        R fv = R(0), qv = R(0), smx2[8];
-        if constexpr (!kF64) {
-          if (ei < ntw) {
-            const size_t e = (size_t)(tw + ei) * Lp + lbase + eg;
-            fv = (R)w.F[e];
-            qv = (R)w.q2[e];
-          }
-    #pragma unroll
-          for (int j = 0; j < 8; ++j) smx2[j] = (R)Sc[lbase + j];
-        }
-        // The test of every (period, branch, lane) of the tile, without a
-        // branch: all TCW periods are tested (the rows past the wave's last
-        // period are spare rows of the array, and their verdicts are dropped
-        // with the mask), and each period's verdict is one bit of hotm.
-        uint32_t hotm = 0;
-    #pragma unroll
-        for (int i = 0; i < TCW; ++i) {
-          uint64_t hot = 0;
-          if constexpr (SKIP && kF64) {
-    #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              if ((need >> (2 * i + h)) & 1u) {
-                double Fr[4], Hr[4];
-                const cdouble* q = cur + 16 * i + 8 * h;
-    #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                  Fr[g] = q[g];
-                  Hr[g] = q[4 + g];
-                }
-    #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                  const double P = fma_uniform_c(lod[4 * h + g], fk[i], Fr[g]);
-                  hot |= __builtin_amdgcn_ballot_w64(fabs(P) > Hr[g]);
-                }
-              }
-            }
-          } else if constexpr (kF64) {
-    #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              double Fr[4], Hr[4];
-    #pragma unroll
-              for (int g = 0; g < 4; ++g) {
-                Fr[g] = Fn[g];
-                Hr[g] = Hn[g];
-              }
-              // prefetch: the other half of this period's row, else the next
-              // period of this tile, else period tw of the next tile (rows past
-              // the tile or the last tile are spare rows)
-              const cdouble* q = h == 0 ? cur + 16 * i + 8 : (i + 1 < TCW) ? cur + 16 * (i + 1) : nxt;
-    #pragma unroll
-              for (int g = 0; g < 4; ++g) {
-                Fn[g] = q[g];
-                Hn[g] = q[4 + g];
-              }
-    #pragma unroll
-              for (int g = 0; g < 4; ++g) {
-                const double P = fma_uniform_c(lod[4 * h + g], fk[i], Fr[g]);
-                hot |= __builtin_amdgcn_ballot_w64(fabs(P) > Hr[g]);
-              }
-            }
-          } else {
-            // FP32 arithmetic; with SKIP only the half rows that are tested
-    #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              if ((need >> (2 * i + h)) & 1u) {
-    #pragma unroll
-                for (int gg = 0; gg < 4; ++gg) {
-                  const int g = 4 * h + gg;
-                  const R Fr = readlane_any(fv, i * 8 + g);
-                  const R P = fma_uniform_c(lod[g], fk[i], Fr);
-                  const R s2 = fma_uniform_c(P, P, readlane_any(qv, i * 8 + g));
-                  hot |= __builtin_amdgcn_ballot_w64(s2 > smx2[g]);
-                }
-              }
-            }
-          }
-          hotm |= (hot != 0 ? 1u : 0u) << i;
-        }
-        hotm &= live;
-        // a wave with fewer than TCW periods prefetched a spare row for the
-        // next tile: load its first period's row again
-        if constexpr (kF64 && !SKIP) {
-          if (ntw < TCW) {
-    #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              Fn[g] = nxt[g];
-              Hn[g] = nxt[4 + g];
-            }
-          }
-        }
-        if (hotm) {
-          // R and Q of (period tw + e / 8, branch lbase + e % 8) gather in lane e
-          R racc = R(0), qacc = R(0);
-          // the overloaded periods of the tile: the per-branch path, with F,
-          // qmax2 and the ratings loaded again
-    #pragma unroll
-          for (int i = 0; i < TCW; ++i) {
-            if ((hotm >> i) & 1u) {
-              const R kt = (R)(Dc[tw + i] * p.c_s * beta);
-              R Fr[8], Qr[8], Sr[8];
-    #pragma unroll
-              for (int g = 0; g < 8; ++g) {
-                if constexpr (kF64) {
-                  Fr[g] = cur[16 * i + fh_col_f(g)];
-                  Qr[g] = Qc[(size_t)(tw + i) * Lp + lbase + g];
-                  Sr[g] = Sc[lbase + g];
-                } else {
-                  Fr[g] = readlane_any(fv, i * 8 + g);
-                  Qr[g] = readlane_any(qv, i * 8 + g);
-                  Sr[g] = smx2[g];
-                }
-              }
-              R zt = R(0), st = R(0);
-    #pragma unroll
-              for (int g = 0; g < 8; ++g) {
-                // a skipped half row holds no overload (and its factors were
-                // not loaded)
-                if (((need >> (2 * i + (g >> 2))) & 1u) == 0) continue;
-                // the flow formed again (the same fused operation, so the same
-                // value as in the test)
-                const R P = fma_uniform_c(lod[g], fk[i], Fr[g]);
-                const R s2 = fma_uniform_c(P, P, Qr[g]);
-                if (__builtin_amdgcn_ballot_w64(s2 > Sr[g])) {
-                  R dP = R(0), dq = R(0);
-                  if (s2 > Sr[g]) {
-                    zt += ctg_overload(P, s2, (R)Mc[lbase + g], eps, eps2, kt, dP, dq);
-                    st = fma(lod[g], dP, st);
-                  }
-                  const R r = pair_sum(dP, dq);  // lane 0: sum of dP, lane 32: of dq
-                  racc = writelane_set(racc, readlane_any(r, 0), i * 8 + g);
-                  qacc = writelane_set(qacc, readlane_any(r, 32), i * 8 + g);
-                }
-              }
-              zsh[i * 64 + lane] += (double)zt;
-              ssh[i * 64 + lane] += (double)st;
-            }
-          }
-          // per (period, 8 branches): stored only when not all zero, and flagged
-          const uint64_t b = __builtin_amdgcn_ballot_w64(racc != R(0) || qacc != R(0));
-          if (lane < ntw && ((b >> (8 * lane)) & 0xFF) != 0) fbits |= (uint64_t)1 << ti;
-          if (b != 0 && lane < ntw * 8 && ((b >> (lane & ~7)) & 0xFF) != 0) {
-            const size_t o = ((size_t)kb * T + tw + ei) * Lp + lbase + eg;
-            w.rpart[o] = (double)racc;
-            w.qpart[o] = (double)qacc;
-          }
-        }
-      }
-      if (lane < ntw) {
-        uint8_t* f = w.rflag + ((size_t)(tw + lane) * (Lp / 8) + (l0 >> 3)) * a.rfs + kb;
-        for (int i = 0; i < ti; ++i) f[(size_t)i * a.rfs] = (uint8_t)((fbits >> i) & 1u);
-      }
-    #pragma unroll
-      for (int i = 0; i < TCW; ++i) {
-        if (i < ntw) {
-          // stored only when not all zero, and flagged
-          const double z = zsh[i * 64 + lane], s2 = ssh[i * 64 + lane];
-          const bool nz = __builtin_amdgcn_ballot_w64(z != 0.0 || s2 != 0.0) != 0;
-          if (lane == 0) w.zflag[((size_t)(tw + i) * a.zfk + kb) * a.zfs + lb] = (uint8_t)nz;
-          if (nz) {
-            const size_t o = ((size_t)lb * T + tw + i) * Kp + k;
-            w.zpart[o] = z;
-            w.spart[o] = s2;
-          }
-        }
-      }
-      }
-
-    }
-  }
-}
-
-__global__ __launch_bounds__(64) void k_ctg_zred_b(const EvalArgs* __restrict__ args,
-                                                   const uint32_t* __restrict__ tab) {
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
-  const EvalArgs& a = args[s];
-  ctg_zred_body<true>(a, b % a.nKc, b / a.nKc);
+  ctg_rows_body<LT>(args[s], xcd_group(b, args[s].nKb * args[s].p.T), dyn);
 }
 
 __global__ __launch_bounds__(kBlock) void k_ctg_asm_b(const EvalArgs* __restrict__ args,
@@ -2554,12 +2101,11 @@ __global__ __launch_bounds__(kBlock) void k_final_b(const EvalArgs* __restrict__
   final_body(args[s], b, smem);
 }
 
-// Blocks of each stage of one problem (stage 1: map-reduce work items).
+// Blocks of each stage of one problem.
 static void stage_blocks(const Problem* pr, const EvalArgs& a, int out[kStages]) {
-  const int span = pr->tile.wl * pr->tile.tc;
   out[0] = pr->nb_br + pr->T + pr->Lp / 16 * (pr->Tp / 16);
-  out[1] = pr->K > 0 ? pr->nLb * a.nKb * ((pr->T + span - 1) / span) : 0;
-  out[2] = pr->K > 0 ? a.nKc * pr->T : 0;
+  out[1] = pr->K > 0 ? a.nKb * pr->T : 0;
+  out[2] = 0;  // the map-reduce finishes z itself
   out[3] = asm_blocks(pr);
   out[4] = pr->G16 / 16 * pr->nsplit + pr->nb_br + (pr->T * pr->G16 + kBlock - 1) / kBlock;
   out[5] = pr->nb_bus + pr->nb_gen + 1;
@@ -2610,20 +2156,14 @@ int plan_batch(const Problem* const* prs, const DevWork* ws, int n, const double
     P.off_tab[q] = o;
     o = align_up(o + (size_t)P.nblk[q] * sizeof(uint32_t));
   }
-  P.off_ctr = o;
-  o = align_up(o + sizeof(int));
   P.bytes = o;
   if (image) {
     image->assign(P.bytes, 0);
     std::memcpy(image->data() + P.off_args, args.data(), (size_t)n * sizeof(EvalArgs));
-    // map-reduce items: problems by decreasing work per item (periods and
-    // branch tiles of a block), each problem's items in its grid order
+    // map-reduce blocks: problems by decreasing work per block (branches)
     std::vector<int> order((size_t)n);
     for (int i = 0; i < n; ++i) order[i] = i;
-    auto item_work = [&](int i) {
-      const Problem* pr = prs[i];
-      return (int64_t)std::min(pr->T, kBatchWl * pr->tile.tc) * pr->tile.lt;
-    };
+    auto item_work = [&](int i) { return prs[i]->Lp; };
     std::stable_sort(order.begin(), order.end(),
                      [&](int a2, int b2) { return item_work(a2) > item_work(b2); });
     for (int q = 0; q < kStages; ++q) {
@@ -2636,36 +2176,7 @@ int plan_batch(const Problem* const* prs, const DevWork* ws, int n, const double
       }
     }
   }
-  // persistent map-reduce: as many blocks as fit on the chip at once
-  int dev = 0, ncu = 256, per_cu = 1;
-  const size_t lds = (size_t)kBatchWl * kBatchTcw * 128 * sizeof(double);
-  if (hipGetDevice(&dev) == hipSuccess)
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  // the skip test (FP64) when a problem's blocks qualify for it; the SKIP
-  // kernel tests every half row of the others
-  P.skip = false;
-  for (int i = 0; i < n; ++i)
-    P.skip = P.skip || (prs[i]->dp.lmaxh != nullptr && prs[i]->tile.lt >= kSkipMinTiles &&
-                        prs[i]->tile.lt <= 64 / kBatchTcw);
-  hipError_t e;
-  if (P.lodf_kind == kLodfF64)
-    e = P.skip ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ctg_pm_b<double, true>,
-                                                              kBatchWl * 64, lds)
-               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ctg_pm_b<double, false>,
-                                                              kBatchWl * 64, lds);
-  else if (P.lodf_kind == kLodfF32)
-    e = P.skip ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ctg_pm_b<float, true>,
-                                                              kBatchWl * 64, lds)
-               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ctg_pm_b<float, false>,
-                                                              kBatchWl * 64, lds);
-  else
-    e = P.skip
-            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ctg_pm_b<uint16_t, true>,
-                                                           kBatchWl * 64, lds)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ctg_pm_b<uint16_t, false>,
-                                                           kBatchWl * 64, lds);
-  if (e != hipSuccess || per_cu < 1) per_cu = 1;
-  P.pm_grid = std::max(1, std::min(P.nblk[1], ncu * per_cu));
+  for (int i = 0; i < n; ++i) P.nsl = std::max(P.nsl, args[i].nsl);
   *plan = P;
   return 0;
 }
@@ -2675,28 +2186,17 @@ int launch_eval_batch(const BatchPlan& P, void* d_buf, void* stream) {
   unsigned char* b = static_cast<unsigned char*>(d_buf);
   const EvalArgs* args = reinterpret_cast<const EvalArgs*>(b + P.off_args);
   auto tab = [&](int q) { return reinterpret_cast<const uint32_t*>(b + P.off_tab[q]); };
-  int* ctr = reinterpret_cast<int*>(b + P.off_ctr);
-  hipLaunchKernelGGL(k_forward_b, dim3(P.nblk[0]), dim3(kBlock), 0, s, args, tab(0), ctr);
+  hipLaunchKernelGGL(k_forward_b, dim3(P.nblk[0]), dim3(kBlock), 0, s, args, tab(0));
   if (P.nblk[1] > 0) {
-    const size_t lds = (size_t)kBatchWl * kBatchTcw * 128 * sizeof(double);
-    const dim3 g(P.pm_grid), blk(kBatchWl * 64);
-    if (P.lodf_kind == kLodfF64 && P.skip)
-      hipLaunchKernelGGL((k_ctg_pm_b<double, true>), g, blk, lds, s, args, tab(1), P.nblk[1], ctr);
-    else if (P.lodf_kind == kLodfF64)
-      hipLaunchKernelGGL((k_ctg_pm_b<double, false>), g, blk, lds, s, args, tab(1), P.nblk[1], ctr);
-    else if (P.lodf_kind == kLodfF32 && P.skip)
-      hipLaunchKernelGGL((k_ctg_pm_b<float, true>), g, blk, lds, s, args, tab(1), P.nblk[1], ctr);
+    const size_t lds = (size_t)P.nsl * 128 * sizeof(double);
+    const dim3 g(P.nblk[1]), blk(kBatchRowWaves * 64);
+    if (P.lodf_kind == kLodfF64)
+      hipLaunchKernelGGL(k_ctg_rows_b<double>, g, blk, lds, s, args, tab(1));
     else if (P.lodf_kind == kLodfF32)
-      hipLaunchKernelGGL((k_ctg_pm_b<float, false>), g, blk, lds, s, args, tab(1), P.nblk[1], ctr);
-    else if (P.skip)
-      hipLaunchKernelGGL((k_ctg_pm_b<uint16_t, true>), g, blk, lds, s, args, tab(1), P.nblk[1],
-                         ctr);
+      hipLaunchKernelGGL(k_ctg_rows_b<float>, g, blk, lds, s, args, tab(1));
     else
-      hipLaunchKernelGGL((k_ctg_pm_b<uint16_t, false>), g, blk, lds, s, args, tab(1), P.nblk[1],
-                         ctr);
+      hipLaunchKernelGGL(k_ctg_rows_b<uint16_t>, g, blk, lds, s, args, tab(1));
   }
-  if (P.nblk[2] > 0)
-    hipLaunchKernelGGL(k_ctg_zred_b, dim3(P.nblk[2]), dim3(64), 0, s, args, tab(2));
   hipLaunchKernelGGL(k_ctg_asm_b, dim3(P.nblk[3]), dim3(kBlock), 0, s, args, tab(3));
   hipLaunchKernelGGL(k_adjoint_b, dim3(P.nblk[4]), dim3(kBlock), 0, s, args, tab(4));
   hipLaunchKernelGGL(k_final_b, dim3(P.nblk[5]), dim3(kBlock), 0, s, args, tab(5));

@@ -16,7 +16,8 @@
 //                  prefix sums): slot -> contingency and contingency -> slot
 //   k_scr_gather   the slots' outage-factor columns into contiguous rows of
 //                  the screening buffer, NaN past the set so that padding
-//                  lanes never test overloaded
+//                  lanes never test overloaded, and each branch's largest
+//                  magnitude over 64 slots (the map-reduce's row bound)
 // Keys: output r 2^32 + k + 1 of SplitMix64 (Steele, Lea and Flood, OOPSLA
 // 2014) seeded with the screening seed, r the index of the refresh.
 #include <hip/hip_runtime.h>
@@ -179,15 +180,27 @@ template <> __device__ __forceinline__ double nan_of<double>() { return __builti
 template <> __device__ __forceinline__ float nan_of<float>() { return __builtin_nanf(""); }
 template <> __device__ __forceinline__ uint16_t nan_of<uint16_t>() { return 0x7FC0; }
 
+__device__ __forceinline__ double widen(double v) { return v; }
+__device__ __forceinline__ double widen(float v) { return (double)v; }
+__device__ __forceinline__ double widen(uint16_t v) {
+  return (double)__uint_as_float((unsigned)v << 16);
+}
+
 template <typename LT>
 __global__ __launch_bounds__(kScrBlock) void k_scr_gather(const LT* lodf, int Kp, int Lp,
                                                           const int* act_k, int na, int Ka,
-                                                          LT* out) {
+                                                          LT* out, double* lmax) {
   const int s = blockIdx.x * kScrBlock + threadIdx.x;
-  if (s >= Ka) return;
+  if (s >= Ka) return;  // whole wavefronts: Ka is a multiple of 64
   const int k = s < na ? act_k[s] : 0;
-  for (int l = blockIdx.y; l < Lp; l += gridDim.y)
-    out[(size_t)l * Ka + s] = s < na ? lodf[(size_t)l * Kp + k] : nan_of<LT>();
+  for (int l = blockIdx.y; l < Lp; l += gridDim.y) {
+    const LT v = s < na ? lodf[(size_t)l * Kp + k] : nan_of<LT>();
+    out[(size_t)l * Ka + s] = v;
+    double m = fmax(fabs(widen(v)), 0.0);  // NaN dropped
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m = fmax(m, __shfl_xor(m, d));
+    if ((threadIdx.x & 63) == 0) lmax[(size_t)(s >> 6) * Lp + l] = m;
+  }
 }
 
 }  // namespace
@@ -199,13 +212,16 @@ int launch_screen_gather(const Problem* pr, void* stream) {
   const dim3 grid((sc.Ka + kScrBlock - 1) / kScrBlock, pr->Lp < 65535 ? pr->Lp : 65535);
   if (dp.lodf_kind == kLodfF64)
     hipLaunchKernelGGL(k_scr_gather<double>, grid, dim3(kScrBlock), 0, st, dp.lodf, pr->Kp,
-                       pr->Lp, sc.act_k, sc.n_act, sc.Ka, static_cast<double*>(sc.lodf_act));
+                       pr->Lp, sc.act_k, sc.n_act, sc.Ka, static_cast<double*>(sc.lodf_act),
+                       sc.lmax_act);
   else if (dp.lodf_kind == kLodfF32)
     hipLaunchKernelGGL(k_scr_gather<float>, grid, dim3(kScrBlock), 0, st, dp.lodf32, pr->Kp,
-                       pr->Lp, sc.act_k, sc.n_act, sc.Ka, static_cast<float*>(sc.lodf_act));
+                       pr->Lp, sc.act_k, sc.n_act, sc.Ka, static_cast<float*>(sc.lodf_act),
+                       sc.lmax_act);
   else
     hipLaunchKernelGGL(k_scr_gather<uint16_t>, grid, dim3(kScrBlock), 0, st, dp.lodf16, pr->Kp,
-                       pr->Lp, sc.act_k, sc.n_act, sc.Ka, static_cast<uint16_t*>(sc.lodf_act));
+                       pr->Lp, sc.act_k, sc.n_act, sc.Ka, static_cast<uint16_t*>(sc.lodf_act),
+                       sc.lmax_act);
   return (int)hipGetLastError();
 }
 
