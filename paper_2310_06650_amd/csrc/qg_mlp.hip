@@ -2,13 +2,14 @@
 // on MFMA (v_mfma_f32_16x16x4f32) and BF16 inference (v_mfma_f32_16x16x32_bf16
 // with FP32 accumulation), GELU activations, mean squared error, Adam.
 //
-// Every matrix product goes through one tiled kernel per operand type: a
-// 256-thread block computes a 64 x 64 tile of op(A) op(B) over a slice of the
-// reduction dimension (grid.z splits it when the output has few tiles) and
-// writes raw sums; a second kernel adds the slices in a fixed order and
-// applies the layer's epilogue (bias, GELU, GELU derivative, BF16 rounding).
-// With one slice and no epilogue the product is written in place.  No
-// floating-point atomics: results are bitwise reproducible.
+// FP32 products of the batch with a weight matrix are one kernel (k_product),
+// the weight gradients another (k_dw), which carries the bias gradient and, in a
+// training step, the Adam update and the loss; the BF16 products are a third
+// (k_gemm_bf16).  Where an output has few tiles grid.z splits the reduction
+// dimension: the blocks write raw sums and k_reduce_epi adds the slices in a
+// fixed order and applies the layer's epilogue (bias, GELU, GELU derivative, BF16
+// rounding); otherwise the product applies it itself.  No floating-point
+// atomics: results are bitwise reproducible.
 //
 // MFMA operand layouts (gfx950): lane l holds A[l%16][KPL*(l/16) + i] and
 // B[KPL*(l/16) + i][l%16] for i < KPL (KPL = 1 for FP32, 8 for BF16); the
@@ -19,6 +20,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 
 #include "qg_internal.h"
 #include "qg_mlp.h"
@@ -33,10 +35,12 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int kT = 64;        // output tile edge
+constexpr int kBK = 32;       // reduction depth of a k-step
 constexpr int kThreads = 256;
-constexpr int kLossBlocks = 256;
+constexpr int kGemm = 512;    // threads of a product's block: wavefronts of 32 x 16 outputs
+constexpr int kEl = kT * kBK / kGemm;  // elements of each operand per thread and k-step
 
-enum Epi { kStore = 0, kBiasGelu = 1, kBias = 2, kGeluBwd = 3, kBiasGeluBf16 = 4 };
+enum Epi { kStore = 0, kBiasGelu = 1, kBias = 2, kGeluBwd = 3, kBiasGeluBf16 = 4, kMse = 5 };
 
 __device__ __forceinline__ float gelu(float z) {
   return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
@@ -53,219 +57,636 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((unsigned)h << 16); }
 
-// C (+ z * M * ldc) = op(A) op(B) over the z-th reduction slice.
-// op(A)[m][k] = TA ? A[k*lda + m] : A[m*lda + k]; op(B)[k][n] likewise.
-// Software-pipelined: the operands of the next 16-wide k-step are loaded
-// into registers while the current one is multiplied from one of two LDS
-// buffers (one barrier per k-step: a buffer is refilled only after every
-// wavefront has passed the barrier that follows its last use).
-template <int TA, int TB>
-__global__ __launch_bounds__(kThreads) void k_gemm_f32(const float* __restrict__ A, int lda,
-                                                      const float* __restrict__ B, int ldb,
-                                                      float* __restrict__ C, int ldc, int M,
-                                                      int N, int K, int kslice) {
-  __shared__ float As[2][kT][17];
-  __shared__ float Bs[2][16][kT + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m0 = blockIdx.y * kT, n0 = blockIdx.x * kT;
-  const int kb = blockIdx.z * kslice, ke = min(K, kb + kslice);
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-  v4f acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  float ra[4], rb[4];  // this thread's elements of the next k-step
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + q * kThreads;
-      const int mm = TA ? (e & 63) : (e >> 4), kk = TA ? (e >> 6) : (e & 15);
-      const int gm = m0 + mm, gk = k0 + kk;
-      ra[q] = (gm < M && gk < ke) ? (TA ? A[(size_t)gk * lda + gm] : A[(size_t)gm * lda + gk]) : 0.f;
+// What happens to the sum s of output element e (column n) of a product.
+struct EpiArgs {
+  int kind;
+  const float* bias;       // [N], or null
+  const uint16_t* bias16;  // [N] BF16 biases, widened, when bias is null
+  float* z;                // kBiasGelu: pre-activation out; kGeluBwd: pre-activation in
+  float* out;              // float result
+  uint16_t* out16;         // kBiasGeluBf16
+  const float* t;          // kMse: targets; out receives d loss / d y
+  float inv;               // kMse: 1 / (M N)
+  float* loss_part;        // kMse: one partial sum of squares per block
+};
+
+// Its column's bias and stored pre-activation are read ahead of the sum.
+struct Aux {
+  float b, z;
+};
+__device__ __forceinline__ Aux epi_aux(const EpiArgs& ep, size_t e, int n) {
+  return {ep.bias ? ep.bias[n] : ep.bias16 ? from_bf16(ep.bias16[n]) : 0.f,
+          ep.kind == kGeluBwd ? ep.z[e] : 0.f};
+}
+__device__ __forceinline__ void epilogue(const EpiArgs& ep, size_t e, const Aux& x, float s) {
+  switch (ep.kind) {
+    case kBiasGelu: {
+      const float z = s + x.b;
+      ep.z[e] = z;
+      ep.out[e] = gelu(z);
+      break;
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + q * kThreads;
-      const int kk = TB ? (e & 15) : (e >> 6), nn = TB ? (e >> 4) : (e & 63);
-      const int gk = k0 + kk, gn = n0 + nn;
-      rb[q] = (gn < N && gk < ke) ? (TB ? B[(size_t)gn * ldb + gk] : B[(size_t)gk * ldb + gn]) : 0.f;
-    }
-  };
-  if (kb < ke) gload(kb);
-  for (int k0 = kb, buf = 0; k0 < ke; k0 += 16, buf ^= 1) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + q * kThreads;
-      As[buf][TA ? (e & 63) : (e >> 4)][TA ? (e >> 6) : (e & 15)] = ra[q];
-      Bs[buf][TB ? (e & 15) : (e >> 6)][TB ? (e >> 4) : (e & 63)] = rb[q];
-    }
-    __syncthreads();
-    if (k0 + 16 < ke) gload(k0 + 16);
-#pragma unroll
-    for (int ks = 0; ks < 16; ks += 4) {
-      float a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[buf][wm + i * 16 + (lane & 15)][ks + (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[buf][ks + (lane >> 4)][wn + j * 16 + (lane & 15)];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
+    case kBias: ep.out[e] = s + x.b; break;
+    case kGeluBwd: ep.out[e] = s * gelu_d(x.z); break;
+    case kBiasGeluBf16: ep.out16[e] = to_bf16(gelu(s + x.b)); break;
+    default: ep.out[e] = s; break;
   }
-  float* Cz = C + (size_t)blockIdx.z * M * ldc;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-        const int col = n0 + wn + j * 16 + (lane & 15);
-        if (row < M && col < N) Cz[(size_t)row * ldc + col] = acc[i][j][r];
-      }
 }
 
-// BF16 operands, row-major A [M][K] and B [K][N], FP32 sums; pipelined like
-// k_gemm_f32 with 32-wide k-steps.
-__global__ __launch_bounds__(kThreads) void k_gemm_bf16(const uint16_t* __restrict__ A, int lda,
+// Sum of one value per thread of a block of N, by a tree in a fixed order (in
+// thread 0); red holds N floats.
+template <int N>
+__device__ __forceinline__ float block_tree(float v, float* red) {
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int s = N / 2; s > 0; s >>= 1) {
+    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
+  }
+  return red[0];
+}
+
+// Raw buffer view of the bytes of a matrix from base on: the address of a load
+// is base + the lane's 32-bit offset, and loads at or past the end return 0.
+// The view of an operand moves with the k-step, so that the lanes' offsets are
+// the same in every step and the loop needs no address arithmetic.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t view(const void* base, int64_t bytes) {
+  const int hi = (int)(bytes >> 32);
+  const uint32_t n = hi < 0 ? 0u : hi > 0 ? 0xFFFFFFFFu : (uint32_t)bytes;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, 0x00020000);
+}
+// View of the k-step at k0 of an operand X[r][k] (rows of ld elements, r from
+// r0 of R, k contiguous) or X[k][r] (k < ke; ROWK).
+template <bool ROWK, typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand(const T* X, int ld, int R, int r0, int k0,
+                                                          int ke) {
+  const int64_t at = ROWK ? (int64_t)k0 * ld + r0 : (int64_t)r0 * ld + k0;
+  return view(X + at, ((ROWK ? (int64_t)ke * ld : (int64_t)R * ld) - at) * (int64_t)sizeof(T));
+}
+
+// FP32 tile product with the reduction over the operands' rows: acc = the
+// 64 x 64 tile at (m0, n0) of A^T B, A [K][M] and B [K][N], over the range [kb, ke).
+// The operands of the next kDepth 32-deep k-steps are in flight in registers
+// while the current one is multiplied from one of two LDS buffers (one barrier
+// per k-step: a buffer is refilled only after every wavefront has passed the
+// barrier that follows its last use).  Past the end of the reduction both
+// operands read zeros; rows and columns past the matrix only reach outputs that
+// are not stored.
+constexpr int kDepth = 2;
+// Both operands sit in LDS with k contiguous: lane l takes k = 8 (l/16) .. + 7 of
+// its row in two 16-byte reads, and the q-th of the k-step's eight MFMAs
+// multiplies everyone's q-th element (which k a lane multiplies when does not
+// matter as long as A and B agree).  Rows are kPitch floats apart: 16-byte
+// aligned, and 16 rows cover every bank once.
+constexpr int kPitch = kBK + 4;
+struct alignas(16) TileLds {
+  float a[2][kT][kPitch];  // [m][k]
+  float b[2][kT][kPitch];  // [n][k]
+};
+
+struct Tile {
+  float ra[kDepth][kEl], rb[kDepth][kEl];
+  unsigned oa[kEl], ob[kEl];  // byte offsets in the operands' views
+  // element e of a k-step's operand: row (or column) e % 64, k = e / 64
+  __device__ __forceinline__ void load(int d, __amdgpu_buffer_rsrc_t va,
+                                       __amdgpu_buffer_rsrc_t vb) {
+#pragma unroll
+    for (int q = 0; q < kEl; ++q)
+      ra[d][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(va, oa[q], 0, 0));
+#pragma unroll
+    for (int q = 0; q < kEl; ++q)
+      rb[d][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vb, ob[q], 0, 0));
+  }
+  __device__ __forceinline__ void put(int d, TileLds& s, int buf) {
+#pragma unroll
+    for (int q = 0; q < kEl; ++q) {
+      const int e = threadIdx.x + q * kGemm;
+      s.a[buf][e & 63][e >> 6] = ra[d][q];
+      s.b[buf][e & 63][e >> 6] = rb[d][q];
+    }
+  }
+  // step(buf): called after the barrier of every k-step with its LDS buffer, before
+  // its products
+  template <class Step>
+  __device__ __forceinline__ void run(const float* __restrict__ A, int lda,
+                                      const float* __restrict__ B, int ldb, int M, int N, int kb,
+                                      int ke, int m0, int n0, TileLds& s, v4f (&acc)[2],
+                                      Step step) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int wm = (wv >> 2) * 32, wn = (wv & 3) * 16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < kEl; ++q) {
+      const int e = threadIdx.x + q * kGemm;
+      oa[q] = ((unsigned)(e >> 6) * lda + (e & 63)) * 4u;
+      ob[q] = ((unsigned)(e >> 6) * ldb + (e & 63)) * 4u;
+    }
+    auto fetch = [&](int d, int k0) {
+      load(d, operand<true>(A, lda, M, m0, k0, ke), operand<true>(B, ldb, N, n0, k0, ke));
+    };
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) fetch(d, kb + d * kBK);
+    // the loads stay ahead of the products, and a k-step's LDS reads ahead of
+    // its first product (a wavefront or two per SIMD do not hide them)
+    auto step1 = [&](int d, int buf, int k0) {
+      put(d, s, buf);
+      __syncthreads();
+      fetch(d, k0 + kDepth * kBK);
+      step(buf);
+      v4f a[2][2], b[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = lane & 15, k = 8 * (lane >> 4) + 4 * h;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          a[i][h] = *reinterpret_cast<const v4f*>(&s.a[buf][wm + i * 16 + r][k]);
+        b[h] = *reinterpret_cast<const v4f*>(&s.b[buf][wn + r][k]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][q >> 2][q & 3], b[q >> 2][q & 3],
+                                                        acc[i], 0, 0, 0);
+    };
+    // whole rounds of kDepth k-steps (zeros past the end): a way out between
+    // two of them would let the compiler move the loads behind it
+    static_assert(kDepth == 2, "one LDS buffer per k-step of a round");
+    int k0 = kb;
+    do {
+#pragma unroll
+      for (int d = 0; d < kDepth; ++d, k0 += kBK) step1(d, d, k0);
+    } while (k0 < ke);
+  }
+};
+
+// f(row, col, value) for the thread's 8 elements of a 64 x 64 tile at (m0, n0)
+// that lie inside the matrix.
+template <class F>
+__device__ __forceinline__ void tile_elements(const v4f (&acc)[2], int m0, int n0, int M, int N,
+                                              F f) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int wm = (wv >> 2) * 32, wn = (wv & 3) * 16;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm + i * 16 + 4 * (lane >> 4) + r, col = n0 + wn + (lane & 15);
+      if (row < M && col < N) f(row, col, acc[i][r]);
+    }
+}
+
+// C = A op(B) for a product whose operands are read once or nearly so (batch
+// rows against a weight matrix): A [M][K] row-major, op(B) = B [K][N] (TB = 0) or
+// B [N][K] transposed (TB = 1).  A block of four wavefronts (eight where MI = 1)
+// computes a tile of 16 MI x 64 outputs; its wavefronts take the 16-deep steps of
+// the block's reduction slice in turn, each holding the whole tile, and are
+// added through LDS at the end in a fixed order.  The main loop has no LDS and
+// no barrier: a lane's 16-byte loads are MFMA operands as they stand (the q-th
+// MFMA of a step takes the q-th of a lane's four k, and with TB = 0 the j-th
+// column block is the j-th column of each lane's four), and DEPTH steps are in
+// flight in registers.
+// Rows of any dword alignment will do.  Past the end of the slice A is
+// masked and B reads zeros (TB = 0) or is masked; rows and columns past the
+// matrix only reach outputs that are not stored.
+// split: raw sums to C + z M N, otherwise the epilogue at once.
+//
+// At 64 rows bound by the weights' first read from HBM: 512 x 29412 (60 MB) with
+// the loss and dY takes 31 us, 2.4 TB/s (a streaming sum of 60 MB that no cache
+// holds takes 28); staged through LDS, in two slices, then added up and compared by
+// kernels of their own it took 67.  Its transposed product takes 24 us (32
+// through LDS).  More steps in flight (DEPTH 3, 4 at MI = 4) were 10 % slower.
+constexpr int kStep = 16;
+constexpr int waves_of(int mi) { return mi == 1 ? 8 : 4; }
+constexpr int kCPitch = kT + 4;
+template <int DEPTH, int MI, int TB>
+__global__ __launch_bounds__(waves_of(MI) * 64) void k_product(const float* __restrict__ A, int lda,
+                                                         const float* __restrict__ B, int ldb,
+                                                         float* __restrict__ C, int M, int N, int K,
+                                                         int kslice, int split, EpiArgs ep) {
+  constexpr int kWaves = waves_of(MI);
+  __shared__ alignas(16) float s[kWaves][16 * MI][kCPitch];
+  const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.y * 16 * MI, n0 = blockIdx.x * kT;
+  const int kb = blockIdx.z * kslice, ke = min(K, kb + kslice);
+  v4f acc[MI][4];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  v4f a[DEPTH][MI], b[DEPTH][4];
+  unsigned oa[MI], ob[4];  // byte offsets in the operands' views
+#pragma unroll
+  for (int i = 0; i < MI; ++i) oa[i] = ((unsigned)(16 * i + r) * lda + 4 * kq) * 4u;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    ob[j] =
+        (TB ? (unsigned)(16 * j + r) * ldb + 4 * kq : (unsigned)(4 * kq + j) * ldb + 4 * r) * 4u;
+  auto fetch = [&](int d, int k0) {
+    const __amdgpu_buffer_rsrc_t va = operand<false>(A, lda, M, m0, k0, ke);
+    const __amdgpu_buffer_rsrc_t vb = operand<TB == 0>(B, ldb, N, n0, k0, ke);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      b[d][j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(vb, ob[j], 0, 0));
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+      a[d][i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(va, oa[i], 0, 0));
+  };
+  int k0 = kb + wv * kStep;
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) fetch(d, k0 + d * kWaves * kStep);
+  // whole rounds of DEPTH steps (zeros past the end): a way out between two of
+  // them would let the compiler move the loads behind it
+  do {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d, k0 += kWaves * kStep) {
+      if (k0 + kStep > ke) {
+        const int left = ke - k0 - 4 * kq;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q >= left) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) a[d][i][q] = 0.f;
+            if (TB) {
+#pragma unroll
+              for (int j = 0; j < 4; ++j) b[d][j][q] = 0.f;
+            }
+          }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                a[d][i][q], TB ? b[d][j][q] : b[d][q][j], acc[i][j], 0, 0, 0);
+      fetch(d, k0 + DEPTH * kWaves * kStep);
+    }
+  } while (k0 - wv * kStep < ke);
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float* row = s[wv][16 * i + 4 * kq + q];
+      if (TB) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) row[16 * j + r] = acc[i][j][q];
+      } else {
+        *reinterpret_cast<v4f*>(row + 4 * r) =
+            v4f{acc[i][0][q], acc[i][1][q], acc[i][2][q], acc[i][3][q]};
+      }
+    }
+  __syncthreads();
+  const int n = n0 + lane;
+  float sq = 0.f;
+  if (n < N) {
+    // rows wv, wv + kWaves, ... of the tile; the bodies are kept apart and small: a
+    // launch meets a cold instruction cache
+    const size_t e0 = (size_t)m0 * N + n;
+    const int rows = min(16 * MI, M - m0);
+    auto sum = [&](int i) {
+      float v = s[0][i][lane];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) v += s[w][i][lane];
+      return v;
+    };
+    if (split) {
+      float* Cz = C + (size_t)blockIdx.z * M * N + e0;
+#pragma unroll 4
+      for (int i = wv; i < rows; i += kWaves) Cz[(size_t)i * N] = sum(i);
+    } else if (ep.kind == kMse) {
+      const float bn = ep.bias[n];
+#pragma unroll
+      for (int q = 0; q < 16 * MI / kWaves; ++q) {
+        const int i = wv + kWaves * q;
+        if (i < rows) {
+          const float d = (sum(i) + bn) - ep.t[e0 + (size_t)i * N];
+          ep.out[e0 + (size_t)i * N] = 2.f * d * ep.inv;
+          sq += d * d;
+        }
+      }
+    } else {
+#pragma unroll 1
+      for (int i = wv; i < rows; i += kWaves) {
+        const size_t e = e0 + (size_t)i * N;
+        epilogue(ep, e, epi_aux(ep, e, n), sum(i));
+      }
+    }
+  }
+  if (!split && ep.kind == kMse) {
+    __syncthreads();  // the partial tiles' LDS becomes the tree's
+    const float tot = block_tree<kWaves * 64>(sq, &s[0][0][0]);
+    if (threadIdx.x == 0) ep.loss_part[blockIdx.y * gridDim.x + blockIdx.x] = tot;
+  }
+}
+
+// Adam's constants of one step (beta1 0.9, beta2 0.999, eps 1e-8).
+struct AdamArgs {
+  float lr, bc1, bc2;
+};
+__device__ __forceinline__ void adam_f32(float* __restrict__ p, float* __restrict__ m,
+                                         float* __restrict__ v, size_t e, float ge,
+                                         const AdamArgs& c) {
+  const float mm = 0.9f * m[e] + 0.1f * ge;
+  const float vv = 0.999f * v[e] + 0.001f * ge * ge;
+  m[e] = mm;
+  v[e] = vv;
+  p[e] -= c.lr * (mm / c.bc1) / (sqrtf(vv / c.bc2) + 1e-8f);
+}
+
+// The block's tile (x, y), such that each XCD takes a contiguous run of tiles of
+// a row of the grid: blocks go to the 8 XCDs in turn.
+__device__ __forceinline__ int2 xcd_tile() {
+  const unsigned n = gridDim.x * gridDim.y, l = blockIdx.y * gridDim.x + blockIdx.x;
+  const unsigned x = l & 7, t = x * (n >> 3) + min(x, n & 7) + (l >> 3);
+  return {(int)(t % gridDim.x), (int)(t / gridDim.x)};
+}
+
+constexpr int kChain = 8;  // k-steps of one FP32 accumulation chain of a weight gradient
+
+// Weight and bias gradient of one layer, dW [M = fan_in][N = n_out] = in^T dZ
+// and db = column sums of dZ [K = batch][N], and with ADAM the update of the
+// layer's weights, biases and moments from them at once: the update needs 28
+// bytes per weight and would otherwise read the gradient again in a pass of
+// its own.  A block's tile goes through LDS so that a wavefront's accesses to
+// the parameters, the moments and the gradient are whole rows of 64.  The
+// column sums are formed by the blocks of the first row of tiles from the
+// staged operand, each column's rows in eight interleaved parts that are then
+// added in order.
+// Chains of kChain k-steps are added up in a second accumulator, so that the
+// rounding error does not grow with a long batch.
+// Bound by memory: at a batch of 64 the 15.1 M weights of 512 x 29412 (421 MB)
+// take 107 us, 4.0 TB/s (89 us with the product left out), the 5.7 M of
+// 11124 x 512 take 39; as products, column sums and a pass of updates these were
+// 32.7 + 15.8 + 101 us for the whole network.  Stores past the caches (read
+// again only in the next step) and neighbouring tiles on one XCD (rows are
+// not line-aligned, so neighbours share lines) give 4 and 3 us of it.  One kernel is
+// the faster at every batch: with sliced products and passes of their own
+// 11124 -> 3 x 512 -> 29412 takes 283 us a step at 64 rows against 264, and
+// 600 -> 3 x 512 -> 600 2597 us at 8192 rows against 1500.
+struct DwArgs {
+  float *gw, *gb;                        // gradients out
+  float *pw, *mw, *vw, *pb, *mb, *vb;    // ADAM: parameters and moments
+  AdamArgs adam;
+  // ADAM or not, block (0, 0) with loss != null: *loss = inv sum loss_part
+  const float* loss_part;
+  int n_loss;
+  float inv;
+  float* loss;
+};
+
+template <bool ADAM>
+__global__ __launch_bounds__(kGemm) void k_dw(const float* __restrict__ in, int fan_in,
+                                                 const float* __restrict__ dZ, int n_out, int batch,
+                                                 DwArgs w) {
+  __shared__ union alignas(16) {
+    TileLds t;
+    float c[kT][kT + 1];
+    float red[kGemm];
+  } s;
+  const int2 t = xcd_tile();
+  const int m0 = t.y * kT, n0 = t.x * kT;
+  const int c = threadIdx.x & 63, q8 = threadIdx.x >> 6;
+  const bool first = t.y == 0;
+  float cs = 0.f;  // this eighth's part of column n0 + c
+  constexpr int R = kT * kT / kGemm;  // elements per thread
+  const int n = n0 + c;
+  const int rows = n < n_out ? min(kT, fan_in - m0) : 0;
+  const size_t e0 = (size_t)m0 * n_out + n;
+  // parameters and moments, in flight with the product's operands
+  float p[R], m[R], v[R];
+  if constexpr (ADAM) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int row = q8 + 8 * i;
+      if (row < rows) {
+        const size_t e = e0 + (size_t)row * n_out;
+        p[i] = w.pw[e];
+        m[i] = w.mw[e];
+        v[i] = w.vw[e];
+      }
+    }
+  }
+  Tile tile;
+  v4f acc[2], done[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+  int left = kChain;
+  tile.run(in, fan_in, dZ, n_out, fan_in, n_out, 0, batch, m0, n0, s.t, acc, [&](int buf) {
+    if (first)
+      for (int k = q8; k < kBK; k += 8) cs += s.t.b[buf][c][k];
+    if (left-- == 0) {
+      left = kChain - 1;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        done[i] += acc[i];
+        acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  });
+  acc[0] += done[0];
+  acc[1] += done[1];
+  __syncthreads();
+  tile_elements(acc, 0, 0, kT, kT, [&](int row, int col, float v) { s.c[row][col] = v; });
+  __syncthreads();
+  if constexpr (ADAM) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int row = q8 + 8 * i;
+      if (row < rows) {
+        const size_t e = e0 + (size_t)row * n_out;
+        const float ge = s.c[row][c];
+        const float mm = 0.9f * m[i] + 0.1f * ge;
+        const float vv = 0.999f * v[i] + 0.001f * ge * ge;
+        __builtin_nontemporal_store(ge, &w.gw[e]);
+        __builtin_nontemporal_store(mm, &w.mw[e]);
+        __builtin_nontemporal_store(vv, &w.vw[e]);
+        __builtin_nontemporal_store(
+            p[i] - w.adam.lr * (mm / w.adam.bc1) / (sqrtf(vv / w.adam.bc2) + 1e-8f), &w.pw[e]);
+      }
+    }
+  } else {
+    for (int row = q8; row < rows; row += 8) w.gw[e0 + (size_t)row * n_out] = s.c[row][c];
+  }
+  if (!first) return;
+  __syncthreads();
+  s.red[threadIdx.x] = cs;
+  __syncthreads();
+  if (q8 == 0 && n < n_out) {
+    float g = s.red[c];
+    for (int q = 1; q < 8; ++q) g += s.red[q * 64 + c];
+    w.gb[n] = g;
+    if constexpr (ADAM) adam_f32(w.pb, w.mb, w.vb, (size_t)n, g, w.adam);
+  }
+  if (t.x == 0 && w.loss) {
+    float part = 0.f;
+    for (int i = threadIdx.x; i < w.n_loss; i += kGemm) part += w.loss_part[i];
+    __syncthreads();
+    const float tot = block_tree<kGemm>(part, s.red);
+    if (threadIdx.x == 0) *w.loss = tot * w.inv;
+  }
+}
+
+// BF16 operands (A32: A in FP32, rounded as it is staged), row-major A [M][K]
+// and B [K][N], FP32 sums; pipelined like the FP32 tile with DEPTH k-steps in
+// flight (a slice of one, of a multiple of three, or of another number).
+// APAIR, PAIR: two neighbouring elements of A, B per load (their rows' length and
+// base even).  Every output's products are added in the order of one accumulator
+// per slice.  Bound by the weights' first read: at 64 rows 512 x 29412 (30 MB) with
+// its biases takes 13.7 us and 11124 x 512 11.9; the whole forward pass of
+// 11124 -> 3 x 512 -> 29412 takes 42 us, and 83 with conversions, copies and an
+// unpipelined loop.
+template <int DEPTH, bool A32, bool APAIR, bool PAIR>
+__global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av, int lda,
                                                        const uint16_t* __restrict__ B, int ldb,
-                                                       float* __restrict__ C, int ldc, int M,
-                                                       int N, int K, int kslice) {
-  __shared__ uint16_t As[2][kT][32 + 8];  // [m][k]
-  __shared__ uint16_t Bs[2][kT][32 + 8];  // [n][k] (transposed for 8 consecutive k per lane)
+                                                       float* __restrict__ C, int M, int N, int K,
+                                                       int kslice, int split, EpiArgs ep) {
+  __shared__ alignas(16) uint16_t As[2][kT][kBK + 8];  // [m][k], 16-byte rows of 8 k
+  __shared__ alignas(16) uint16_t Bs[2][kT][kBK + 4];  // [n][k] (transposed), 8-byte halves
+  const float* __restrict__ Af = static_cast<const float*>(Av);
+  const uint16_t* __restrict__ Ah = static_cast<const uint16_t*>(Av);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int m0 = blockIdx.y * kT, n0 = blockIdx.x * kT;
   const int kb = blockIdx.z * kslice, ke = min(K, kb + kslice);
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-  v4f acc[2][2];
+  const int wm = (wv >> 2) * 32, wn = (wv & 3) * 16;
+  v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+  // A: FP32 element by element, BF16 in pairs of k where its rows are even;
+  // B: pairs (n, n + 1) of one k
+  float rf[DEPTH][kEl];
+  unsigned ra[DEPTH][kEl / 2], rb[DEPTH][kEl / 2];
+  unsigned oa[kEl], ob[kEl / 2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int q = 0; q < kEl; ++q) {
+    const int e = tid + q * kGemm;
+    oa[q] = A32 ? ((unsigned)(e >> 5) * lda + (e & 31)) * 4u
+                : ((unsigned)(e >> 4) * lda + 2 * (e & 15)) * 2u;
+    if (q < kEl / 2) ob[q] = ((unsigned)(e >> 5) * ldb + 2 * (e & 31)) * 2u;
+  }
+  auto pair = [](__amdgpu_buffer_rsrc_t v, unsigned o, bool whole) -> unsigned {
+    if (whole) return __builtin_amdgcn_raw_buffer_load_b32(v, o, 0, 0);
+    return (unsigned)__builtin_amdgcn_raw_buffer_load_b16(v, o, 0, 0) |
+           (unsigned)__builtin_amdgcn_raw_buffer_load_b16(v, o + 2, 0, 0) << 16;
+  };
+  auto load = [&](int d, int k0) {
+    if constexpr (A32) {
+      const __amdgpu_buffer_rsrc_t va = operand<false>(Af, lda, M, m0, k0, ke);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  uint16_t ra[8], rb[8];
-  auto gload = [&](int k0) {
+      for (int q = 0; q < kEl; ++q)
+        rf[d][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(va, oa[q], 0, 0));
+    } else {
+      const __amdgpu_buffer_rsrc_t va = operand<false>(Ah, lda, M, m0, k0, ke);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = tid + q * kThreads;  // 64 x 32 tile
-      const int mm = e >> 5, kk = e & 31;
-      const int gm = m0 + mm, gk = k0 + kk;
-      ra[q] = (gm < M && gk < ke) ? A[(size_t)gm * lda + gk] : (uint16_t)0;
+      for (int q = 0; q < kEl / 2; ++q) ra[d][q] = pair(va, oa[q], APAIR);
+    }
+    const __amdgpu_buffer_rsrc_t vb = operand<true>(B, ldb, N, n0, k0, ke);
+#pragma unroll
+    for (int q = 0; q < kEl / 2; ++q) rb[d][q] = pair(vb, ob[q], PAIR);
+  };
+  auto put = [&](int d, int buf, int left) {
+    if constexpr (A32) {
+#pragma unroll
+      for (int q = 0; q < kEl; ++q) {
+        const int e = tid + q * kGemm;
+        As[buf][e >> 5][e & 31] = (e & 31) < left ? to_bf16(rf[d][q]) : (uint16_t)0;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kEl / 2; ++q) {
+        const int e = tid + q * kGemm, k = 2 * (e & 15);
+        const unsigned v = k + 1 < left ? ra[d][q] : k < left ? ra[d][q] & 0xFFFFu : 0u;
+        *reinterpret_cast<unsigned*>(&As[buf][e >> 4][k]) = v;
+      }
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = tid + q * kThreads;  // 32 x 64 tile, coalesced along n
-      const int kk = e >> 6, nn = e & 63;
-      const int gk = k0 + kk, gn = n0 + nn;
-      rb[q] = (gn < N && gk < ke) ? B[(size_t)gk * ldb + gn] : (uint16_t)0;
+    for (int q = 0; q < kEl / 2; ++q) {
+      const int e = tid + q * kGemm;
+      const int k = e >> 5, n = 2 * (e & 31);
+      Bs[buf][n][k] = (uint16_t)rb[d][q];
+      Bs[buf][n + 1][k] = (uint16_t)(rb[d][q] >> 16);
     }
   };
-  if (kb < ke) gload(kb);
-  for (int k0 = kb, buf = 0; k0 < ke; k0 += 32, buf ^= 1) {
+  if (kb < ke) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = tid + q * kThreads;
-      As[buf][e >> 5][e & 31] = ra[q];
-      Bs[buf][e & 63][e >> 6] = rb[q];
-    }
+    for (int d = 0; d < DEPTH; ++d) load(d, kb + d * kBK);
+  }
+  auto step1 = [&](int d, int buf, int k0) {
+    put(d, buf, ke - k0);
     __syncthreads();
-    if (k0 + 32 < ke) gload(k0 + 32);
-    v8bf a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint16_t* src = &As[buf][wm + i * 16 + (lane & 15)][8 * (lane >> 4)];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[i][u] = __builtin_bit_cast(__bf16, src[u]);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint16_t* src = &Bs[buf][wn + j * 16 + (lane & 15)][8 * (lane >> 4)];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) b[j][u] = __builtin_bit_cast(__bf16, src[u]);
-    }
+    load(d, k0 + DEPTH * kBK);
+    v8bf a[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
+      a[i] = __builtin_bit_cast(
+          v8bf, *reinterpret_cast<const uint4*>(&As[buf][wm + i * 16 + (lane & 15)][8 * (lane >> 4)]));
+    const uint16_t* src = &Bs[buf][wn + (lane & 15)][8 * (lane >> 4)];
+    const uint2 lo = *reinterpret_cast<const uint2*>(src);
+    const uint2 hi = *reinterpret_cast<const uint2*>(src + 4);
+    const v8bf b = __builtin_bit_cast(v8bf, uint4{lo.x, lo.y, hi.x, hi.y});
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int i = 0; i < 2; ++i)
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i], 0, 0, 0);
+  };
+  // whole rounds of DEPTH k-steps, as in the FP32 tile
+  int buf = 0;
+  for (int k0 = kb; k0 < ke;) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d, k0 += kBK, buf ^= 1) step1(d, buf, k0);
   }
-  float* Cz = C + (size_t)blockIdx.z * M * ldc;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-        const int col = n0 + wn + j * 16 + (lane & 15);
-        if (row < M && col < N) Cz[(size_t)row * ldc + col] = acc[i][j][r];
-      }
+  if (split) {
+    float* Cz = C + (size_t)blockIdx.z * M * N;
+    tile_elements(acc, m0, n0, M, N,
+                  [&](int row, int col, float v) { Cz[(size_t)row * N + col] = v; });
+    return;
+  }
+  // the two kinds' bodies are kept apart: a launch meets a cold instruction cache
+  if (ep.kind == kBias) {
+    const int n = n0 + wn + (lane & 15);
+    const float b = n < N ? from_bf16(ep.bias16[n]) : 0.f;
+    tile_elements(acc, m0, n0, M, N,
+                  [&](int row, int col, float v) { ep.out[(size_t)row * N + col] = v + b; });
+    return;
+  }
+  tile_elements(acc, m0, n0, M, N, [&](int row, int col, float v) {
+    const size_t e = (size_t)row * N + col;
+    epilogue(ep, e, epi_aux(ep, e, col), v);
+  });
 }
 
 // out = epilogue(sum over slices of P[s][m][n]) for an M x N matrix (ld N).
-struct EpiArgs {
-  int kind;
-  const float* bias;  // [N]
-  float* z;           // kBiasGelu: pre-activation out; kGeluBwd: pre-activation in
-  float* out;         // float result
-  uint16_t* out16;    // kBiasGeluBf16
-};
-
 // The slices of 32 elements are summed by 8 groups of threads (group g takes
-// slices g, g + 8, ...), the group sums then added in group order: a fixed
-// order, with 8 independent chains of loads in flight per element.
+// slices g, g + 8, ..., eight loads in flight), the group sums then added in
+// group order: a fixed order.
 __global__ __launch_bounds__(kThreads) void k_reduce_epi(const float* __restrict__ P, int slices,
                                                          int M, int N, EpiArgs ep) {
   __shared__ float red[8][33];
   const size_t MN = (size_t)M * N;
   const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
   for (size_t e0 = (size_t)blockIdx.x * 32; e0 < MN; e0 += (size_t)gridDim.x * 32) {
-    const size_t ec = e0 + c;
+    const size_t e = e0 + c, ec = e < MN ? e : MN - 1;
+    Aux x{0.f, 0.f};
+    if (g == 0) x = epi_aux(ep, ec, (int)(ec % N));
     float part = 0.f;
-    if (ec < MN)
-      for (int q = g; q < slices; q += 8) part += P[(size_t)q * MN + ec];
+    for (int q0 = g; q0 < slices; q0 += 64) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = P[(size_t)min(q0 + 8 * u, slices - 1) * MN + ec];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (q0 + 8 * u < slices) part += v[u];
+    }
     red[g][c] = part;
     __syncthreads();
-    const size_t e = ec;
-    const bool mine = g == 0 && e < MN;
-    float s = 0.f;
-    if (mine)
+    if (g == 0 && e < MN) {
+      float s = 0.f;
+#pragma unroll
       for (int q = 0; q < 8; ++q) s += red[q][c];
-    __syncthreads();  // red is refilled by the next round
-    if (!mine) continue;
-    const int n = (int)(e % N);
-    switch (ep.kind) {
-      case kBiasGelu: {
-        const float z = s + ep.bias[n];
-        ep.z[e] = z;
-        ep.out[e] = gelu(z);
-        break;
-      }
-      case kBias: ep.out[e] = s + ep.bias[n]; break;
-      case kGeluBwd: ep.out[e] = s * gelu_d(ep.z[e]); break;
-      case kBiasGeluBf16: ep.out16[e] = to_bf16(gelu(s + ep.bias[n])); break;
-      default: ep.out[e] = s; break;
+      epilogue(ep, e, x, s);
     }
+    __syncthreads();  // red is refilled by the next round
   }
-}
-
-// db[n] = sum_m dZ[m][n]: 64 columns a block, each column's rows in four
-// interleaved quarters (thread q takes rows q, q + 4, ...), the quarters
-// then added in order
-__global__ __launch_bounds__(kThreads) void k_colsum(const float* __restrict__ dZ, int M, int N,
-                                                     float* __restrict__ db) {
-  __shared__ float red[4][64];
-  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + c;
-  float s = 0.f;
-  if (n < N)
-    for (int m = q; m < M; m += 4) s += dZ[(size_t)m * N + n];
-  red[q][c] = s;
-  __syncthreads();
-  if (q == 0 && n < N) db[n] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
 // dY = 2 (Y - T) / (M N); per-block partial sums of (Y - T)^2
@@ -280,47 +701,8 @@ __global__ __launch_bounds__(kThreads) void k_mse(const float* __restrict__ Y,
     dY[e] = 2.f * d * inv;
     acc += d * d;
   }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-// loss = inv * sum of the n <= kThreads block partials, by a tree in a fixed order
-__global__ __launch_bounds__(kThreads) void k_loss_final(const float* __restrict__ part, int n,
-                                                         float inv, float* loss) {
-  __shared__ float red[kThreads];
-  red[threadIdx.x] = (int)threadIdx.x < n ? part[threadIdx.x] : 0.f;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *loss = red[0] * inv;
-}
-
-__global__ __launch_bounds__(kThreads) void k_adam_f32(float* __restrict__ p, float* __restrict__ m,
-                                                       float* __restrict__ v,
-                                                       const float* __restrict__ g, size_t n,
-                                                       float lr, float bc1, float bc2) {
-  for (size_t e = (size_t)blockIdx.x * kThreads + threadIdx.x; e < n;
-       e += (size_t)gridDim.x * kThreads) {
-    const float ge = g[e];
-    const float mm = 0.9f * m[e] + 0.1f * ge;
-    const float vv = 0.999f * v[e] + 0.001f * ge * ge;
-    m[e] = mm;
-    v[e] = vv;
-    p[e] -= lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void k_from_bf16_bias(const uint16_t* __restrict__ b16,
-                                                             int n, float* __restrict__ b) {
-  const int e = blockIdx.x * kThreads + threadIdx.x;
-  if (e < n) b[e] = from_bf16(b16[e]);
+  const float tot = block_tree<kThreads>(acc, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
 __global__ __launch_bounds__(kThreads) void k_to_bf16(const float* __restrict__ x, size_t n,
@@ -333,6 +715,9 @@ __global__ __launch_bounds__(kThreads) void k_to_bf16(const float* __restrict__ 
 // ---------------------------------------------------------------------------
 // host side
 
+constexpr int kLossBlocks = 256;  // blocks of k_mse
+constexpr int kOneSlice = 512;    // most blocks of a product in tiles of 16 rows
+
 struct Ws {
   float* z[QG_MLP_MAX_DEPTH];  // pre-activations [B][width]
   float* h[QG_MLP_MAX_DEPTH];  // activations [B][width]
@@ -341,8 +726,9 @@ struct Ws {
   float* da;                   // [B][width]
   float* dz;                   // [B][width]
   float* part;                 // product slices
-  float* loss_part;            // [kLossBlocks]
-  uint16_t* a16[2];            // BF16 activations [B][max(d_in, width)]
+  float* loss_part;            // [loss_parts]
+  uint16_t* a16[2];            // BF16 activations [B][width]
+  int loss_parts;              // at most: blocks of k_mse, or of the output layer's product
   size_t part_floats;
   size_t total;
 };
@@ -371,10 +757,25 @@ void layout(const qg_mlp_desc* d, qg_mlp_layout* L) {
   L->n_params = o;
 }
 
-// product slices: about four blocks per CU when the output has few tiles,
-// each slice at least 32 deep (the pipelined k-loop needs a few k-steps)
-int slices_for(int M, int N, int K) {
-  const int tiles = ((M + kT - 1) / kT) * ((N + kT - 1) / kT);
+int tiles_of(int M, int N) { return ((M + kT - 1) / kT) * ((N + kT - 1) / kT); }
+
+// Slices of a deep FP32 product: about one block per CU, each slice at least 64
+// deep.  At 64 x 512 over 29412 or 11124 (8 tiles) 32 slices take 24.2 and 12.4 us,
+// 16 take 35.5 and 17.3, 64 take 30.6 and 17.7 (more sums to write, fewer rows
+// of the weights in each).
+int slices_f32(int M, int N, int K) {
+  const int tiles = tiles_of(M, N);
+  if (tiles >= 64 && K <= 512) return 1;  // no second kernel: 5.8 against 4.6 + 4.8 us (7353 x 200)
+  int s = 1;
+  while (s < kMaxSlices && tiles * s < 256 && K / (s * 2) >= 2 * kBK) s *= 2;
+  return s;
+}
+
+// Slices of a BF16 product.  The hidden layers' sums are rounded to BF16, so
+// their slices are part of the result: about four blocks per CU, each slice at
+// least 32 deep.
+int slices_bf16(int M, int N, int K) {
+  const int tiles = tiles_of(M, N);
   int s = 1;
   while (s < kMaxSlices && tiles * s < 1024 && K / (s * 2) >= 32) s *= 2;
   return s;
@@ -401,10 +802,10 @@ Ws carve(const qg_mlp_desc* d, int B, void* base) {
   // slices, or one B x d_out slice
   w.part_floats = std::max((size_t)kMaxSlices * BW, BO);
   w.part = reinterpret_cast<float*>(take(w.part_floats * 4));
-  w.loss_part = reinterpret_cast<float*>(take(kLossBlocks * 4));
-  const size_t wide = (size_t)B * std::max(d->d_in, d->width);
-  w.a16[0] = reinterpret_cast<uint16_t*>(take(wide * 2));
-  w.a16[1] = reinterpret_cast<uint16_t*>(take(wide * 2));
+  w.loss_parts = std::max(std::max(kLossBlocks, kOneSlice), tiles_of(B, d->d_out));
+  w.loss_part = reinterpret_cast<float*>(take((size_t)w.loss_parts * 4));
+  w.a16[0] = reinterpret_cast<uint16_t*>(take(BW * 2));
+  w.a16[1] = reinterpret_cast<uint16_t*>(take(BW * 2));
   w.total = o;
   return w;
 }
@@ -413,38 +814,99 @@ int grid1(size_t n) { return (int)std::min<size_t>(4096, (n + kThreads - 1) / kT
 // k_reduce_epi: 32 elements a block and round
 int grid_red(size_t n) { return (int)std::min<size_t>(4096, (n + 31) / 32); }
 
-// C = op(A) op(B) with epilogue; slices go through ws.part
 int fit_slices(int sl, int M, int N, const Ws& w) {
   while (sl > 1 && (size_t)sl * M * N > w.part_floats) sl /= 2;
   return sl;
 }
 
-hipError_t product(hipStream_t s, int ta, int tb, const float* A, int lda, const float* B, int ldb,
-                   int M, int N, int K, const EpiArgs& ep, const Ws& w) {
-  const int sl = fit_slices(slices_for(M, N, K), M, N, w);
-  const bool direct = (sl == 1 && ep.kind == kStore);
-  float* dst = direct ? ep.out : w.part;
-  const int kslice = ((K + sl - 1) / sl + 15) / 16 * 16;
-  const dim3 grid((N + kT - 1) / kT, (M + kT - 1) / kT, sl);
-  if (!ta && !tb) hipLaunchKernelGGL((k_gemm_f32<0, 0>), grid, dim3(kThreads), 0, s, A, lda, B, ldb, dst, N, M, N, K, kslice);
-  else if (ta && !tb) hipLaunchKernelGGL((k_gemm_f32<1, 0>), grid, dim3(kThreads), 0, s, A, lda, B, ldb, dst, N, M, N, K, kslice);
-  else if (!ta && tb) hipLaunchKernelGGL((k_gemm_f32<0, 1>), grid, dim3(kThreads), 0, s, A, lda, B, ldb, dst, N, M, N, K, kslice);
-  else hipLaunchKernelGGL((k_gemm_f32<1, 1>), grid, dim3(kThreads), 0, s, A, lda, B, ldb, dst, N, M, N, K, kslice);
-  if (!direct)
-    hipLaunchKernelGGL(k_reduce_epi, dim3(grid_red((size_t)M * N)), dim3(kThreads), 0, s, w.part,
-                       sl, M, N, ep);
+// How k_product computes an M x N product over K: tiles of 16 mi rows, at most
+// sl slices.  A product that is not deep and has few tiles is cut into tiles of 16
+// rows, read with eight wavefronts a block, instead of slices: the second kernel
+// costs more than the weights' repeated reads from L2.  One forward pass of
+// 600 -> 3 x 512 -> 600 at 64 rows takes 26.6 us in this way, 35.4 in slices; of
+// 1400 -> 2 x 256 -> 3300 18.1, in slices 30.2.  With more blocks than kOneSlice the
+// repeated reads win (29412 outputs: 79.7 us a pass against 53.7).  The transposed
+// product reads 64 bytes of each of the weights' rows at a time, which a few
+// blocks do slowly over a long reduction: 600 -> 3 x 512 -> 600 trains in 85.8 us with
+// the limit at 256, in 92.4 with 512, and 1400 -> 2 x 256 -> 3300 in 62.4, in 63.0
+// with 128.
+struct Plan {
+  int mi, sl;
+};
+Plan plan_f32(int tb, int M, int N, int K, const Ws& w) {
+  const int64_t t16 = (int64_t)((M + 15) / 16) * ((N + kT - 1) / kT);
+  if (K <= (tb ? 256 : 1024) && t16 <= kOneSlice) return {1, 1};
+  return {M <= 16 ? 1 : M <= 32 ? 2 : 4, fit_slices(slices_f32(M, N, K), M, N, w)};
+}
+int blocks_of(const Plan& p, int M, int N) {
+  return ((M + 16 * p.mi - 1) / (16 * p.mi)) * ((N + kT - 1) / kT);
+}
+
+// The slices' sums of an M x N product in w.part through the epilogue.
+void reduce_epi(hipStream_t s, const Ws& w, int slices, int M, int N, const EpiArgs& ep) {
+  hipLaunchKernelGGL(k_reduce_epi, dim3(grid_red((size_t)M * N)), dim3(kThreads), 0, s, w.part,
+                     slices, M, N, ep);
+}
+
+// A op(B) with epilogue as planned; slices go through ws.part
+hipError_t product(hipStream_t s, int tb, const float* A, int lda, const float* B, int ldb, int M,
+                   int N, int K, const Plan& p, const EpiArgs& ep, const Ws& w) {
+  const int kRound = waves_of(p.mi) * kStep;
+  const int kslice = ((K + p.sl - 1) / p.sl + kRound - 1) / kRound * kRound;
+  const int sl = (K + kslice - 1) / kslice;
+  const int split = sl > 1;
+  const dim3 grid((N + kT - 1) / kT, (M + 16 * p.mi - 1) / (16 * p.mi), sl);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(waves_of(p.mi) * 64), 0, s, A, lda, B, ldb, w.part, M, N,
+                       K, kslice, split, ep);
+  };
+  auto rows = [&](auto t) {
+    constexpr int T = decltype(t)::value;
+    const int steps = kslice / kRound;  // of a wavefront
+    if (p.mi == 1) {
+      if (steps == 1) go(k_product<1, 1, T>);
+      else if (steps == 2) go(k_product<2, 1, T>);
+      else go(k_product<4, 1, T>);
+    } else if (p.mi == 2) {
+      if (steps == 1) go(k_product<1, 2, T>);
+      else go(k_product<2, 2, T>);
+    } else {
+      if (steps == 1) go(k_product<1, 4, T>);
+      else go(k_product<2, 4, T>);
+    }
+  };
+  if (tb) rows(std::integral_constant<int, 1>{});
+  else rows(std::integral_constant<int, 0>{});
+  if (split) reduce_epi(s, w, sl, M, N, ep);
   return hipGetLastError();
 }
 
-hipError_t product16(hipStream_t s, const uint16_t* A, int lda, const uint16_t* B, int ldb, int M,
-                     int N, int K, const EpiArgs& ep, const Ws& w) {
-  const int sl = fit_slices(slices_for(M, N, K), M, N, w);
-  const int kslice = ((K + sl - 1) / sl + 31) / 32 * 32;
+// A B with BF16 operands (a32: A in FP32)
+hipError_t product16(hipStream_t s, const void* A, bool a32, int lda, const uint16_t* B, int M,
+                     int N, int K, int sl, const EpiArgs& ep, const Ws& w) {
+  const int kslice = ((K + sl - 1) / sl + kBK - 1) / kBK * kBK;
+  const int split = sl > 1;
   const dim3 grid((N + kT - 1) / kT, (M + kT - 1) / kT, sl);
-  hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(kThreads), 0, s, A, lda, B, ldb, w.part, N, M, N, K,
-                     kslice);
-  hipLaunchKernelGGL(k_reduce_epi, dim3(grid_red((size_t)M * N)), dim3(kThreads), 0, s, w.part, sl,
-                     M, N, ep);
+  const bool pair = N % 2 == 0 && (reinterpret_cast<uintptr_t>(B) & 3u) == 0;
+  const bool apair = lda % 2 == 0;  // A is the workspace's
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kGemm), 0, s, A, lda, B, N, w.part, M, N, K, kslice,
+                       split, ep);
+  };
+  auto depth = [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    if (a32 && pair) go(k_gemm_bf16<D, true, false, true>);
+    else if (a32) go(k_gemm_bf16<D, true, false, false>);
+    else if (apair && pair) go(k_gemm_bf16<D, false, true, true>);
+    else if (apair) go(k_gemm_bf16<D, false, true, false>);
+    else if (pair) go(k_gemm_bf16<D, false, false, true>);
+    else go(k_gemm_bf16<D, false, false, false>);
+  };
+  const int steps = kslice / kBK;
+  if (steps == 1) depth(std::integral_constant<int, 1>{});
+  else if (steps % 3 == 0) depth(std::integral_constant<int, 3>{});
+  else depth(std::integral_constant<int, 2>{});
+  if (split) reduce_epi(s, w, sl, M, N, ep);
   return hipGetLastError();
 }
 
@@ -461,20 +923,99 @@ qg_status dev_fail(hipError_t e, const char* where) {
   return qg::fail(QG_ERR_DEVICE, std::string(where) + ": " + hipGetErrorString(e));
 }
 
-// forward in FP32, activations kept for the reverse pass
+// forward in FP32, activations kept for the reverse pass; the output layer's
+// product ends in out (with its bias, an epilogue of kind kBias or kMse)
 hipError_t forward(hipStream_t s, const qg_mlp_desc* d, const qg_mlp_layout& L, const float* P,
-                   const float* x, int B, const Ws& w) {
+                   const float* x, int B, EpiArgs out, const Plan& out_plan, const Ws& w) {
   const float* in = x;
   int fan_in = d->d_in;
   for (int i = 0; i < d->depth; ++i) {
-    EpiArgs ep{kBiasGelu, P + L.b_off[i], w.z[i], w.h[i], nullptr};
-    hipError_t e = product(s, 0, 0, in, fan_in, P + L.w_off[i], d->width, B, d->width, fan_in, ep, w);
+    EpiArgs ep{};
+    ep.kind = kBiasGelu;
+    ep.bias = P + L.b_off[i];
+    ep.z = w.z[i];
+    ep.out = w.h[i];
+    hipError_t e = product(s, 0, in, fan_in, P + L.w_off[i], d->width, B, d->width, fan_in,
+                           plan_f32(0, B, d->width, fan_in, w), ep, w);
     if (e != hipSuccess) return e;
     in = w.h[i];
     fan_in = d->width;
   }
-  EpiArgs ep{kBias, P + L.b_off[d->depth], nullptr, w.y, nullptr};
-  return product(s, 0, 0, in, fan_in, P + L.w_off[d->depth], d->d_out, B, d->d_out, fan_in, ep, w);
+  out.bias = P + L.b_off[d->depth];
+  return product(s, 0, in, fan_in, P + L.w_off[d->depth], d->d_out, B, d->d_out, fan_in,
+                 out_plan, out, w);
+}
+
+// Adam's state of a training step.
+struct Update {
+  float *p, *m, *v;
+  AdamArgs adam;
+};
+
+// Loss, gradient and (u non-null) the update; null buffers checked before.
+hipError_t grad_step(hipStream_t s, const qg_mlp_desc* d, const qg_mlp_layout& L, const float* P,
+                     const float* x, const float* t, int B, float* grad, float* loss,
+                     const Update* u, const Ws& w) {
+  const int D = d->depth, W = d->width;
+  const size_t BO = (size_t)B * d->d_out;
+  const float inv = 1.0f / (float)BO;
+  const Plan op = plan_f32(0, B, d->d_out, W, w);
+  const bool one = op.sl == 1;  // the output layer's product ends in dY and the loss
+  EpiArgs out{};
+  out.kind = one ? kMse : kBias;
+  out.out = one ? w.dy : w.y;
+  out.t = t;
+  out.inv = inv;
+  out.loss_part = w.loss_part;
+  hipError_t e = forward(s, d, L, P, x, B, out, op, w);
+  if (e != hipSuccess) return e;
+  int n_loss = blocks_of(op, B, d->d_out);
+  if (!one) {
+    n_loss = kLossBlocks;
+    hipLaunchKernelGGL(k_mse, dim3(kLossBlocks), dim3(kThreads), 0, s, w.y, t, BO, inv, w.dy,
+                       w.loss_part);
+  }
+  // output layer: dW_out = h_D^T dY, db_out = colsum dY, dh_D = dY W_out^T
+  const float* dcur = w.dy;  // gradient at the current layer's output
+  int n_out = d->d_out;
+  for (int i = D; i >= 0; --i) {
+    const float* in = (i == 0) ? x : w.h[i - 1];
+    const int fan_in = (i == 0) ? d->d_in : W;
+    float* dst = (dcur == w.dz) ? w.da : w.dz;
+    if (i > 0) {
+      // dz_{i-1} = (dcur W_i^T) * gelu'(z_{i-1}), W_i is [fan_in][n_out]; before
+      // the layer's update
+      EpiArgs ep{};
+      ep.kind = kGeluBwd;
+      ep.z = w.z[i - 1];
+      ep.out = dst;
+      e = product(s, 1, dcur, n_out, P + L.w_off[i], n_out, B, fan_in, n_out,
+                  plan_f32(1, B, fan_in, n_out, w), ep, w);
+      if (e != hipSuccess) return e;
+    }
+    const size_t wo = (size_t)L.w_off[i], bo = (size_t)L.b_off[i];
+    DwArgs a{};
+    a.gw = grad + wo;
+    a.gb = grad + bo;
+    if (i == D) {
+      a.loss_part = w.loss_part;
+      a.n_loss = n_loss;
+      a.inv = inv;
+      a.loss = loss;
+    }
+    const dim3 grid((n_out + kT - 1) / kT, (fan_in + kT - 1) / kT);
+    if (u) {
+      a.pw = u->p + wo; a.mw = u->m + wo; a.vw = u->v + wo;
+      a.pb = u->p + bo; a.mb = u->m + bo; a.vb = u->v + bo;
+      a.adam = u->adam;
+      hipLaunchKernelGGL(k_dw<true>, grid, dim3(kGemm), 0, s, in, fan_in, dcur, n_out, B, a);
+    } else {
+      hipLaunchKernelGGL(k_dw<false>, grid, dim3(kGemm), 0, s, in, fan_in, dcur, n_out, B, a);
+    }
+    dcur = dst;
+    n_out = W;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -499,9 +1040,11 @@ qg_status qg_mlp_forward(const qg_mlp_desc* desc, const float* d_params, const f
   layout(desc, &L);
   const Ws w = carve(desc, batch, d_ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = forward(s, desc, L, d_params, d_x, batch, w);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_y, w.y, (size_t)batch * desc->d_out * 4, hipMemcpyDeviceToDevice, s);
+  EpiArgs out{};
+  out.kind = kBias;
+  out.out = d_y;
+  hipError_t e = forward(s, desc, L, d_params, d_x, batch, out,
+                         plan_f32(0, batch, desc->d_out, desc->width, w), w);
   return e == hipSuccess ? QG_OK : dev_fail(e, "mlp forward");
 }
 
@@ -515,36 +1058,7 @@ qg_status qg_mlp_grad(const qg_mlp_desc* desc, const float* d_params, const floa
   layout(desc, &L);
   const Ws w = carve(desc, batch, d_ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int B = batch, D = desc->depth, W = desc->width;
-  hipError_t e = forward(s, desc, L, d_params, d_x, B, w);
-  if (e != hipSuccess) return dev_fail(e, "mlp forward");
-  const size_t BO = (size_t)B * desc->d_out;
-  const float inv = 1.0f / (float)BO;
-  hipLaunchKernelGGL(k_mse, dim3(kLossBlocks), dim3(kThreads), 0, s, w.y, d_t, BO, inv, w.dy,
-                     w.loss_part);
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kThreads), 0, s, w.loss_part, kLossBlocks, inv,
-                     d_loss);
-  // output layer: dW_out = h_D^T dY, db_out = colsum dY, dh_D = dY W_out^T
-  const float* dcur = w.dy;  // gradient at the current layer's output
-  int n_out = desc->d_out;
-  for (int i = D; i >= 0; --i) {
-    const float* in = (i == 0) ? d_x : w.h[i - 1];
-    const int fan_in = (i == 0) ? desc->d_in : W;
-    EpiArgs ew{kStore, nullptr, nullptr, d_grad + L.w_off[i], nullptr};
-    e = product(s, 1, 0, in, fan_in, dcur, n_out, fan_in, n_out, B, ew, w);
-    if (e != hipSuccess) return dev_fail(e, "mlp weight gradient");
-    hipLaunchKernelGGL(k_colsum, dim3((n_out + 63) / 64), dim3(kThreads), 0, s, dcur, B, n_out,
-                       d_grad + L.b_off[i]);
-    if (i == 0) break;
-    // dz_{i-1} = (dcur W_i^T) * gelu'(z_{i-1}), W_i is [fan_in][n_out]
-    float* dst = (dcur == w.dz) ? w.da : w.dz;
-    EpiArgs eb{kGeluBwd, nullptr, w.z[i - 1], dst, nullptr};
-    e = product(s, 0, 1, dcur, n_out, d_params + L.w_off[i], n_out, B, fan_in, n_out, eb, w);
-    if (e != hipSuccess) return dev_fail(e, "mlp activation gradient");
-    dcur = dst;
-    n_out = W;
-  }
-  e = hipGetLastError();
+  hipError_t e = grad_step(s, desc, L, d_params, d_x, d_t, batch, d_grad, d_loss, nullptr, w);
   return e == hipSuccess ? QG_OK : dev_fail(e, "mlp reverse");
 }
 
@@ -552,17 +1066,18 @@ qg_status qg_mlp_train_step(const qg_mlp_desc* desc, float* d_params, float* d_m
                             float* d_grad, const float* d_x, const float* d_t, int32_t batch,
                             int64_t iter, float lr, float* d_loss, void* d_ws, void* stream) {
   if (!d_m || !d_v || iter < 1 || !(lr > 0.f)) return qg::fail(QG_ERR_ARG, "bad Adam arguments");
-  qg_status st = qg_mlp_grad(desc, d_params, d_x, d_t, batch, d_grad, d_loss, d_ws, stream);
+  qg_status st = check_common(desc, batch, d_ws);
   if (st != QG_OK) return st;
+  if (!d_params || !d_x || !d_t || !d_grad || !d_loss) return qg::fail(QG_ERR_ARG, "null buffer");
   qg_mlp_layout L;
   layout(desc, &L);
+  const Ws w = carve(desc, batch, d_ws);
   const float bc1 = 1.0f - std::pow(0.9f, (float)iter);
   const float bc2 = 1.0f - std::pow(0.999f, (float)iter);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_adam_f32, dim3(grid1((size_t)L.n_params)), dim3(kThreads), 0, s, d_params,
-                     d_m, d_v, d_grad, (size_t)L.n_params, lr, bc1, bc2);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? QG_OK : dev_fail(e, "mlp Adam");
+  const Update u{d_params, d_m, d_v, AdamArgs{lr, bc1, bc2}};
+  hipError_t e = grad_step(static_cast<hipStream_t>(stream), desc, L, d_params, d_x, d_t, batch,
+                           d_grad, d_loss, &u, w);
+  return e == hipSuccess ? QG_OK : dev_fail(e, "mlp training step");
 }
 
 qg_status qg_mlp_to_bf16(const qg_mlp_desc* desc, const float* d_params, uint16_t* d_params16,
@@ -588,27 +1103,31 @@ qg_status qg_mlp_forward_bf16(const qg_mlp_desc* desc, const uint16_t* d_params1
   const Ws w = carve(desc, batch, d_ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int B = batch;
-  hipLaunchKernelGGL(k_to_bf16, dim3(grid1((size_t)B * desc->d_in)), dim3(kThreads), 0, s, d_x,
-                     (size_t)B * desc->d_in, w.a16[0]);
-  // the epilogue adds each layer's bias widened from its BF16 image (scratch:
-  // ws.dz for hidden layers, ws.dy for the output layer)
-  int cur = 0, fan_in = desc->d_in;
+  const void* in = d_x;
+  int fan_in = desc->d_in;
   hipError_t e = hipSuccess;
   for (int i = 0; i < desc->depth && e == hipSuccess; ++i) {
-    hipLaunchKernelGGL(k_from_bf16_bias, dim3((desc->width + kThreads - 1) / kThreads),
-                       dim3(kThreads), 0, s, d_params16 + L.b_off[i], desc->width, w.dz);
-    EpiArgs ep{kBiasGeluBf16, w.dz, nullptr, nullptr, w.a16[cur ^ 1]};
-    e = product16(s, w.a16[cur], fan_in, d_params16 + L.w_off[i], desc->width, B, desc->width,
-                  fan_in, ep, w);
-    cur ^= 1;
+    EpiArgs ep{};
+    ep.kind = kBiasGeluBf16;
+    ep.bias16 = d_params16 + L.b_off[i];
+    ep.out16 = w.a16[i & 1];
+    const int sl = fit_slices(slices_bf16(B, desc->width, fan_in), B, desc->width, w);
+    e = product16(s, in, i == 0, fan_in, d_params16 + L.w_off[i], B, desc->width, fan_in, sl, ep,
+                  w);
+    in = w.a16[i & 1];
     fan_in = desc->width;
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_from_bf16_bias, dim3((desc->d_out + kThreads - 1) / kThreads),
-                       dim3(kThreads), 0, s, d_params16 + L.b_off[desc->depth], desc->d_out, w.dy);
-    EpiArgs ep{kBias, w.dy, nullptr, d_y, nullptr};
-    e = product16(s, w.a16[cur], fan_in, d_params16 + L.w_off[desc->depth], desc->d_out, B,
-                  desc->d_out, fan_in, ep, w);
+    EpiArgs ep{};
+    ep.kind = kBias;
+    ep.bias16 = d_params16 + L.b_off[desc->depth];
+    ep.out = d_y;
+    // one slice where the output has tiles enough: no second kernel
+    const int sl = tiles_of(B, desc->d_out) >= 64 && fan_in <= 1024
+                       ? 1
+                       : fit_slices(slices_bf16(B, desc->d_out, fan_in), B, desc->d_out, w);
+    e = product16(s, in, false, fan_in, d_params16 + L.w_off[desc->depth], B, desc->d_out, fan_in,
+                  sl, ep, w);
   }
   if (e == hipSuccess) e = hipGetLastError();
   return e == hipSuccess ? QG_OK : dev_fail(e, "mlp bf16 forward");

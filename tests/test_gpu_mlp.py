@@ -152,3 +152,45 @@ def test_deterministic(qg):
     g2 = net.grad_and_loss(xd, td)[0].cpu().numpy().copy()
     torch.cuda.synchronize()
     assert np.array_equal(a, b) and np.array_equal(g1, g2)
+
+
+# edges of the products: reduction tails, odd row lengths, one to four blocks
+# of 16 batch rows and the first of a second tile, an output layer with tiles
+# enough for one slice (its loss comes from the product), a batch past which the
+# weight gradient is a product of its own
+EDGE_SHAPES = [(33, 65, 1, 67, 1), (130, 63, 2, 4200, 16), (257, 97, 1, 4161, 33),
+               (64, 32, 2, 40, 65), (50, 41, 1, 61, 257)]
+
+
+@pytest.mark.parametrize("shape", EDGE_SHAPES)
+def test_product_edges(qg, shape):
+    """Products of at most 4,200 FP32 terms carry under sqrt(4200) 2^-24 = 4e-6
+    relative error: outputs, loss and first moments at 2e-5 normwise as above,
+    second moments (squares) at twice that, the BF16 forward at 3e-2.  The update
+    itself follows from the stored moments in a handful of FP32 roundings: within
+    1e-5 of the learning rate and an ulp of the parameter."""
+    import torch
+    net, params, x, t, xd, td = make(qg, *shape, seed=sum(shape))
+    p0 = net.params.cpu().numpy().astype(np.float64)
+    y = net.forward(xd)
+    y16 = net.forward_bf16(xd)
+    torch.cuda.synchronize()
+    y_ref = omlp.forward(params, x)
+    assert rel(y.cpu().numpy(), y_ref) < 2e-5
+    assert rel(y16.cpu().numpy(), y_ref) < 3e-2
+    loss_ref, grads_ref = omlp.loss_and_grad(params, x, t)
+    g, loss = net.grad_and_loss(xd, td)
+    loss1 = net.train_step(xd, td, 1e-3)
+    torch.cuda.synchronize()
+    assert abs(float(loss) - loss_ref) <= 2e-5 * loss_ref
+    assert abs(float(loss1) - loss_ref) <= 2e-5 * loss_ref
+    g, p1, m, v = (a.cpu().numpy().astype(np.float64) for a in (g, net.params, net.m, net.v))
+    for i, (dW, db) in enumerate(grads_ref):
+        wo, bo = net.offsets(i)
+        for off, ref in ((wo, dW.reshape(-1)), (bo, db)):
+            sl = slice(off, off + ref.size)
+            assert rel(g[sl], ref) < 2e-5, i
+            assert rel(m[sl], 0.1 * ref) < 2e-5, i
+            assert rel(v[sl], 0.001 * ref ** 2) < 4e-5, i
+            want = p0[sl] - 1e-3 * (m[sl] / 0.1) / (np.sqrt(v[sl] / 0.001) + 1e-8)
+            assert np.all(np.abs(p1[sl] - want) <= 1e-8 + 2.0 ** -23 * np.abs(want)), i
