@@ -188,7 +188,7 @@ struct Problem {
   int nb_br;      // blocks of the per-(t, branch) kernels
   int nb_bus;     // blocks of the per-(t, bus chunk) kernels
   int bus_chunks; // bus chunks per period
-  int nb_gen;     // blocks of the per-(t, generator) final stage
+  int nb_gen;     // blocks of one variable of every (t, generator) in the final stage
   int nsplit;     // reduction splits of the adjoint product
   int nKc, nLc;   // chunks of Kp (64 wide) and Lp (256 wide)
   CtgTile tile;

@@ -41,8 +41,6 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 struct StepParams {
   double eps, beta, rho_s;
-  double alpha[QG_NCLASS];
-  double bc1, bc2;
 };
 
 struct EvalArgs {
@@ -363,27 +361,14 @@ __device__ __forceinline__ double strided_sum(const double* src, int n, size_t s
   return acc;
 }
 
-// Homotopy and step sizes of this step: from the arguments, or from the row
-// of the schedule table (eqs. (norm_t)-(step_size), evaluated on the host per
-// iteration) that the step counter points at.
-__device__ void resolve_params(const EvalArgs& a, StepParams& sp) {
-  if (a.mode.schedule == 0) {
-    sp.eps = a.mode.eps;
-    sp.beta = a.mode.beta;
-    sp.rho_s = a.mode.rho_s;
-    for (int c = 0; c < QG_NCLASS; ++c) sp.alpha[c] = 0.0;
-    sp.bc1 = sp.bc2 = 1.0;
-    return;
-  }
-  // the row of this step, copied ahead by the previous step (k_ctg_asm) or
-  // by k_set_step: one load instead of the counter and then the row
+// Homotopy of this step: from the arguments, or from the row of the schedule
+// table (eqs. (norm_t)-(step_size), evaluated on the host per iteration) that the
+// step counter points at, copied ahead by the previous step (k_ctg_asm) or by
+// k_set_step: one load instead of the counter and then the row.
+__device__ __forceinline__ StepParams resolve_params(const EvalArgs& a) {
+  if (a.mode.schedule == 0) return {a.mode.eps, a.mode.beta, a.mode.rho_s};
   const double* row = a.w.snext;
-  sp.eps = row[0];
-  sp.beta = row[1];
-  sp.rho_s = row[2];
-  for (int c = 0; c < QG_NCLASS; ++c) sp.alpha[c] = row[3 + c];
-  sp.bc1 = row[9];
-  sp.bc2 = row[10];
+  return {row[0], row[1], row[2]};
 }
 
 // Contribution of one overloaded outage element: with s = sqrt(s2),
@@ -414,21 +399,35 @@ __device__ __forceinline__ R ctg_overload(R P, R s2, R smx, R eps, R eps2, R kt,
 
 constexpr int kSegChunk = 1024;
 
-template <int NV>
-__device__ __forceinline__ void bus_segsum(const double* const (&src)[NV], const int* bptr,
-                                           int i0, int nbus, double* lds, double (&acc)[NV]) {
+// A chunk's slots are all in flight at once; ahead() issues loads of the
+// caller's that go out with the first chunk's.
+template <int NV, class Ahead>
+__device__ __forceinline__ void bus_segsum(const double* const (&src)[NV], const DevProblem& p,
+                                           int i0, int nbus, double* lds, double (&acc)[NV],
+                                           Ahead ahead) {
+  constexpr int U = kSegChunk / kBlock;
   const int tid = threadIdx.x;
-  const int s_lo = bptr[i0], s_hi = bptr[i0 + nbus];
+  const int* bptr = p.bptr;
+  // the ends of the whole range are known without a load to wait for
+  const int s_lo = i0 == 0 ? 0 : bptr[i0], s_hi = i0 + nbus == p.N ? p.twoL : bptr[i0 + nbus];
   int a = 0, b = 0;
   if (tid < nbus) { a = bptr[i0 + tid]; b = bptr[i0 + tid + 1]; }
+  ahead();
 #pragma unroll
   for (int q = 0; q < NV; ++q) acc[q] = 0.0;
   for (int c0 = s_lo; c0 < s_hi; c0 += kSegChunk) {
     const int c1 = min(c0 + kSegChunk, s_hi);
-    for (int s = c0 + tid; s < c1; s += kBlock) {
+    double v[NV][U];
 #pragma unroll
-      for (int q = 0; q < NV; ++q) lds[q * kSegChunk + (s - c0)] = src[q][s];
+    for (int u = 0; u < U; ++u) {
+      const int s = min(c0 + u * kBlock + tid, c1 - 1);
+#pragma unroll
+      for (int q = 0; q < NV; ++q) v[q][u] = src[q][s];
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < NV; ++q) lds[q * kSegChunk + u * kBlock + tid] = v[q][u];
     __syncthreads();
     const int lo = max(a, c0), hi = min(b, c1);
     for (int s = lo; s < hi; ++s) {
@@ -571,19 +570,17 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     w.epQ[ep + p.slot_fr[l]] = qf;
     w.epQ[ep + p.slot_to[l]] = qt;
     // thermal penalty on the larger side (ties: from side), Example 1
-    const double sf = sqrt(pf * pf + qf * qf), st = sqrt(pt * pt + qt * qt);
-    const bool use_f = sf >= st;
-    const double eb = (use_f ? sf : st) - p.br_smax[l];
+    const double sf2 = pf * pf + qf * qf, st2 = pt * pt + qt * qt;
+    const bool use_f = sf2 >= st2;
+    const double ss2 = use_f ? sf2 : st2;
+    const double rs = ss2 > 0.0 ? rsqrt_nr(ss2) : 0.0;
+    const double eb = ss2 * rs - p.br_smax[l];
     const double kbr = p.dt[t] * p.c_s * sp.beta;
     double kth;
     part[0] = kbr * soft_relu_pair(eb, sp.eps, kth);
-    kth *= kbr;
-    double kpf = 0.0, kqf = 0.0, kpt = 0.0, kqt = 0.0;
-    if (use_f) {
-      if (sf > 0.0) { kpf = kth * pf / sf; kqf = kth * qf / sf; }
-    } else {
-      if (st > 0.0) { kpt = kth * pt / st; kqt = kth * qt / st; }
-    }
+    kth *= kbr * rs;
+    const double kpf = use_f ? kth * pf : 0.0, kqf = use_f ? kth * qf : 0.0;
+    const double kpt = use_f ? 0.0 : kth * pt, kqt = use_f ? 0.0 : kth * qt;
     // angle-difference penalty
     const double ea = fabs(d) - p.ang_max;
     const double kang = p.dt[t] * p.c_ang * sp.beta;
@@ -769,10 +766,9 @@ __device__ void reserve_pad_block(const EvalArgs& a, const StepParams& sp, int t
   for (int k = p.K + tid; k < p.Kp; k += kBlock) w.Fk[(size_t)t * p.Kp + k] = 0.0;
 }
 
-// LDS of a kernel that runs both segmented sums and an MFMA slab: the slab
-// keeps four wavefronts x up to 4 row tiles x 256 partial results.
+// LDS of an MFMA slab: four wavefronts x up to 4 row tiles x 256 partial
+// results.
 constexpr int kSlabLds = 4 * 4 * 256;
-static_assert(kSlabLds >= 2 * kSegChunk + 8 * kBlock, "LDS carve");
 // LDS of the forward kernel: the flow slab's single row tile (its block sums
 // need 32 doubles), so that LDS does not limit its blocks per CU.
 constexpr int kFwdLds = 4 * 1 * 256;
@@ -823,16 +819,24 @@ __device__ void flow_slab(const EvalArgs& a, int blk, double* smem) {
 // Blocks [0, T): the reserve shortfall and the padding of one period each;
 // [T, T + nb_br): branch forward; then (Lp / 16) x (Tp / 16) flow slabs.
 __device__ __forceinline__ void forward_body(const EvalArgs& a, int b, double* smem) {
-  StepParams sp;
-  resolve_params(a, sp);
-  if (b == 0 && threadIdx.x == 0) {
+  const StepParams sp = resolve_params(a);
+  if (b == 0 && threadIdx.x < QG_NCLASS + 3) {
+    // the step's parameters for the later kernels, with the row's step sizes and
+    // bias corrections (0 and 1 without a schedule); one entry a thread: an
+    // array indexed by a loop would live in scratch memory, whose set-up delays
+    // the kernel that follows
     double* pb = a.w.params;
-    pb[PB_EPS] = sp.eps;
-    pb[PB_BETA] = sp.beta;
-    pb[PB_RHO] = sp.rho_s;
-    for (int c = 0; c < QG_NCLASS; ++c) pb[PB_ALPHA + c] = sp.alpha[c];
-    pb[PB_BC1] = sp.bc1;
-    pb[PB_BC2] = sp.bc2;
+    const int c = threadIdx.x;
+    const bool sched = a.mode.schedule != 0;
+    if (c < QG_NCLASS)
+      pb[PB_ALPHA + c] = sched ? a.w.snext[3 + c] : 0.0;
+    else if (c == QG_NCLASS)
+      pb[PB_EPS] = sp.eps;
+    else if (c == QG_NCLASS + 1)
+      pb[PB_BETA] = sp.beta;
+    else
+      pb[PB_RHO] = sp.rho_s;
+    if (c < 2) pb[PB_BC1 + c] = sched ? a.w.snext[3 + QG_NCLASS + c] : 1.0;
   }
   if (b < a.p.T)
     reserve_pad_block(a, sp, b, smem);
@@ -860,22 +864,33 @@ __device__ void bus_balance(const EvalArgs& a, int blk, double* smem) {
   const int nbus = min(kBlock, p.N - i0);
   const double eps = w.params[PB_EPS], beta = w.params[PB_BETA];
   const double* src[2] = {w.epP + (size_t)t * p.twoL, w.epQ + (size_t)t * p.twoL};
+  // the bus's loads and its first generator, in flight with the endpoint flows
+  const int i = i0 + tid;
+  const size_t ti = (size_t)t * p.N + i;
+  int g0 = 0, g1 = 0, j0 = -1;
+  double ldp = 0.0, ldq = 0.0;
+  if (tid < nbus) {
+    g0 = p.gptr[i];
+    g1 = p.gptr[i + 1];
+    ldp = p.load_p[ti];
+    ldq = p.load_q[ti];
+  }
   double fl[2];
-  bus_segsum<2>(src, p.bptr, i0, nbus, smem, fl);
+  bus_segsum<2>(src, p, i0, nbus, smem, fl, [&]() {
+    if (g0 < g1) j0 = p.glist[g0];
+  });
   double part[1] = {0.0};
   if (tid < nbus) {
-    const int i = i0 + tid;
     const double* xP = a.x + 2 * (size_t)p.T * p.N;
     const double* xQ = xP + (size_t)p.T * p.G;
     double sp_ = 0.0, sq = 0.0;
-    for (int g = p.gptr[i]; g < p.gptr[i + 1]; ++g) {
-      const size_t e = (size_t)t * p.G + p.glist[g];
+    for (int g = g0; g < g1; ++g) {
+      const size_t e = (size_t)t * p.G + (g == g0 ? j0 : p.glist[g]);
       sp_ += xP[e];
       sq += xQ[e];
     }
-    const size_t ti = (size_t)t * p.N + i;
-    const double dp = p.load_p[ti] + fl[0] - sp_;
-    const double dq = p.load_q[ti] + fl[1] - sq;
+    const double dp = ldp + fl[0] - sp_;
+    const double dq = ldq + fl[1] - sq;
     const double kb = p.dt[t] * beta;
     // |.|_eps = sqrt(v^2 + eps^2) and its derivative v / |.|_eps from one
     // reciprocal square root each (0 where both vanish)
@@ -885,8 +900,8 @@ __device__ void bus_balance(const EvalArgs& a, int blk, double* smem) {
     w.lamp[ti] = lp;
     w.lamq[ti] = lq;
     // the same multipliers per generator of the bus (read by k_final)
-    for (int g = p.gptr[i]; g < p.gptr[i + 1]; ++g) {
-      const size_t e = (size_t)t * p.G + p.glist[g];
+    for (int g = g0; g < g1; ++g) {
+      const size_t e = (size_t)t * p.G + (g == g0 ? j0 : p.glist[g]);
       w.lamg[e] = lp;
       w.lamqg[e] = lq;
     }
@@ -1435,21 +1450,27 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t v) {
 // R and Q of the wavefront's 64 branches (lane = branch l of period t) from
 // the map-reduce's per-contingency-block sums.  Few branches hold any, and
 // those that do mostly hold one in every block, so each is summed across the
-// lanes (lane = contingency block, one 16-byte load each), four branches'
-// loads in flight together.
-__device__ __forceinline__ void gather_rq(const EvalArgs& a, int t, int g, double& r, double& q) {
+// lanes (lane = contingency block, one 16-byte load each), eight branches'
+// loads in flight together.  mid() runs while the first branches' loads are
+// in flight.
+// hot: the lane's word of the first 64 contingency blocks (hot_word).
+__device__ __forceinline__ uint64_t hot_word(const EvalArgs& a, int t, int g, int c) {
+  const int ng = a.p.Lp >> 6;
+  return g < ng && c < a.nKb ? a.w.hot[((size_t)t * ng + g) * a.rqs + c] : (uint64_t)0;
+}
+template <class Mid>
+__device__ __forceinline__ void gather_rq(const EvalArgs& a, int t, int g, uint64_t hot, double& r,
+                                          double& q, Mid mid) {
+  constexpr int U = 8;
   const DevProblem& p = a.p;
   const int lane = threadIdx.x & 63;
-  const int ng = p.Lp >> 6;
+  bool first = true;
   for (int c0 = 0; c0 < a.nKb; c0 += 64) {
-    const bool in = c0 + lane < a.nKb;
-    const uint64_t word =
-        in ? a.w.hot[((size_t)t * ng + g) * a.rqs + c0 + lane] : (uint64_t)0;
+    const uint64_t word = c0 == 0 ? hot : hot_word(a, t, g, c0 + lane);
     uint64_t any = wave_or(word);
     const double2* src = reinterpret_cast<const double2*>(a.w.rq) +
                          ((size_t)t * p.Lp + g * 64) * a.rqs + c0 + lane;
-    while (any) {
-      constexpr int U = 4;
+    do {
       int row[U];
       double2 v[U];
 #pragma unroll
@@ -1459,17 +1480,24 @@ __device__ __forceinline__ void gather_rq(const EvalArgs& a, int t, int g, doubl
         v[u] = double2{0.0, 0.0};
         if (row[u] >= 0 && ((word >> row[u]) & 1)) v[u] = src[(size_t)row[u] * a.rqs];
       }
+      if (first) mid();
+      first = false;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < U; u += 2) {
         if (row[u] < 0) break;
-        const double s = pair_sum(v[u].x, v[u].y);
-        const double rs = readlane_f64(s, 0), qs = readlane_f64(s, 32);
+        const double s = quad_sum(v[u].x, v[u].y, v[u + 1].x, v[u + 1].y);
+        const double r0 = readlane_f64(s, 0), r1 = readlane_f64(s, 16);
+        const double q0 = readlane_f64(s, 32), q1 = readlane_f64(s, 48);
         if (lane == row[u]) {
-          r += rs;
-          q += qs;
+          r += r0;
+          q += q0;
+        }
+        if (lane == row[u + 1]) {
+          r += r1;
+          q += q1;
         }
       }
-    }
+    } while (any);
   }
 }
 
@@ -1496,10 +1524,11 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
   }
   double sacc[1] = {0.0};
   if (K > 0) {
-    // per-chunk worst penalties and sums: chunk c0 + u in lane u (vector
-    // loads, issued first), combined by wavefront reductions (the argmax is
-    // a total order, the sum has a fixed order); then the k-block partials
-    // of R and Q.  Without contingencies the partials were never written.
+    // per-chunk worst penalties and sums (chunk c0 + u in lane u), combined by
+    // wavefront reductions (the argmax is a total order, the sum has a fixed
+    // order) and followed by the worst contingency's factor and flow, all
+    // while the k-block partials of R and Q are in flight.  Without
+    // contingencies the partials were never written.
     const int lane = tid & 63;
     double zmax = -DBL_MAX, zsum = 0.0;
     int kstar = INT_MAX;
@@ -1511,29 +1540,40 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
       ci = (int)w.zargp[ob + lane];
       cs = w.zsump[ob + lane];
     }
+    // the outaged branch's own factor is NaN: it never tests overloaded
+    double lo = 0.0, fstar = 0.0, sm_k = 0.0;
+    auto worst = [&]() {
+      for (int c0 = 0; c0 < a.nKc; c0 += 64) {
+        if (c0 > 0) {
+          const int c = c0 + lane;
+          cz = c < a.nKc ? w.zmaxp[ob + c] : -DBL_MAX;
+          ci = c < a.nKc ? (int)w.zargp[ob + c] : INT_MAX;
+          cs = c < a.nKc ? w.zsump[ob + c] : 0.0;
+        }
+        wave_argmax(cz, ci);
+        const double ssum = wave_sum(cs);
+        if (better(cz, ci, zmax, kstar)) { zmax = cz; kstar = ci; }
+        zsum += ssum;
+      }
+      if (!(kstar >= 0 && kstar < K)) kstar = 0;  // NaN penalties: keep every index in range
+      fstar = w.Fk[(size_t)t * Kp + kstar];
+      if (hasl) {
+        lo = lodf_value(p, l, kstar);
+        const int sl = kk >= 0 && a.act_slot ? a.act_slot[kk] : kk;
+        if (sl >= 0) sm_k = w.smean[(size_t)t * Kp + sl];
+      }
+    };
     if constexpr (SPLIT) {
-      const int g = lc * (kBlock / 64) + (tid >> 6);
-      if (g < (Lp >> 6)) gather_rq(a, t, __builtin_amdgcn_readfirstlane(g), r, q);
+      const int g = __builtin_amdgcn_readfirstlane(lc * (kBlock / 64) + (tid >> 6));
+      gather_rq(a, t, g, hot_word(a, t, g, lane), r, q, worst);
     } else {
+      worst();
       const size_t st = (size_t)T * Lp;
       if (hasl) {
         r = strided_sum<16>(w.rpart + o, a.nKb, st);
         q = strided_sum<16>(w.qpart + o, a.nKb, st);
       }
     }
-    for (int c0 = 0; c0 < a.nKc; c0 += 64) {
-      if (c0 > 0) {
-        const int c = c0 + lane;
-        cz = c < a.nKc ? w.zmaxp[ob + c] : -DBL_MAX;
-        ci = c < a.nKc ? (int)w.zargp[ob + c] : INT_MAX;
-        cs = c < a.nKc ? w.zsump[ob + c] : 0.0;
-      }
-      wave_argmax(cz, ci);
-      const double ssum = wave_sum(cs);
-      if (better(cz, ci, zmax, kstar)) { zmax = cz; kstar = ci; }
-      zsum += ssum;
-    }
-    if (!(kstar >= 0 && kstar < K)) kstar = 0;  // NaN penalties: keep every index in range
     // weight of every scored contingency: 1/K for the mean (plus 1 for the
     // period's worst), or 1 for the plain sum
     const double invK = 1.0 / (double)K;
@@ -1541,9 +1581,7 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
     if (hasl) {
       r *= wk;
       q *= wk;
-      // the outaged branch's own factor is NaN: it never tests overloaded
-      const double lo = lodf_value(p, l, kstar);
-      const double P = fma(lo, w.Fk[(size_t)t * Kp + kstar], Fl);
+      const double P = fma(lo, fstar, Fl);
       const double s2 = fma(P, P, q2l);
       if (!p.ctg_sum && s2 > sm2) {
         double dP, dq;
@@ -1552,10 +1590,7 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
         q += dq;
         sacc[0] = lo * dP;
       }
-      if (kk >= 0) {
-        const int sl = a.act_slot ? a.act_slot[kk] : kk;
-        if (sl >= 0) r += w.smean[(size_t)t * Kp + sl];
-      }
+      r += sm_k;
     }
     if (lc == 0 && tid == 0) {
       w.tpart[a.toff.cmax + t] = p.ctg_sum ? 0.0 : zmax;
@@ -1595,10 +1630,7 @@ __device__ __forceinline__ void ctg_asm_body(const EvalArgs& a, int b, int nbloc
     a.w.snext[threadIdx.x] = a.w.sched[s1 * kSchedStride + threadIdx.x];
   }
   if (b < nper) {
-    StepParams sp{};
-    sp.eps = a.w.params[PB_EPS];
-    sp.beta = a.w.params[PB_BETA];
-    sp.rho_s = a.w.params[PB_RHO];
+    const StepParams sp{a.w.params[PB_EPS], a.w.params[PB_BETA], a.w.params[PB_RHO]};
     period_block(a, sp, b / nsl, b % nsl, smem);
   } else if (b < nper + nasm) {
     // XCD-grouped: the blocks of consecutive periods store the transposed
@@ -1740,18 +1772,20 @@ __device__ __forceinline__ void adam_entry(double* x, double* m, double* v, size
   adam_store(x, m, v, e, adam_load(x, m, v, e), g, lr, lo, hi, c);
 }
 
+// Blocks [0, nb_bus): voltages and angles of one period's buses; then nb_gen
+// blocks for each generator variable p, q, r, u (one variable a thread: four
+// chains of Adam's divisions and roots in one thread took longer than every other
+// block); then the sum of the terms.
 __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* smem) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
   const int tid = threadIdx.x;
   const int T = p.T, N = p.N, G = p.G;
   AdamCtx ac;
-  double alpha[QG_NCLASS];
   if (a.fuse_adam) {
     ac.b1 = a.mode.adam_b1; ac.b2 = a.mode.adam_b2; ac.eps = a.mode.adam_eps;
     ac.eps_num = a.mode.eps_in_num;
     ac.bc1 = w.params[PB_BC1]; ac.bc2 = w.params[PB_BC2];
-    for (int c = 0; c < QG_NCLASS; ++c) alpha[c] = w.params[PB_ALPHA + c];
   }
   double* xm = const_cast<double*>(a.x);
   if (bx < a.nb_bus) {
@@ -1768,11 +1802,12 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
     const AdamVar st = upd ? adam_load(xm, a.m, a.v, et) : AdamVar{0.0, 0.0, 0.0};
     const double vlo = upd ? p.vmin[i] : 0.0, vhi = upd ? p.vmax[i] : 0.0;
     double gsum[2];
-    bus_segsum<2>(src, p.bptr, i0, nbus, smem, gsum);
+    bus_segsum<2>(src, p, i0, nbus, smem, gsum, []() {});
     if (tid < nbus) {
       if (a.fuse_adam) {
-        adam_store(xm, a.m, a.v, ev, sv, gsum[0], alpha[QG_C_V], vlo, vhi, ac);
-        adam_store(xm, a.m, a.v, et, st, gsum[1], alpha[QG_C_TH], -DBL_MAX, DBL_MAX, ac);
+        adam_store(xm, a.m, a.v, ev, sv, gsum[0], w.params[PB_ALPHA + QG_C_V], vlo, vhi, ac);
+        adam_store(xm, a.m, a.v, et, st, gsum[1], w.params[PB_ALPHA + QG_C_TH], -DBL_MAX, DBL_MAX,
+                   ac);
       } else if (a.grad) {
         a.grad[ev] = gsum[0];
         a.grad[et] = gsum[1];
@@ -1781,78 +1816,68 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
     return;
   }
   const int gb = bx - a.nb_bus;
-  if (gb < a.nb_gen) {
-    // dL/dp: device partials, balance multiplier, and the DC part: the MFMA
-    // split partials plus the worst contingency's rank-1 term
-    // S*_t (ISF[br(k*)][bus(j)] - rowsum/N).
-    const int idx = gb * kBlock + tid;
+  if (gb < 4 * a.nb_gen) {
+    const int cls = gb / a.nb_gen;  // p, q, r, u
+    const int idx = (gb - cls * a.nb_gen) * kBlock + tid;
     if (idx >= T * G) return;
     const int t = idx / G, j = idx - t * G;
     const size_t TG = (size_t)T * G;
-    const size_t base = 2 * (size_t)T * N;
-    const size_t e = (size_t)t * G + j;
-    // every single load first (the Adam state of the four variables too),
-    // then the partial sums
-    AdamVar s4[4];
-    if (a.fuse_adam)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s4[q] = adam_load(xm, a.m, a.v, base + q * TG + e);
-    const double gd0 = w.gdev[e], gd1 = w.gdev[TG + e], gd2 = w.gdev[2 * TG + e];
-    const double gd3 = w.gdev[3 * TG + e];
-    const double lg = w.lamg[e], lqg = w.lamqg[e], drs = w.drs[t];
-    const double isk = w.isfk[(size_t)t * p.G16 + j];
-    const double pmax = p.pmax[j], qmin = p.qmin[j], qmax = p.qmax[j], rmax = p.rmax[j];
-    const double smax = strided_sum<16>(w.smaxp + (size_t)t * a.nLc, a.nLc, 1);
-    double dc = smax * isk;
-    dc += strided_sum<16>(w.gpdc + (size_t)t * p.G16 + j, a.nsplit, (size_t)T * p.G16);
-    const double gp = gd0 - lg + dc;
-    const double gq = gd1 - lqg;
-    const double gr = gd2 - drs;
-    const double gu = gd3;
-    if (a.fuse_adam) {
-      adam_store(xm, a.m, a.v, base + e, s4[0], gp, alpha[QG_C_P], 0.0, pmax, ac);
-      adam_store(xm, a.m, a.v, base + TG + e, s4[1], gq, alpha[QG_C_Q], qmin, qmax, ac);
-      adam_store(xm, a.m, a.v, base + 2 * TG + e, s4[2], gr, alpha[QG_C_R], 0.0, rmax, ac);
-      adam_store(xm, a.m, a.v, base + 3 * TG + e, s4[3], gu, alpha[QG_C_U], 0.0, 1.0, ac);
-    } else if (a.grad) {
-      a.grad[base + e] = gp;
-      a.grad[base + TG + e] = gq;
-      a.grad[base + 2 * TG + e] = gr;
-      a.grad[base + 3 * TG + e] = gu;
+    const size_t e = 2 * (size_t)T * N + cls * TG + idx;
+    // every single load first (the Adam state too), then the partial sums
+    AdamVar sv{0.0, 0.0, 0.0};
+    if (a.fuse_adam) sv = adam_load(xm, a.m, a.v, e);
+    double g = w.gdev[cls * TG + idx], lo = 0.0, hi = 1.0;
+    if (cls == 0) {
+      // dL/dp: device partials, balance multiplier, and the DC part: the MFMA
+      // split partials plus the worst contingency's rank-1 term
+      // S*_t (ISF[br(k*)][bus(j)] - rowsum/N).
+      const double lg = w.lamg[idx], isk = w.isfk[(size_t)t * p.G16 + j];
+      hi = p.pmax[j];
+      const double smax = strided_sum<16>(w.smaxp + (size_t)t * a.nLc, a.nLc, 1);
+      double dc = smax * isk;
+      dc += strided_sum<16>(w.gpdc + (size_t)t * p.G16 + j, a.nsplit, (size_t)T * p.G16);
+      g = g - lg + dc;
+    } else if (cls == 1) {
+      lo = p.qmin[j];
+      hi = p.qmax[j];
+      g -= w.lamqg[idx];
+    } else if (cls == 2) {
+      hi = p.rmax[j];
+      g -= w.drs[t];
     }
+    if (a.fuse_adam)
+      adam_store(xm, a.m, a.v, e, sv, g, w.params[PB_ALPHA + QG_C_P + cls], lo, hi, ac);
+    else if (a.grad)
+      a.grad[e] = g;
     return;
   }
-  // terms: deterministic sums of the partials (one pass, so that all of a
-  // thread's loads are in flight together)
+  // terms: deterministic sums of the partials, two of the eight a wavefront
+  // with all of a lane's loads in flight together
+  if (a.mode.schedule && tid == kBlock - 1) w.step[0] = w.step[0] + 1;
   const TermOffsets& to = a.toff;
-  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  const int lane = tid & 63, wv = tid >> 6;
   const int ndev = T * ((G + kBlock - 1) / kBlock);  // device-term slices
-  const int nq = max(max(a.nb_br, ndev), a.nb_bus);
-  for (int q = tid; q < nq; q += kBlock) {
-    const bool ib = q < a.nb_br, it = q < T, iu = q < a.nb_bus, id = q < ndev;
-    const double br = ib ? w.tpart[to.br + q] : 0.0, an = ib ? w.tpart[to.ang + q] : 0.0;
-    const double dv = id ? w.tpart[to.dev + q] : 0.0, pn = id ? w.tpart[to.pen + q] : 0.0;
-    const double rs = it ? w.tpart[to.rsv + q] : 0.0, cx = it ? w.tpart[to.cmax + q] : 0.0;
-    const double cm = it ? w.tpart[to.cmean + q] : 0.0, bl = iu ? w.tpart[to.bal + q] : 0.0;
-    v[0] += dv; v[1] += bl; v[2] += br; v[3] += an;
-    v[4] += pn; v[5] += rs; v[6] += cx; v[7] += cm;
-  }
-  block_sum<8>(v, smem);
-  if (tid == 0) {
-    double out[QG_NTERMS];
-    for (int q = 0; q < 8; ++q) out[q] = v[q];
-    out[QG_T_LOADVAL] = p.vload;
-    out[QG_T_TOTAL] = v[0] + v[1] + v[2] + v[3] + v[4] + v[5] + v[6] + v[7] - p.vload;
-    for (int q = 0; q < QG_NTERMS; ++q) {
-      w.terms[q] = out[q];
-      if (a.terms_out) a.terms_out[q] = out[q];
-    }
-    if (a.mode.schedule) w.step[0] = w.step[0] + 1;
+  const int qa = wv == 0 ? QG_T_BR : wv == 1 ? QG_T_DEV : wv == 2 ? QG_T_BAL : QG_T_CTG_MAX;
+  const int qb = wv == 0 ? QG_T_ANG : wv == 1 ? QG_T_PEN : wv == 2 ? QG_T_RSV : QG_T_CTG_MEAN;
+  const int oa = wv == 0 ? to.br : wv == 1 ? to.dev : wv == 2 ? to.bal : to.cmax;
+  const int ob = wv == 0 ? to.ang : wv == 1 ? to.pen : wv == 2 ? to.rsv : to.cmean;
+  const int na = wv == 0 ? a.nb_br : wv == 1 ? ndev : wv == 2 ? a.nb_bus : T;
+  const int nb = wv == 0 ? a.nb_br : wv == 1 ? ndev : T;
+  const double sum = pair_sum(strided_sum<8>(w.tpart + oa + lane, (na - lane + 63) >> 6, 64),
+                              strided_sum<8>(w.tpart + ob + lane, (nb - lane + 63) >> 6, 64));
+  if ((lane & 31) == 0) smem[lane == 0 ? qa : qb] = sum;
+  __syncthreads();
+  if (tid < QG_NTERMS) {
+    double tot = smem[0];
+    for (int q = 1; q < QG_T_LOADVAL; ++q) tot += smem[q];
+    const double o = tid < QG_T_LOADVAL ? smem[tid] : tid == QG_T_LOADVAL ? p.vload : tot - p.vload;
+    w.terms[tid] = o;
+    if (a.terms_out) a.terms_out[tid] = o;
   }
 }
 
 __global__ __launch_bounds__(kBlock) void k_final(EvalArgs a) {
-  __shared__ double smem[2 * kSegChunk + 8 * kBlock];
+  __shared__ double smem[2 * kSegChunk];
   final_body(a, blockIdx.x, smem);
 }
 
@@ -2022,7 +2047,8 @@ static void launch_stage(const Problem* pr, const EvalArgs& a, int stage, hipStr
                          s, a);
       break;
     default:
-      hipLaunchKernelGGL(k_final, dim3(pr->nb_bus + pr->nb_gen + 1), dim3(kBlock), 0, s, a);
+      hipLaunchKernelGGL(k_final, dim3(pr->nb_bus + 4 * pr->nb_gen + 1), dim3(kBlock), 0, s,
+                         a);
       break;
   }
 }
@@ -2095,7 +2121,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_b(const EvalArgs* __restrict
 
 __global__ __launch_bounds__(kBlock) void k_final_b(const EvalArgs* __restrict__ args,
                                                     const uint32_t* __restrict__ tab) {
-  __shared__ double smem[2 * kSegChunk + 8 * kBlock];
+  __shared__ double smem[2 * kSegChunk];
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
   final_body(args[s], b, smem);
@@ -2108,7 +2134,7 @@ static void stage_blocks(const Problem* pr, const EvalArgs& a, int out[kStages])
   out[2] = 0;  // the map-reduce finishes z itself
   out[3] = asm_blocks(pr);
   out[4] = pr->G16 / 16 * pr->nsplit + pr->nb_br + (pr->T * pr->G16 + kBlock - 1) / kBlock;
-  out[5] = pr->nb_bus + pr->nb_gen + 1;
+  out[5] = pr->nb_bus + 4 * pr->nb_gen + 1;
 }
 
 static size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
