@@ -193,7 +193,9 @@ typedef struct {
   /* mean duration per launch when profile = 1, in stream order: k_forward,
    * k_ctg_main, k_ctg_zred, k_ctg_asm, k_adjoint, k_final (slots 6, 7 unused);
    * under a period-split tile k_ctg_rows runs in k_ctg_main's place and does
-   * k_ctg_zred's work, whose slot then shows only the events' distance */
+   * k_ctg_zred's work, whose slot then shows only the events' distance; grids
+   * of up to 768 branches run k_update, shown in k_final's slot, for k_adjoint
+   * and k_final */
   double kernel_ms[QG_NKERNELS];
   int64_t kernel_calls[QG_NKERNELS];
   /* device time of the steps, from HIP events on the solve's stream around
@@ -427,9 +429,10 @@ qg_status qg_debug_fetch(const qg_problem* prob, const void* d_workspace, const 
  * one kernel of the step, stage 0..5 in stream order (k_forward, k_ctg_main,
  * k_ctg_zred, k_ctg_asm, k_adjoint, k_final), launched reps times back to back
  * on the stream after one full evaluation at x (homotopy h) has produced its
- * inputs; each of these launches recomputes the same outputs.  Synchronises
- * the stream.  Errors: ARG (stage, reps outside [1, 100000], pointers),
- * DEVICE.
+ * inputs; each of these launches recomputes the same outputs.  A stage whose
+ * work another kernel does (see qg_report.kernel_ms) launches nothing.
+ * Synchronises the stream.  Errors: ARG (stage, reps outside [1, 100000],
+ * pointers), DEVICE.
  */
 qg_status qg_time_stage(qg_problem* prob, const double* d_x, const qg_homotopy* h, int32_t stage,
                         int32_t reps, void* d_workspace, void* stream, double* mean_us);

@@ -19,6 +19,8 @@ constexpr int kCtgMaxTc = 8;            // periods per block of the contingency 
 constexpr int kCtgSlices = 16;          // most branch slices (wavefronts) of a k_ctg_rows block
 constexpr int kCtgLdsBytes = 64 * 1024; // LDS budget of one contingency block
 constexpr int kAdjStepsPerBlock = 32;   // MFMA k-steps per block of the adjoint product
+constexpr int kUpdateBlock = 1024;      // threads per block of k_update
+constexpr int kUpdateMaxL = 768;        // most branches of a grid that takes it
 constexpr int kSchedCap = 2048;         // solve steps per uploaded schedule table
 constexpr int kSchedStride = 16;        // doubles per step in the schedule table
 constexpr int kStepGraphs = 6;          // cached step graphs of 1, 2, 4, ..., 32 steps

@@ -19,6 +19,7 @@
 //   k_final         per-(t, bus) segmented sums of endpoint adjoints and per-(t, generator)
 //                     gradient assembly, then either the gradient or the fused Adam
 //                     update with clip (Alg. 3), and the deterministic sum of the terms.
+//   k_update        k_adjoint and k_final in one launch, in a small grid's own step
 //
 // Every reduction has a fixed order (no floating-point atomics), so a step is
 // bitwise reproducible run to run.
@@ -34,6 +35,11 @@
 #include <vector>
 
 #include "qg_internal.h"
+
+// Products and sums contract to FMAs inside an expression only: across statements
+// the choice would depend on where a function is inlined, and the kernels of a
+// problem's own step and of a batch, which share functions, would round differently.
+#pragma clang fp contract(on)
 
 namespace qg {
 
@@ -1651,16 +1657,15 @@ __global__ __launch_bounds__(kBlock) void k_ctg_asm(EvalArgs a) {
 // ---------------------------------------------------------------------------
 // K6: adjoint DC product + branch reverse
 
-__device__ void branch_reverse(const EvalArgs& a, int blk) {
+// Adjoints of branch l's two ends in period t, at their bus-sorted slots.
+__device__ __forceinline__ void branch_reverse(const EvalArgs& a, int t, int l, double* gv,
+                                               double* gt) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
   const int T = p.T, L = p.L, N = p.N;
-  const int idx = blk * kBlock + threadIdx.x;
-  if (idx >= T * L) return;
-  const int t = idx / L, l = idx - t * L;
   const size_t TL = (size_t)T * L, e = (size_t)t * L + l;
   const double cs = w.bco[0 * TL + e], sn = w.bco[1 * TL + e];
-  const int f = p.br_from[l], o = p.br_to[l];
+  const int f = p.br_from[l], o = p.br_to[l], sf = p.slot_fr[l], so = p.slot_to[l];
   const double vf = a.x[(size_t)t * N + f], vt = a.x[(size_t)t * N + o];
   const double Qc = w.qtot[(size_t)t * p.Lp + l];
   const double lpf = w.lamp[(size_t)t * N + f] + w.bco[2 * TL + e];
@@ -1680,11 +1685,27 @@ __device__ void branch_reverse(const EvalArgs& a, int blk) {
   const double gd = w.bco[6 * TL + e] + lpf * vv * (g * sn - b * cs) +
                     lqf * vv * (-b * sn - g * cs) + lpt * vv * (g * sn + b * cs) +
                     lqt * vv * (-b * sn + g * cs);
+  gv[sf] = gvf;
+  gt[sf] = gd;
+  gv[so] = gvt;
+  gt[so] = -gd;
+}
+
+__device__ void reverse_block(const EvalArgs& a, int blk) {
+  const DevProblem& p = a.p;
+  const int idx = blk * kBlock + threadIdx.x;
+  if (idx >= p.T * p.L) return;
+  const int t = idx / p.L;
   const size_t ep = (size_t)t * p.twoL;
-  w.epGV[ep + p.slot_fr[l]] = gvf;
-  w.epGT[ep + p.slot_fr[l]] = gd;
-  w.epGV[ep + p.slot_to[l]] = gvt;
-  w.epGT[ep + p.slot_to[l]] = -gd;
+  branch_reverse(a, t, idx - t * p.L, a.w.epGV + ep, a.w.epGT + ep);
+}
+
+// Branches [k0, k1) of slice sp of the adjoint product's reduction.
+__device__ __forceinline__ void adjoint_slice(const EvalArgs& a, int sp, int& k0, int& k1) {
+  const int steps = a.p.Lp / 4;
+  const int per = (steps + a.nsplit - 1) / a.nsplit;
+  k0 = min(steps, sp * per) * 4;
+  k1 = min(steps, (sp + 1) * per) * 4;
 }
 
 // Blocks [0, nslab * nsplit): the DC part of dL/dp, one 16-generator slab and
@@ -1699,9 +1720,8 @@ __device__ __forceinline__ void adjoint_body(const EvalArgs& a, int bx, double* 
     const int g = xcd_group(bx, nslab * a.nsplit);
     const int slab = g % nslab, sp = g / nslab;
     const int n0 = slab * 16;
-    const int steps = p.Lp / 4;
-    const int per = (steps + a.nsplit - 1) / a.nsplit;
-    const int k0 = min(steps, sp * per) * 4, k1 = min(steps, (sp + 1) * per) * 4;
+    int k0, k1;
+    adjoint_slice(a, sp, k0, k1);
     const int T = p.T, Tp = p.Tp, G16 = p.G16;
     double* out = a.w.gpdc + (size_t)sp * T * G16;
     const double* gfT = a.w.gfT;
@@ -1717,7 +1737,7 @@ __device__ __forceinline__ void adjoint_body(const EvalArgs& a, int bx, double* 
   }
   const int b = bx - nslab * a.nsplit;
   if (b < a.nb_br) {
-    branch_reverse(a, xcd_group(b, a.nb_br));
+    reverse_block(a, xcd_group(b, a.nb_br));
     return;
   }
   // the worst outage's ISF row of each period (generator columns), for the
@@ -1772,6 +1792,67 @@ __device__ __forceinline__ void adam_entry(double* x, double* m, double* v, size
   adam_store(x, m, v, e, adam_load(x, m, v, e), g, lr, lo, hi, c);
 }
 
+// Entry idx of q, r or u (cls 1, 2, 3).
+__device__ __forceinline__ void final_qru(const EvalArgs& a, const AdamCtx& ac, int cls, int idx) {
+  const DevProblem& p = a.p;
+  const DevWork& w = a.w;
+  const int t = idx / p.G, j = idx - t * p.G;
+  const size_t TG = (size_t)p.T * p.G;
+  const size_t e = 2 * (size_t)p.T * p.N + cls * TG + idx;
+  double* xm = const_cast<double*>(a.x);
+  AdamVar sv{0.0, 0.0, 0.0};
+  if (a.fuse_adam) sv = adam_load(xm, a.m, a.v, e);
+  double g = w.gdev[cls * TG + idx], lo = 0.0, hi = 1.0;
+  if (cls == 1) {
+    lo = p.qmin[j];
+    hi = p.qmax[j];
+    g -= w.lamqg[idx];
+  } else if (cls == 2) {
+    hi = p.rmax[j];
+    g -= w.drs[t];
+  }
+  if (a.fuse_adam)
+    adam_store(xm, a.m, a.v, e, sv, g, w.params[PB_ALPHA + QG_C_P + cls], lo, hi, ac);
+  else if (a.grad)
+    a.grad[e] = g;
+}
+
+// The deterministic sums of the terms' partials, two of the eight a wavefront
+// with all of a lane's loads in flight together (four wavefronts; others only
+// pass the barrier), and the step counter.
+__device__ __forceinline__ void final_terms(const EvalArgs& a, double* smem) {
+  const DevProblem& p = a.p;
+  const DevWork& w = a.w;
+  const int tid = threadIdx.x, T = p.T, G = p.G;
+  if (a.mode.schedule && tid == 255) w.step[0] = w.step[0] + 1;
+  const TermOffsets& to = a.toff;
+  const int lane = tid & 63, wv = min(tid >> 6, 3);
+  const int ndev = T * ((G + kBlock - 1) / kBlock);  // device-term slices
+  const int qa = wv == 0 ? QG_T_BR : wv == 1 ? QG_T_DEV : wv == 2 ? QG_T_BAL : QG_T_CTG_MAX;
+  const int qb = wv == 0 ? QG_T_ANG : wv == 1 ? QG_T_PEN : wv == 2 ? QG_T_RSV : QG_T_CTG_MEAN;
+  const int oa = wv == 0 ? to.br : wv == 1 ? to.dev : wv == 2 ? to.bal : to.cmax;
+  const int ob = wv == 0 ? to.ang : wv == 1 ? to.pen : wv == 2 ? to.rsv : to.cmean;
+  const int na = wv == 0 ? a.nb_br : wv == 1 ? ndev : wv == 2 ? a.nb_bus : T;
+  const int nb = wv == 0 ? a.nb_br : wv == 1 ? ndev : T;
+  const double sum = pair_sum(strided_sum<8>(w.tpart + oa + lane, (na - lane + 63) >> 6, 64),
+                              strided_sum<8>(w.tpart + ob + lane, (nb - lane + 63) >> 6, 64));
+  if (tid < 256 && (lane & 31) == 0) smem[lane == 0 ? qa : qb] = sum;
+  __syncthreads();
+  if (tid < QG_NTERMS) {
+    double tot = smem[0];
+    for (int q = 1; q < QG_T_LOADVAL; ++q) tot += smem[q];
+    const double o = tid < QG_T_LOADVAL ? smem[tid] : tid == QG_T_LOADVAL ? p.vload : tot - p.vload;
+    w.terms[tid] = o;
+    if (a.terms_out) a.terms_out[tid] = o;
+  }
+}
+
+__device__ __forceinline__ AdamCtx adam_ctx(const EvalArgs& a) {
+  if (!a.fuse_adam) return AdamCtx{};
+  return AdamCtx{a.mode.adam_b1,      a.mode.adam_b2,      a.mode.adam_eps,
+                 a.w.params[PB_BC1], a.w.params[PB_BC2], a.mode.eps_in_num};
+}
+
 // Blocks [0, nb_bus): voltages and angles of one period's buses; then nb_gen
 // blocks for each generator variable p, q, r, u (one variable a thread: four
 // chains of Adam's divisions and roots in one thread took longer than every other
@@ -1781,12 +1862,7 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
   const DevWork& w = a.w;
   const int tid = threadIdx.x;
   const int T = p.T, N = p.N, G = p.G;
-  AdamCtx ac;
-  if (a.fuse_adam) {
-    ac.b1 = a.mode.adam_b1; ac.b2 = a.mode.adam_b2; ac.eps = a.mode.adam_eps;
-    ac.eps_num = a.mode.eps_in_num;
-    ac.bc1 = w.params[PB_BC1]; ac.bc2 = w.params[PB_BC2];
-  }
+  const AdamCtx ac = adam_ctx(a);
   double* xm = const_cast<double*>(a.x);
   if (bx < a.nb_bus) {
     const int t = bx / a.bus_chunks;
@@ -1820,65 +1896,188 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
     const int cls = gb / a.nb_gen;  // p, q, r, u
     const int idx = (gb - cls * a.nb_gen) * kBlock + tid;
     if (idx >= T * G) return;
+    if (cls > 0) {
+      final_qru(a, ac, cls, idx);
+      return;
+    }
+    // dL/dp: device partials, balance multiplier, and the DC part: the MFMA
+    // split partials plus the worst contingency's rank-1 term
+    // S*_t (ISF[br(k*)][bus(j)] - rowsum/N).  Every single load first (the Adam
+    // state too), then the partial sums.
     const int t = idx / G, j = idx - t * G;
-    const size_t TG = (size_t)T * G;
-    const size_t e = 2 * (size_t)T * N + cls * TG + idx;
-    // every single load first (the Adam state too), then the partial sums
+    const size_t e = 2 * (size_t)T * N + idx;
     AdamVar sv{0.0, 0.0, 0.0};
     if (a.fuse_adam) sv = adam_load(xm, a.m, a.v, e);
-    double g = w.gdev[cls * TG + idx], lo = 0.0, hi = 1.0;
-    if (cls == 0) {
-      // dL/dp: device partials, balance multiplier, and the DC part: the MFMA
-      // split partials plus the worst contingency's rank-1 term
-      // S*_t (ISF[br(k*)][bus(j)] - rowsum/N).
-      const double lg = w.lamg[idx], isk = w.isfk[(size_t)t * p.G16 + j];
-      hi = p.pmax[j];
-      const double smax = strided_sum<16>(w.smaxp + (size_t)t * a.nLc, a.nLc, 1);
-      double dc = smax * isk;
-      dc += strided_sum<16>(w.gpdc + (size_t)t * p.G16 + j, a.nsplit, (size_t)T * p.G16);
-      g = g - lg + dc;
-    } else if (cls == 1) {
-      lo = p.qmin[j];
-      hi = p.qmax[j];
-      g -= w.lamqg[idx];
-    } else if (cls == 2) {
-      hi = p.rmax[j];
-      g -= w.drs[t];
-    }
+    const double gd = w.gdev[idx], lg = w.lamg[idx], isk = w.isfk[(size_t)t * p.G16 + j];
+    const double hi = p.pmax[j];
+    const double smax = strided_sum<16>(w.smaxp + (size_t)t * a.nLc, a.nLc, 1);
+    const double dc = strided_sum<16>(w.gpdc + (size_t)t * p.G16 + j, a.nsplit, (size_t)T * p.G16);
+    const double g = gd - lg + fma(smax, isk, dc);
     if (a.fuse_adam)
-      adam_store(xm, a.m, a.v, e, sv, g, w.params[PB_ALPHA + QG_C_P + cls], lo, hi, ac);
+      adam_store(xm, a.m, a.v, e, sv, g, w.params[PB_ALPHA + QG_C_P], 0.0, hi, ac);
     else if (a.grad)
       a.grad[e] = g;
     return;
   }
-  // terms: deterministic sums of the partials, two of the eight a wavefront
-  // with all of a lane's loads in flight together
-  if (a.mode.schedule && tid == kBlock - 1) w.step[0] = w.step[0] + 1;
-  const TermOffsets& to = a.toff;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int ndev = T * ((G + kBlock - 1) / kBlock);  // device-term slices
-  const int qa = wv == 0 ? QG_T_BR : wv == 1 ? QG_T_DEV : wv == 2 ? QG_T_BAL : QG_T_CTG_MAX;
-  const int qb = wv == 0 ? QG_T_ANG : wv == 1 ? QG_T_PEN : wv == 2 ? QG_T_RSV : QG_T_CTG_MEAN;
-  const int oa = wv == 0 ? to.br : wv == 1 ? to.dev : wv == 2 ? to.bal : to.cmax;
-  const int ob = wv == 0 ? to.ang : wv == 1 ? to.pen : wv == 2 ? to.rsv : to.cmean;
-  const int na = wv == 0 ? a.nb_br : wv == 1 ? ndev : wv == 2 ? a.nb_bus : T;
-  const int nb = wv == 0 ? a.nb_br : wv == 1 ? ndev : T;
-  const double sum = pair_sum(strided_sum<8>(w.tpart + oa + lane, (na - lane + 63) >> 6, 64),
-                              strided_sum<8>(w.tpart + ob + lane, (nb - lane + 63) >> 6, 64));
-  if ((lane & 31) == 0) smem[lane == 0 ? qa : qb] = sum;
-  __syncthreads();
-  if (tid < QG_NTERMS) {
-    double tot = smem[0];
-    for (int q = 1; q < QG_T_LOADVAL; ++q) tot += smem[q];
-    const double o = tid < QG_T_LOADVAL ? smem[tid] : tid == QG_T_LOADVAL ? p.vload : tot - p.vload;
-    w.terms[tid] = o;
-    if (a.terms_out) a.terms_out[tid] = o;
-  }
+  final_terms(a, smem);
 }
 
 __global__ __launch_bounds__(kBlock) void k_final(EvalArgs a) {
   __shared__ double smem[2 * kSegChunk];
   final_body(a, blockIdx.x, smem);
+}
+
+// ---------------------------------------------------------------------------
+// K6 and K7 in one launch, for grids whose step is bound by its launches: a
+// period's branches and buses are one block's, so the end adjoints stay in LDS
+// and the updates follow a barrier instead of a launch, and one block forms every
+// slice of a p slab.  Sums have the order of k_adjoint and k_final: the results are
+// bitwise theirs.
+
+// Period t's voltages and angles: the branches' end adjoints to their slots in
+// LDS, then each bus's segment in ascending slot order.  Only this block reads
+// or writes the period's V and theta in this kernel.
+__device__ __forceinline__ void update_period(const EvalArgs& a, const AdamCtx& ac, int t,
+                                             double* gv, double* gt) {
+  const DevProblem& p = a.p;
+  const int N = p.N, tid = threadIdx.x;
+  double* xm = const_cast<double*>(a.x);
+  // the first buses' Adam state and segments, in flight with the branches
+  const size_t TN = (size_t)p.T * N;
+  AdamVar sv{0.0, 0.0, 0.0}, st{0.0, 0.0, 0.0};
+  double vlo = 0.0, vhi = 0.0;
+  int lo = 0, hi = 0;
+  auto fetch = [&](int i) {
+    if (i < N) {
+      lo = p.bptr[i];
+      hi = p.bptr[i + 1];
+      if (a.fuse_adam) {
+        const size_t ev = (size_t)t * N + i;
+        sv = adam_load(xm, a.m, a.v, ev);
+        st = adam_load(xm, a.m, a.v, TN + ev);
+        vlo = p.vmin[i];
+        vhi = p.vmax[i];
+      }
+    }
+  };
+  fetch(tid);
+  for (int l = tid; l < p.L; l += kUpdateBlock) branch_reverse(a, t, l, gv, gt);
+  __syncthreads();
+  for (int i = tid; i < N; i += kUpdateBlock) {
+    const size_t ev = (size_t)t * N + i, et = TN + ev;
+    double sum_v = 0.0, sum_t = 0.0;
+    for (int s = lo; s < hi; ++s) {
+      sum_v += gv[s];
+      sum_t += gt[s];
+    }
+    if (a.fuse_adam) {
+      adam_store(xm, a.m, a.v, ev, sv, sum_v, a.w.params[PB_ALPHA + QG_C_V], vlo, vhi, ac);
+      adam_store(xm, a.m, a.v, et, st, sum_t, a.w.params[PB_ALPHA + QG_C_TH], -DBL_MAX, DBL_MAX,
+                 ac);
+    } else if (a.grad) {
+      a.grad[ev] = sum_v;
+      a.grad[et] = sum_t;
+    }
+    fetch(i + kUpdateBlock);
+  }
+}
+
+// p of 16 generators in 16 periods: every slice of the adjoint product, a quarter
+// of a slice a wavefront as k_adjoint cuts them, then what k_final does.
+__device__ __forceinline__ void update_slab(const EvalArgs& a, const AdamCtx& ac, int blk,
+                                            double* smem) {
+  const DevProblem& p = a.p;
+  const DevWork& w = a.w;
+  const int tid = threadIdx.x, lane = tid & 63, T = p.T, Tp = p.Tp, G = p.G, G16 = p.G16;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mtiles = Tp / 16;
+  const int n0 = blk / mtiles * 16, r0 = blk % mtiles * 16;
+  double* xm = const_cast<double*>(a.x);
+  // everything else of the thread's output first, in flight with the product
+  const int j = n0 + (tid & 15), t = r0 + (lane >> 4) + 4 * (tid >> 6);
+  const bool out = tid < 256 && t < T && j < G;
+  const size_t idx = (size_t)t * G + j, e = 2 * (size_t)T * p.N + idx;
+  AdamVar sv{0.0, 0.0, 0.0};
+  double gd = 0.0, lg = 0.0, hi = 0.0, smax = 0.0, isk = 0.0;
+  if (out) {
+    if (a.fuse_adam) sv = adam_load(xm, a.m, a.v, e);
+    gd = w.gdev[idx];
+    lg = w.lamg[idx];
+    hi = p.pmax[j];
+    const int bks = p.brk[(int)w.kstar[t]];
+    isk = p.isf_ga[(size_t)bks * G16 + j];
+    smax = strided_sum<4>(w.smaxp + (size_t)t * a.nLc, a.nLc, 1);
+  }
+  const int kr = lane >> 4, cc = lane & 15;
+  const bool row = r0 + cc < T;  // rows past T of gfT are never written: they enter as zeros
+  const double* __restrict__ A = w.gfT + r0 + cc;
+  const double* __restrict__ B = p.isf_ga + n0 + cc;
+  for (int seg = wv; seg < 4 * a.nsplit; seg += kUpdateBlock / 64) {
+    constexpr int NB = 8;
+    int k0, k1;
+    adjoint_slice(a, seg >> 2, k0, k1);
+    const int steps = (k1 - k0) >> 2, q = seg & 3;
+    const int s0 = (steps * q) >> 2, s1 = (steps * (q + 1)) >> 2;
+    v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int st = s0; st < s1; st += NB) {
+      double bb[NB], aa[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const bool in = st + u < s1;
+        const int k = k0 + (st + u) * 4 + kr;
+        bb[u] = in ? B[(size_t)k * G16] : 0.0;
+        aa[u] = in && row ? A[(size_t)k * Tp] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+        if (st + u < s1) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(aa[u], bb[u], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) smem[(seg * 4 + r) * 64 + lane] = acc[r];
+  }
+  __syncthreads();
+  if (!out) return;
+  double dc = 0.0;
+  for (int sp = 0; sp < a.nsplit; ++sp) {
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v += smem[(sp * 4 + q) * 256 + tid];
+    w.gpdc[((size_t)sp * T + t) * G16 + j] = v;
+    dc += v;
+  }
+  const double g = gd - lg + fma(smax, isk, dc);
+  if (a.fuse_adam)
+    adam_store(xm, a.m, a.v, e, sv, g, w.params[PB_ALPHA + QG_C_P], 0.0, hi, ac);
+  else if (a.grad)
+    a.grad[e] = g;
+}
+
+// Blocks [0, T): one period's voltages and angles each; then the p slabs, (G16 /
+// 16) x (Tp / 16); then the blocks of q, r and u; then the terms.  Every block
+// updates entries of x that no other block of the kernel reads.
+__global__ __launch_bounds__(kUpdateBlock) void k_update(EvalArgs a) {
+  extern __shared__ double dyn[];
+  const DevProblem& p = a.p;
+  const AdamCtx ac = adam_ctx(a);
+  int bx = blockIdx.x;
+  if (bx < p.T) {
+    update_period(a, ac, bx, dyn, dyn + p.twoL);
+    return;
+  }
+  bx -= p.T;
+  const int nslab = p.G16 / 16 * (p.Tp / 16);
+  if (bx < nslab) {
+    update_slab(a, ac, bx, dyn);
+    return;
+  }
+  bx -= nslab;
+  const int TG = p.T * p.G, nb = (TG + kUpdateBlock - 1) / kUpdateBlock;
+  if (bx < 3 * nb) {
+    const int cls = 1 + bx / nb, idx = (bx - (cls - 1) * nb) * kUpdateBlock + threadIdx.x;
+    if (idx < TG) final_qru(a, ac, cls, idx);
+    return;
+  }
+  final_terms(a, dyn);
 }
 
 // ---------------------------------------------------------------------------
@@ -2009,6 +2208,15 @@ static int asm_blocks(const Problem* pr) {
   return pr->T * ((pr->G + kBlock - 1) / kBlock) + pr->nLc * pr->T + pr->nb_bus;
 }
 
+// Whether the reverse pass and the update of a problem's own step are one
+// kernel.  A launch and the loads it waits for cost 2 to 3 us, but a period's branches
+// then come through one CU, at about 48 GB/s from the other XCDs' stores.  A step
+// in one kernel and in two takes 16.5 and 18.5 us with 20 branches and 4 periods,
+// 21.2 and 24.3 with 183 and 48, 24.2 and 26.4 with 420 and 24, 25.0 and 25.2 with 700
+// and 12, 26.6 and 26.2 with 864 and 18, 43.6 and 39.1 with 1680 and 24.  A batch fills the
+// chip with its problems and stays with two.
+static bool one_update(const Problem* pr) { return pr->L <= kUpdateMaxL; }
+
 // One kernel of the step, in stream order 0..kStages-1.
 static void launch_stage(const Problem* pr, const EvalArgs& a, int stage, hipStream_t s) {
   switch (stage) {
@@ -2040,6 +2248,7 @@ static void launch_stage(const Problem* pr, const EvalArgs& a, int stage, hipStr
                            s, a);
       break;
     case 4:
+      if (one_update(pr)) break;  // k_update does both stages' work
       hipLaunchKernelGGL(k_adjoint,
                          dim3(pr->G16 / 16 * pr->nsplit + pr->nb_br +
                               (pr->T * pr->G16 + kBlock - 1) / kBlock),
@@ -2047,6 +2256,14 @@ static void launch_stage(const Problem* pr, const EvalArgs& a, int stage, hipStr
                          s, a);
       break;
     default:
+      if (one_update(pr)) {
+        // a period's end adjoints, or a slab's partial tiles
+        const size_t lds = sizeof(double) * std::max(4 * (size_t)pr->L, 4 * (size_t)pr->nsplit * 256);
+        const int nb = (pr->T * pr->G + kUpdateBlock - 1) / kUpdateBlock;
+        hipLaunchKernelGGL(k_update, dim3(pr->T + pr->G16 / 16 * (pr->Tp / 16) + 3 * nb + 1),
+                           dim3(kUpdateBlock), lds, s, a);
+        break;
+      }
       hipLaunchKernelGGL(k_final, dim3(pr->nb_bus + 4 * pr->nb_gen + 1), dim3(kBlock), 0, s,
                          a);
       break;

@@ -857,3 +857,30 @@ def test_sum_aggregation(qg, name):
     tr, gr = ob.evaluate(oracle_model(c), x, 1e-2, 0.9, 1.0, agg="sum", active=A)
     assert_terms_close(qg, t, tr)
     assert_grad_close(c, g, gr)
+
+
+# edges of the one-kernel reverse pass and update: tiles of 16 periods and 16
+# generators, and the most branches that take it (768) and one more
+@pytest.mark.parametrize("shape", [(6, 8, 1, 1), (30, 42, 16, 16), (30, 42, 17, 17),
+                                   (548, 768, 33, 5), (548, 769, 33, 5)])
+def test_update_kernel_matches_batched_step(qg, shape):
+    """A solve of a problem alone (for grids of up to 768 branches the reverse pass
+    and the update are one kernel) and the same solve as a batch of one (two
+    kernels) end in the same point and moments, bit for bit; every sum has one
+    order in both."""
+    import torch
+    n_bus, n_branch, n_gen, n_period = shape
+    c = synth.make_case(seed=n_branch, n_bus=n_bus, n_branch=n_branch, n_gen=n_gen,
+                        n_period=n_period, n_ctg=None, tree="prufer", mesh=3.0, name="edge")
+    opts = qg.solve_opts(5, [1e-3] * 6, alphaf=[1e-4] * 6, eps0=1e-1, epsf=1e-3, use_graph=1)
+    p = qg.Problem(c)
+    p.set_tile("s4x4x4")
+    ends = []
+    for solve in (lambda *s: p.solve(*s, opts), lambda x, m, v: qg.solve_batch([p], [x], [m], [v], opts)):
+        x, m, v = p.new_vector(synth.flat_start(c)), p.new_vector(), p.new_vector()
+        solve(x, m, v)
+        torch.cuda.synchronize()
+        ends.append([a.cpu().numpy().copy() for a in (x, m, v)])
+    for a, b in zip(*ends):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+    p.close()
