@@ -430,7 +430,7 @@ qg_status qg_debug_fetch(const qg_problem* prob, const void* d_workspace, const 
  * k_ctg_zred, k_ctg_asm, k_adjoint, k_final), launched reps times back to back
  * on the stream after one full evaluation at x (homotopy h) has produced its
  * inputs; each of these launches recomputes the same outputs.  A stage whose
- * work another kernel does (see qg_report.kernel_ms) launches nothing.
+ * work another kernel does (see kernel_ms of qg_solve_report) launches nothing.
  * Synchronises the stream.  Errors: ARG (stage, reps outside [1, 100000],
  * pointers), DEVICE.
  */

@@ -153,8 +153,8 @@ WorkLayout work_layout(const Problem& p) {
   const size_t cnt[] = {
       kParams * D, 8,                                   // params, step
       (size_t)kSchedCap * kSchedStride * D,             // sched
-      T * twoL * D, T * twoL * D,                       // epP, epQ
-      9 * T * L * D,                                    // bco
+      T * twoL * 2 * D, T * L,                          // ep, bside
+      3 * T * L * 2 * D,                                // bco
       T * p.Lp * D,                                     // q2
       T * p.Lp * D, T * p.Kp * D,                       // F, Fk
       T * N * D, T * N * D,                             // lamp, lamq
@@ -166,7 +166,7 @@ WorkLayout work_layout(const Problem& p) {
       (size_t)p.Lp * p.Tp * D,                          // gfT
       T * p.Lp * D,                                     // qtot
       (size_t)p.nsplit * T * p.G16 * D,                 // gpdc
-      T * twoL * D, T * twoL * D,                       // epGV, epGT
+      T * twoL * 2 * D, 0,                              // epG
       nterm * D,                                        // tpart
       QG_NTERMS * D,                                    // terms
       T * D,                                            // drs
@@ -794,13 +794,17 @@ DevWork carve_workspace(const Problem* p, void* ws) {
   w.params = D(0);
   w.step = reinterpret_cast<int64_t*>(base + wl.off[1]);
   w.sched = D(2);
-  w.epP = D(3); w.epQ = D(4); w.bco = D(5); w.q2 = D(6);
+  w.ep = reinterpret_cast<Pair*>(D(3));
+  w.bside = reinterpret_cast<uint8_t*>(base + wl.off[4]);
+  w.bco = reinterpret_cast<Pair*>(D(5));
+  w.q2 = D(6);
   w.F = D(7); w.Fk = D(8); w.lamp = D(9); w.lamq = D(10); w.gdev = D(11);
   w.zpart = D(12); w.spart = D(13); w.rpart = w.rq = D(14);
   w.qpart = w.rpart + (size_t)p->nKb_max * p->T * p->Lp;
   w.hot = reinterpret_cast<uint64_t*>(base + wl.off[15]);
   w.smean = D(16); w.zval = D(17); w.gfT = D(18); w.qtot = D(19); w.gpdc = D(20);
-  w.epGV = D(21); w.epGT = D(22); w.tpart = D(23); w.terms = D(24);
+  w.epG = reinterpret_cast<Pair*>(D(21));
+  w.tpart = D(23); w.terms = D(24);
   w.drs = D(25); w.zmaxp = D(26); w.zargp = D(27); w.zsump = D(28); w.kstar = D(29);
   w.smaxp = D(30);
   w.lamg = D(31); w.lamqg = D(32); w.isfk = D(33); w.thr = D(34);

@@ -83,14 +83,22 @@ struct DevProblem {
   double c_p, c_q, c_s, c_ang, ang_max, c_rsv, rho, vload;
 };
 
+// Two doubles moved together.
+struct alignas(16) Pair {
+  double x, y;
+};
+
 // Device view of the caller's workspace.
 struct DevWork {
   double* params;      // [kParams] parameters of the step being evaluated
   int64_t* step;       // [1] index of the current step in the schedule table
   double* sched;       // [kSchedCap][kSchedStride] per-step eps, beta, rho_s, alpha[6], bc1, bc2
   double* snext;       // [kSchedStride] the schedule row of the next scheduled evaluation
-  double* epP; double* epQ;      // [T][2L] branch flows at bus-sorted endpoint slots
-  double* bco;         // [9][T][L] per-branch reverse coefficients
+  Pair* ep;            // [T][2L] branch flows (p, q) at bus-sorted endpoint slots
+  // [3][T][L] per-branch reverse coefficients: cosine and sine, thermal derivative
+  // by p and q, angle derivative and 2 q, the latter two pairs of the sides in bside
+  Pair* bco;
+  uint8_t* bside;      // [T][L] kThermalTo, kReactiveTo
   double* q2;          // [T][Lp]  max(q_fr^2, q_to^2)
   double* F;           // [T][Lp]  base-case DC flows
   double* Fk;          // [T][Kp]  flows of the outaged branches
@@ -106,7 +114,7 @@ struct DevWork {
   double* gfT;         // [Lp][Tp] dL/dF, transposed
   double* qtot;        // [T][Lp]  dL/d qmax2
   double* gpdc;        // [nsplit][T][G16] DC part of dL/dp (split-K partials)
-  double* epGV; double* epGT;    // [T][2L] endpoint adjoints
+  Pair* epG;           // [T][2L] endpoint adjoints (V, theta)
   double* tpart;       // term partial sums
   double* terms;       // [QG_NTERMS] last evaluated terms
   double* drs;         // [T]       reserve-shortfall derivative, subtracted from dL/dr
@@ -119,6 +127,10 @@ struct DevWork {
   double* isfk;        // [T][G16]  ISF[br(k*_t)][bus(j)] - rowsum/N of the period's worst outage
   double* thr;         // [T][Lp]  test radius of the outage flows
 };
+
+// Sides of a branch in DevWork::bside: set where the larger apparent power, the
+// larger reactive flow is the to side's.
+constexpr uint8_t kThermalTo = 1, kReactiveTo = 2;
 
 // Offsets of the term partial sums inside DevWork::tpart.
 struct TermOffsets {

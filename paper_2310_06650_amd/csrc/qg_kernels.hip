@@ -407,10 +407,9 @@ constexpr int kSegChunk = 1024;
 
 // A chunk's slots are all in flight at once; ahead() issues loads of the
 // caller's that go out with the first chunk's.
-template <int NV, class Ahead>
-__device__ __forceinline__ void bus_segsum(const double* const (&src)[NV], const DevProblem& p,
-                                           int i0, int nbus, double* lds, double (&acc)[NV],
-                                           Ahead ahead) {
+template <class Ahead>
+__device__ __forceinline__ void bus_segsum(const Pair* src, const DevProblem& p, int i0,
+                                           int nbus, Pair* lds, double (&acc)[2], Ahead ahead) {
   constexpr int U = kSegChunk / kBlock;
   const int tid = threadIdx.x;
   const int* bptr = p.bptr;
@@ -419,26 +418,24 @@ __device__ __forceinline__ void bus_segsum(const double* const (&src)[NV], const
   int a = 0, b = 0;
   if (tid < nbus) { a = bptr[i0 + tid]; b = bptr[i0 + tid + 1]; }
   ahead();
-#pragma unroll
-  for (int q = 0; q < NV; ++q) acc[q] = 0.0;
+  acc[0] = acc[1] = 0.0;
   for (int c0 = s_lo; c0 < s_hi; c0 += kSegChunk) {
     const int c1 = min(c0 + kSegChunk, s_hi);
-    double v[NV][U];
+    double vx[U], vy[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int s = min(c0 + u * kBlock + tid, c1 - 1);
-#pragma unroll
-      for (int q = 0; q < NV; ++q) v[q][u] = src[q][s];
+      const Pair e = src[min(c0 + u * kBlock + tid, c1 - 1)];
+      vx[u] = e.x;
+      vy[u] = e.y;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int q = 0; q < NV; ++q) lds[q * kSegChunk + u * kBlock + tid] = v[q][u];
+    for (int u = 0; u < U; ++u) lds[u * kBlock + tid] = Pair{vx[u], vy[u]};
     __syncthreads();
     const int lo = max(a, c0), hi = min(b, c1);
     for (int s = lo; s < hi; ++s) {
-#pragma unroll
-      for (int q = 0; q < NV; ++q) acc[q] += lds[q * kSegChunk + (s - c0)];
+      const Pair e = lds[s - c0];
+      acc[0] += e.x;
+      acc[1] += e.y;
     }
     __syncthreads();
   }
@@ -571,10 +568,8 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     const double pt = g * vt * vt + vv * (-g * cs + b * sn);
     const double qt = -(b + bh) * vt * vt + vv * (b * cs + g * sn);
     const size_t ep = (size_t)t * p.twoL;
-    w.epP[ep + p.slot_fr[l]] = pf;
-    w.epP[ep + p.slot_to[l]] = pt;
-    w.epQ[ep + p.slot_fr[l]] = qf;
-    w.epQ[ep + p.slot_to[l]] = qt;
+    w.ep[ep + p.slot_fr[l]] = Pair{pf, qf};
+    w.ep[ep + p.slot_to[l]] = Pair{pt, qt};
     // thermal penalty on the larger side (ties: from side), Example 1
     const double sf2 = pf * pf + qf * qf, st2 = pt * pt + qt * qt;
     const bool use_f = sf2 >= st2;
@@ -585,8 +580,6 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     double kth;
     part[0] = kbr * soft_relu_pair(eb, sp.eps, kth);
     kth *= kbr * rs;
-    const double kpf = use_f ? kth * pf : 0.0, kqf = use_f ? kth * qf : 0.0;
-    const double kpt = use_f ? 0.0 : kth * pt, kqt = use_f ? 0.0 : kth * qt;
     // angle-difference penalty
     const double ea = fabs(d) - p.ang_max;
     const double kang = p.dt[t] * p.c_ang * sp.beta;
@@ -607,15 +600,14 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     const double thr = A > 0.0 ? sqrt(A) * (1.0 - 0x1p-50) : -1.0;
     w.thr[(size_t)t * p.Lp + l] = thr;
     const size_t TL = (size_t)T * L, e = (size_t)t * L + l;
-    w.bco[0 * TL + e] = cs;
-    w.bco[1 * TL + e] = sn;
-    w.bco[2 * TL + e] = kpf;
-    w.bco[3 * TL + e] = kqf;
-    w.bco[4 * TL + e] = kpt;
-    w.bco[5 * TL + e] = kqt;
-    w.bco[6 * TL + e] = kd;
-    w.bco[7 * TL + e] = qfr ? 2.0 * qf : 0.0;
-    w.bco[8 * TL + e] = qfr ? 0.0 : 2.0 * qt;
+    // written once and read once: 49 bytes and four stores a branch, the ends'
+    // flows in one scattered 16-byte store each (nine coefficients and four
+    // 8-byte stores took 1.6 us more of 14.7 at 2800 branches and 48 periods, and as
+    // much in the reverse pass)
+    w.bco[e] = Pair{cs, sn};
+    w.bco[TL + e] = Pair{kth * (use_f ? pf : pt), kth * (use_f ? qf : qt)};
+    w.bco[2 * TL + e] = Pair{kd, 2.0 * (qfr ? qf : qt)};
+    w.bside[e] = (uint8_t)((use_f ? 0 : kThermalTo) | (qfr ? 0 : kReactiveTo));
   }
   block_sum<2>(part, lds);
   if (threadIdx.x == 0) {
@@ -860,7 +852,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(EvalArgs a) {
 // Per-(t, bus) power balance (Example 4): segmented sums of the bus's
 // endpoint flows staged through LDS, minus its generators; multipliers and
 // the soft-abs value.
-__device__ void bus_balance(const EvalArgs& a, int blk, double* smem) {
+__device__ void bus_balance(const EvalArgs& a, int blk, Pair* smem) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
   const int tid = threadIdx.x;
@@ -869,7 +861,6 @@ __device__ void bus_balance(const EvalArgs& a, int blk, double* smem) {
   const int i0 = c * kBlock;
   const int nbus = min(kBlock, p.N - i0);
   const double eps = w.params[PB_EPS], beta = w.params[PB_BETA];
-  const double* src[2] = {w.epP + (size_t)t * p.twoL, w.epQ + (size_t)t * p.twoL};
   // the bus's loads and its first generator, in flight with the endpoint flows
   const int i = i0 + tid;
   const size_t ti = (size_t)t * p.N + i;
@@ -882,7 +873,7 @@ __device__ void bus_balance(const EvalArgs& a, int blk, double* smem) {
     ldq = p.load_q[ti];
   }
   double fl[2];
-  bus_segsum<2>(src, p, i0, nbus, smem, fl, [&]() {
+  bus_segsum(w.ep + (size_t)t * p.twoL, p, i0, nbus, smem, fl, [&]() {
     if (g0 < g1) j0 = p.glist[g0];
   });
   double part[1] = {0.0};
@@ -913,7 +904,7 @@ __device__ void bus_balance(const EvalArgs& a, int blk, double* smem) {
     }
     part[0] = kb * (p.c_p * (xp * rp) + p.c_q * (xq * rq));
   }
-  block_sum<1>(part, smem);
+  block_sum<1>(part, reinterpret_cast<double*>(smem));
   if (tid == 0) w.tpart[a.toff.bal + blk] = part[0];
 }
 
@@ -1625,7 +1616,7 @@ __device__ void ctg_assemble(const EvalArgs& a, int t, int lc, double* red) {
 // blocks, which only need the forward flows.
 template <bool SPLIT>
 __device__ __forceinline__ void ctg_asm_body(const EvalArgs& a, int b, int nblocks,
-                                             double* smem) {
+                                             Pair* smem) {
   const int T = a.p.T, nasm = a.nLc * T;
   const int nsl = (a.p.G + kBlock - 1) / kBlock, nper = T * nsl;
   // scheduled steps: the next step's schedule row (the counter is advanced
@@ -1637,12 +1628,12 @@ __device__ __forceinline__ void ctg_asm_body(const EvalArgs& a, int b, int nbloc
   }
   if (b < nper) {
     const StepParams sp{a.w.params[PB_EPS], a.w.params[PB_BETA], a.w.params[PB_RHO]};
-    period_block(a, sp, b / nsl, b % nsl, smem);
+    period_block(a, sp, b / nsl, b % nsl, reinterpret_cast<double*>(smem));
   } else if (b < nper + nasm) {
     // XCD-grouped: the blocks of consecutive periods store the transposed
     // flow adjoints gfT[l][t] of the same branches through one L2
     const int g = xcd_group(b - nper, nasm);
-    ctg_assemble<SPLIT>(a, g / a.nLc, g % a.nLc, smem);
+    ctg_assemble<SPLIT>(a, g / a.nLc, g % a.nLc, reinterpret_cast<double*>(smem));
   } else {
     bus_balance(a, b - nper - nasm, smem);
   }
@@ -1650,28 +1641,33 @@ __device__ __forceinline__ void ctg_asm_body(const EvalArgs& a, int b, int nbloc
 
 template <bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_ctg_asm(EvalArgs a) {
-  __shared__ double smem[2 * kSegChunk + 16];
+  __shared__ Pair smem[kSegChunk];
   ctg_asm_body<SPLIT>(a, blockIdx.x, gridDim.x, smem);
 }
 
 // ---------------------------------------------------------------------------
 // K6: adjoint DC product + branch reverse
 
-// Adjoints of branch l's two ends in period t, at their bus-sorted slots.
-__device__ __forceinline__ void branch_reverse(const EvalArgs& a, int t, int l, double* gv,
-                                               double* gt) {
+// Adjoints (V, theta) of branch l's two ends in period t, at their bus-sorted
+// slots.
+__device__ __forceinline__ void branch_reverse(const EvalArgs& a, int t, int l, Pair* ge) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
   const int T = p.T, L = p.L, N = p.N;
   const size_t TL = (size_t)T * L, e = (size_t)t * L + l;
-  const double cs = w.bco[0 * TL + e], sn = w.bco[1 * TL + e];
+  const Pair trig = w.bco[e], kth = w.bco[TL + e], kq = w.bco[2 * TL + e];
+  const int side = w.bside[e];
+  const double cs = trig.x, sn = trig.y;
   const int f = p.br_from[l], o = p.br_to[l], sf = p.slot_fr[l], so = p.slot_to[l];
   const double vf = a.x[(size_t)t * N + f], vt = a.x[(size_t)t * N + o];
   const double Qc = w.qtot[(size_t)t * p.Lp + l];
-  const double lpf = w.lamp[(size_t)t * N + f] + w.bco[2 * TL + e];
-  const double lqf = w.lamq[(size_t)t * N + f] + w.bco[3 * TL + e] + Qc * w.bco[7 * TL + e];
-  const double lpt = w.lamp[(size_t)t * N + o] + w.bco[4 * TL + e];
-  const double lqt = w.lamq[(size_t)t * N + o] + w.bco[5 * TL + e] + Qc * w.bco[8 * TL + e];
+  const bool th_to = side & kThermalTo, q_to = side & kReactiveTo;
+  const double lpf = w.lamp[(size_t)t * N + f] + (th_to ? 0.0 : kth.x);
+  const double lqf =
+      w.lamq[(size_t)t * N + f] + (th_to ? 0.0 : kth.y) + Qc * (q_to ? 0.0 : kq.y);
+  const double lpt = w.lamp[(size_t)t * N + o] + (th_to ? kth.x : 0.0);
+  const double lqt =
+      w.lamq[(size_t)t * N + o] + (th_to ? kth.y : 0.0) + Qc * (q_to ? kq.y : 0.0);
   const double g = p.br_g[l], b = p.br_b[l], bh = p.br_bh[l];
   const double A = -g * cs - b * sn;   // p_fr cross coefficient
   const double Bq = b * cs - g * sn;   // q_fr
@@ -1682,13 +1678,11 @@ __device__ __forceinline__ void branch_reverse(const EvalArgs& a, int t, int l, 
   const double gvt = lpf * (vf * A) + lqf * (vf * Bq) + lpt * (2.0 * g * vt + vf * Ct) +
                      lqt * (-2.0 * (b + bh) * vt + vf * Dq);
   const double vv = vf * vt;
-  const double gd = w.bco[6 * TL + e] + lpf * vv * (g * sn - b * cs) +
+  const double gd = kq.x + lpf * vv * (g * sn - b * cs) +
                     lqf * vv * (-b * sn - g * cs) + lpt * vv * (g * sn + b * cs) +
                     lqt * vv * (-b * sn + g * cs);
-  gv[sf] = gvf;
-  gt[sf] = gd;
-  gv[so] = gvt;
-  gt[so] = -gd;
+  ge[sf] = Pair{gvf, gd};
+  ge[so] = Pair{gvt, -gd};
 }
 
 __device__ void reverse_block(const EvalArgs& a, int blk) {
@@ -1696,8 +1690,7 @@ __device__ void reverse_block(const EvalArgs& a, int blk) {
   const int idx = blk * kBlock + threadIdx.x;
   if (idx >= p.T * p.L) return;
   const int t = idx / p.L;
-  const size_t ep = (size_t)t * p.twoL;
-  branch_reverse(a, t, idx - t * p.L, a.w.epGV + ep, a.w.epGT + ep);
+  branch_reverse(a, t, idx - t * p.L, a.w.epG + (size_t)t * p.twoL);
 }
 
 // Branches [k0, k1) of slice sp of the adjoint product's reduction.
@@ -1857,7 +1850,7 @@ __device__ __forceinline__ AdamCtx adam_ctx(const EvalArgs& a) {
 // blocks for each generator variable p, q, r, u (one variable a thread: four
 // chains of Adam's divisions and roots in one thread took longer than every other
 // block); then the sum of the terms.
-__device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* smem) {
+__device__ __forceinline__ void final_body(const EvalArgs& a, int bx, Pair* smem) {
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
   const int tid = threadIdx.x;
@@ -1869,7 +1862,6 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
     const int c = bx - t * a.bus_chunks;
     const int i0 = c * kBlock;
     const int nbus = min(kBlock, N - i0);
-    const double* src[2] = {w.epGV + (size_t)t * p.twoL, w.epGT + (size_t)t * p.twoL};
     // the bus's Adam state, loaded while the endpoint sums are formed
     const int i = i0 + tid;
     const size_t ev = (size_t)t * N + i, et = (size_t)T * N + ev;
@@ -1878,7 +1870,7 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
     const AdamVar st = upd ? adam_load(xm, a.m, a.v, et) : AdamVar{0.0, 0.0, 0.0};
     const double vlo = upd ? p.vmin[i] : 0.0, vhi = upd ? p.vmax[i] : 0.0;
     double gsum[2];
-    bus_segsum<2>(src, p, i0, nbus, smem, gsum, []() {});
+    bus_segsum(w.epG + (size_t)t * p.twoL, p, i0, nbus, smem, gsum, []() {});
     if (tid < nbus) {
       if (a.fuse_adam) {
         adam_store(xm, a.m, a.v, ev, sv, gsum[0], w.params[PB_ALPHA + QG_C_V], vlo, vhi, ac);
@@ -1919,11 +1911,11 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, double* sm
       a.grad[e] = g;
     return;
   }
-  final_terms(a, smem);
+  final_terms(a, reinterpret_cast<double*>(smem));
 }
 
 __global__ __launch_bounds__(kBlock) void k_final(EvalArgs a) {
-  __shared__ double smem[2 * kSegChunk];
+  __shared__ Pair smem[kSegChunk];
   final_body(a, blockIdx.x, smem);
 }
 
@@ -1938,7 +1930,7 @@ __global__ __launch_bounds__(kBlock) void k_final(EvalArgs a) {
 // LDS, then each bus's segment in ascending slot order.  Only this block reads
 // or writes the period's V and theta in this kernel.
 __device__ __forceinline__ void update_period(const EvalArgs& a, const AdamCtx& ac, int t,
-                                             double* gv, double* gt) {
+                                              Pair* ge) {
   const DevProblem& p = a.p;
   const int N = p.N, tid = threadIdx.x;
   double* xm = const_cast<double*>(a.x);
@@ -1961,14 +1953,15 @@ __device__ __forceinline__ void update_period(const EvalArgs& a, const AdamCtx& 
     }
   };
   fetch(tid);
-  for (int l = tid; l < p.L; l += kUpdateBlock) branch_reverse(a, t, l, gv, gt);
+  for (int l = tid; l < p.L; l += kUpdateBlock) branch_reverse(a, t, l, ge);
   __syncthreads();
   for (int i = tid; i < N; i += kUpdateBlock) {
     const size_t ev = (size_t)t * N + i, et = TN + ev;
     double sum_v = 0.0, sum_t = 0.0;
     for (int s = lo; s < hi; ++s) {
-      sum_v += gv[s];
-      sum_t += gt[s];
+      const Pair e = ge[s];
+      sum_v += e.x;
+      sum_t += e.y;
     }
     if (a.fuse_adam) {
       adam_store(xm, a.m, a.v, ev, sv, sum_v, a.w.params[PB_ALPHA + QG_C_V], vlo, vhi, ac);
@@ -2056,18 +2049,19 @@ __device__ __forceinline__ void update_slab(const EvalArgs& a, const AdamCtx& ac
 // 16) x (Tp / 16); then the blocks of q, r and u; then the terms.  Every block
 // updates entries of x that no other block of the kernel reads.
 __global__ __launch_bounds__(kUpdateBlock) void k_update(EvalArgs a) {
-  extern __shared__ double dyn[];
+  extern __shared__ Pair dyn2[];
+  double* smem = reinterpret_cast<double*>(dyn2);
   const DevProblem& p = a.p;
   const AdamCtx ac = adam_ctx(a);
   int bx = blockIdx.x;
   if (bx < p.T) {
-    update_period(a, ac, bx, dyn, dyn + p.twoL);
+    update_period(a, ac, bx, dyn2);
     return;
   }
   bx -= p.T;
   const int nslab = p.G16 / 16 * (p.Tp / 16);
   if (bx < nslab) {
-    update_slab(a, ac, bx, dyn);
+    update_slab(a, ac, bx, smem);
     return;
   }
   bx -= nslab;
@@ -2077,7 +2071,7 @@ __global__ __launch_bounds__(kUpdateBlock) void k_update(EvalArgs a) {
     if (idx < TG) final_qru(a, ac, cls, idx);
     return;
   }
-  final_terms(a, dyn);
+  final_terms(a, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -2320,7 +2314,7 @@ __global__ __launch_bounds__(kBatchRowWaves * 64) void k_ctg_rows_b(const EvalAr
 
 __global__ __launch_bounds__(kBlock) void k_ctg_asm_b(const EvalArgs* __restrict__ args,
                                                       const uint32_t* __restrict__ tab) {
-  __shared__ double smem[2 * kSegChunk + 16];
+  __shared__ Pair smem[kSegChunk];
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
   const EvalArgs& a = args[s];
@@ -2338,7 +2332,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_b(const EvalArgs* __restrict
 
 __global__ __launch_bounds__(kBlock) void k_final_b(const EvalArgs* __restrict__ args,
                                                     const uint32_t* __restrict__ tab) {
-  __shared__ double smem[2 * kSegChunk];
+  __shared__ Pair smem[kSegChunk];
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
   final_body(args[s], b, smem);
