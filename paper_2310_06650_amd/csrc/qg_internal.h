@@ -38,6 +38,29 @@ inline int lodf_kind_of(uint32_t flags) {
 }
 inline size_t lodf_elem_bytes(int kind) { return kind == kLodfF64 ? 8 : kind == kLodfF32 ? 4 : 2; }
 
+// Pointer to device memory in a kernel's arguments.  Kernels of a batch read
+// their arguments from memory, where the compiler cannot see that the pointers
+// are to global memory: it would use flat accesses, which also count and wait
+// as LDS accesses.
+#ifdef __HIPCC__
+#define QG_BOTH __host__ __device__
+#else
+#define QG_BOTH
+#endif
+template <class T>
+struct DevPtr {
+  T* p;
+  DevPtr() = default;
+  QG_BOTH DevPtr(T* q) : p(q) {}
+  QG_BOTH operator T*() const {
+#if defined(__HIP_DEVICE_COMPILE__) && __HIP_DEVICE_COMPILE__
+    return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
+#else
+    return p;
+#endif
+  }
+};
+
 // Device view of the constant arena (all pointers into caller memory).
 struct DevProblem {
   int N, L, G, T, M, K;
@@ -48,35 +71,36 @@ struct DevProblem {
   int Tp;    // T padded to 16 (MFMA rows)
   int twoL;  // endpoint slots per period
   // branches
-  const int* br_from; const int* br_to; const int* slot_fr; const int* slot_to;
-  const double* br_g; const double* br_b; const double* br_bh; const double* br_smax;
-  const double* ctg_smax;   // [Lp] contingency rating (1 on padding)
-  const double* ctg_smax2;  // [Lp] its square
-  const int* kof;           // [Lp] contingency index of a branch, -1 if none
-  const int* brk;           // [Kp] outaged branch of a contingency (0 on padding)
+  DevPtr<const int> br_from, br_to, slot_fr, slot_to;
+  DevPtr<const double> br_g, br_b, br_bh, br_smax;
+  DevPtr<const double> ctg_smax;  // [Lp] contingency rating (1 on padding)
+  DevPtr<const double> ctg_smax2;  // [Lp] its square
+  DevPtr<const int> kof;  // [Lp] contingency index of a branch, -1 if none
+  DevPtr<const int> brk;  // [Kp] outaged branch of a contingency (0 on padding)
   // buses
-  const int* bptr;          // [N+1] endpoint-slot ranges (bus-sorted)
-  const int* gptr;          // [N+1] generator ranges
-  const int* glist;         // [G]   generators sorted by bus
-  const double* vmin; const double* vmax;
+  DevPtr<const int> bptr;  // [N+1] endpoint-slot ranges (bus-sorted)
+  DevPtr<const int> gptr;  // [N+1] generator ranges
+  DevPtr<const int> glist;  // [G]   generators sorted by bus
+  DevPtr<const double> vmin, vmax;
   // generators
-  const int* gen_bus;
-  const double *pmin, *pmax, *qmin, *qmax, *rmax, *ru, *rd, *rusu, *rdsd, *p0, *u0;
-  const double *con, *csu, *csd, *cr;
-  const double *seg_cost, *seg_size, *pcum;   // [G*M]
+  DevPtr<const int> gen_bus;
+  DevPtr<const double> pmin, pmax, qmin, qmax, rmax, ru, rd, rusu, rdsd, p0, u0;
+  DevPtr<const double> con, csu, csd, cr;
+  DevPtr<const double> seg_cost, seg_size, pcum;  // [G*M]
   // periods
-  const double* load_p; const double* load_q;  // [T*N]
-  const double* dt; const double* rsv_req; const double* sum_load;  // [T]
+  DevPtr<const double> load_p, load_q;  // [T*N]
+  DevPtr<const double> dt, rsv_req, sum_load;  // [T]
   // sensitivities, restricted to generator buses
-  const double* isf_gT;  // [G4][Lp]  ISF[l][bus(j)] - rsum[l]/N, zero padded (B of the flow product)
-  const double* isf_ga;  // [Lp][G16] ISF[l][bus(j)] - rsum[l]/N (B of the adjoint product)
-  const double* cload;   // [T][Lp]   sum_i ISF[l][i] load_p[t][i] - rsum[l] sum_load[t] / N
-  const double* rsum;    // [Lp]      sum_i ISF[l][i]
-  const double* lodf;    // [Lp][Kp]  outage factors; NaN marks (k,k) and padding
-  const float* lodf32;   //           the same in FP32 (QG_FLAG_CTG_FP32)
-  const uint16_t* lodf16;  //         the same in BF16 (QG_FLAG_CTG_BF16)
+  // [G4][Lp] ISF[l][bus(j)] - rsum[l]/N, zero padded (B of the flow product)
+  DevPtr<const double> isf_gT;
+  DevPtr<const double> isf_ga;  // [Lp][G16] ISF[l][bus(j)] - rsum[l]/N (B of the adjoint product)
+  DevPtr<const double> cload;  // [T][Lp]   sum_i ISF[l][i] load_p[t][i] - rsum[l] sum_load[t] / N
+  DevPtr<const double> rsum;  // [Lp]      sum_i ISF[l][i]
+  DevPtr<const double> lodf;  // [Lp][Kp]  outage factors; NaN marks (k,k) and padding
+  DevPtr<const float> lodf32;  //           the same in FP32 (QG_FLAG_CTG_FP32)
+  DevPtr<const uint16_t> lodf16;  //         the same in BF16 (QG_FLAG_CTG_BF16)
   int lodf_kind;         // 0 FP64, 1 FP32, 2 BF16 (one of the three pointers is set)
-  const double* lmax;    // [Kp/64][Lp] max |lodf| (as stored) of each branch over
+  DevPtr<const double> lmax;  // [Kp/64][Lp] max |lodf| (as stored) of each branch over
                          // 64 contingencies, NaN left out (null with QG_FLAG_CTG_NO_SKIP)
   int ctg_sum;           // 1: per-period sum over contingencies instead of max + mean
   // prices
@@ -90,42 +114,42 @@ struct alignas(16) Pair {
 
 // Device view of the caller's workspace.
 struct DevWork {
-  double* params;      // [kParams] parameters of the step being evaluated
-  int64_t* step;       // [1] index of the current step in the schedule table
-  double* sched;       // [kSchedCap][kSchedStride] per-step eps, beta, rho_s, alpha[6], bc1, bc2
-  double* snext;       // [kSchedStride] the schedule row of the next scheduled evaluation
-  Pair* ep;            // [T][2L] branch flows (p, q) at bus-sorted endpoint slots
+  DevPtr<double> params;  // [kParams] parameters of the step being evaluated
+  DevPtr<int64_t> step;  // [1] index of the current step in the schedule table
+  DevPtr<double> sched;  // [kSchedCap][kSchedStride] per-step eps, beta, rho_s, alpha[6], bc1, bc2
+  DevPtr<double> snext;  // [kSchedStride] the schedule row of the next scheduled evaluation
+  DevPtr<Pair> ep;  // [T][2L] branch flows (p, q) at bus-sorted endpoint slots
   // [3][T][L] per-branch reverse coefficients: cosine and sine, thermal derivative
   // by p and q, angle derivative and 2 q, the latter two pairs of the sides in bside
-  Pair* bco;
-  uint8_t* bside;      // [T][L] kThermalTo, kReactiveTo
-  double* q2;          // [T][Lp]  max(q_fr^2, q_to^2)
-  double* F;           // [T][Lp]  base-case DC flows
-  double* Fk;          // [T][Kp]  flows of the outaged branches
-  double* lamp; double* lamq;    // [T][N] balance multipliers
-  double* gdev;        // [4][T][G] device-only partials of p, q, r, u
-  double* zpart; double* spart;  // [nLb][T][Kp]
-  double* rpart; double* qpart;  // [nKb][T][Lp] (branch-stacked tile)
-  double* rq;          // [T][Lp][nKb_max][2] R and Q per contingency block (period-split
+  DevPtr<Pair> bco;
+  DevPtr<uint8_t> bside;  // [T][L] kThermalTo, kReactiveTo
+  DevPtr<double> q2;  // [T][Lp]  max(q_fr^2, q_to^2)
+  DevPtr<double> F;  // [T][Lp]  base-case DC flows
+  DevPtr<double> Fk;  // [T][Kp]  flows of the outaged branches
+  DevPtr<double> lamp, lamq;  // [T][N] balance multipliers
+  DevPtr<double> gdev;  // [4][T][G] device-only partials of p, q, r, u
+  DevPtr<double> zpart, spart;  // [nLb][T][Kp]
+  DevPtr<double> rpart, qpart;  // [nKb][T][Lp] (branch-stacked tile)
+  DevPtr<double> rq;  // [T][Lp][nKb_max][2] R and Q per contingency block (period-split
                        // tile; the memory of rpart and qpart), stored where flagged:
-  uint64_t* hot;       // [T][Lp/64][nKb_max] flags of 64 branches per contingency block
-  double* smean;       // [T][Kp]
-  double* zval;        // [T][Kp]
-  double* gfT;         // [Lp][Tp] dL/dF, transposed
-  double* qtot;        // [T][Lp]  dL/d qmax2
-  double* gpdc;        // [nsplit][T][G16] DC part of dL/dp (split-K partials)
-  Pair* epG;           // [T][2L] endpoint adjoints (V, theta)
-  double* tpart;       // term partial sums
-  double* terms;       // [QG_NTERMS] last evaluated terms
-  double* drs;         // [T]       reserve-shortfall derivative, subtracted from dL/dr
-  double* zmaxp;       // [T][nKc]  per-chunk worst penalty
-  double* zargp;       // [T][nKc]  its contingency index
-  double* zsump;       // [T][nKc]  per-chunk penalty sum
-  double* kstar;       // [T]       worst contingency of the period
-  double* smaxp;       // [T][nLc]  per-chunk dL/dF of the worst contingency's own branch
-  double* lamg; double* lamqg;   // [T][G] balance multipliers at each generator's bus
-  double* isfk;        // [T][G16]  ISF[br(k*_t)][bus(j)] - rowsum/N of the period's worst outage
-  double* thr;         // [T][Lp]  test radius of the outage flows
+  DevPtr<uint64_t> hot;  // [T][Lp/64][nKb_max] flags of 64 branches per contingency block
+  DevPtr<double> smean;  // [T][Kp]
+  DevPtr<double> zval;  // [T][Kp]
+  DevPtr<double> gfT;  // [Lp][Tp] dL/dF, transposed
+  DevPtr<double> qtot;  // [T][Lp]  dL/d qmax2
+  DevPtr<double> gpdc;  // [nsplit][T][G16] DC part of dL/dp (split-K partials)
+  DevPtr<Pair> epG;  // [T][2L] endpoint adjoints (V, theta)
+  DevPtr<double> tpart;  // term partial sums
+  DevPtr<double> terms;  // [QG_NTERMS] last evaluated terms
+  DevPtr<double> drs;  // [T]       reserve-shortfall derivative, subtracted from dL/dr
+  DevPtr<double> zmaxp;  // [T][nKc]  per-chunk worst penalty
+  DevPtr<double> zargp;  // [T][nKc]  its contingency index
+  DevPtr<double> zsump;  // [T][nKc]  per-chunk penalty sum
+  DevPtr<double> kstar;  // [T]       worst contingency of the period
+  DevPtr<double> smaxp;  // [T][nLc]  per-chunk dL/dF of the worst contingency's own branch
+  DevPtr<double> lamg, lamqg;  // [T][G] balance multipliers at each generator's bus
+  DevPtr<double> isfk;  // [T][G16]  ISF[br(k*_t)][bus(j)] - rowsum/N of the period's worst outage
+  DevPtr<double> thr;  // [T][Lp]  test radius of the outage flows
 };
 
 // Sides of a branch in DevWork::bside: set where the larger apparent power, the

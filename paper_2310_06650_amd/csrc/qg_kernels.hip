@@ -52,11 +52,8 @@ struct StepParams {
 struct EvalArgs {
   DevProblem p;
   DevWork w;
-  const double* x;
-  double* grad;
-  double* terms_out;
-  double* m;
-  double* v;
+  DevPtr<const double> x;
+  DevPtr<double> grad, terms_out, m, v;
   EvalMode mode;
   int fuse_adam;
   int nb_br, nb_bus, bus_chunks, nb_gen, nsplit;
@@ -69,12 +66,11 @@ struct EvalArgs {
   // contingency act_k[s] (the identity when act_k is null), na slots in use,
   // outage factors of the slots in rows of kst entries at lodf_sel;
   // act_slot maps a contingency back to its slot (-1 when not scored)
-  const int* act_k;
-  const int* act_slot;
+  DevPtr<const int> act_k, act_slot;
   int na, kst;
   const void* lodf_sel;
   // [nKb][Lp] largest |factor| of a branch over 64 slots (null: test every row)
-  const double* lmax;
+  DevPtr<const double> lmax;
 };
 
 // ---------------------------------------------------------------------------
@@ -1245,7 +1241,7 @@ __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* 
   constexpr bool kF64 = std::is_same<R, double>::value;
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
-  const LT* __restrict__ lodf = static_cast<const LT*>(a.lodf_sel);
+  const LT* __restrict__ lodf = DevPtr<const LT>(static_cast<const LT*>(a.lodf_sel));
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int T = p.T, L = p.L, Lp = p.Lp, ng = Lp >> 6;
@@ -1465,7 +1461,7 @@ __device__ __forceinline__ void gather_rq(const EvalArgs& a, int t, int g, uint6
   for (int c0 = 0; c0 < a.nKb; c0 += 64) {
     const uint64_t word = c0 == 0 ? hot : hot_word(a, t, g, c0 + lane);
     uint64_t any = wave_or(word);
-    const double2* src = reinterpret_cast<const double2*>(a.w.rq) +
+    const double2* src = reinterpret_cast<const double2*>(+a.w.rq) +
                          ((size_t)t * p.Lp + g * 64) * a.rqs + c0 + lane;
     do {
       int row[U];
@@ -1792,7 +1788,7 @@ __device__ __forceinline__ void final_qru(const EvalArgs& a, const AdamCtx& ac, 
   const int t = idx / p.G, j = idx - t * p.G;
   const size_t TG = (size_t)p.T * p.G;
   const size_t e = 2 * (size_t)p.T * p.N + cls * TG + idx;
-  double* xm = const_cast<double*>(a.x);
+  double* xm = const_cast<double*>(+a.x);
   AdamVar sv{0.0, 0.0, 0.0};
   if (a.fuse_adam) sv = adam_load(xm, a.m, a.v, e);
   double g = w.gdev[cls * TG + idx], lo = 0.0, hi = 1.0;
@@ -1856,7 +1852,7 @@ __device__ __forceinline__ void final_body(const EvalArgs& a, int bx, Pair* smem
   const int tid = threadIdx.x;
   const int T = p.T, N = p.N, G = p.G;
   const AdamCtx ac = adam_ctx(a);
-  double* xm = const_cast<double*>(a.x);
+  double* xm = const_cast<double*>(+a.x);
   if (bx < a.nb_bus) {
     const int t = bx / a.bus_chunks;
     const int c = bx - t * a.bus_chunks;
@@ -1933,7 +1929,7 @@ __device__ __forceinline__ void update_period(const EvalArgs& a, const AdamCtx& 
                                               Pair* ge) {
   const DevProblem& p = a.p;
   const int N = p.N, tid = threadIdx.x;
-  double* xm = const_cast<double*>(a.x);
+  double* xm = const_cast<double*>(+a.x);
   // the first buses' Adam state and segments, in flight with the branches
   const size_t TN = (size_t)p.T * N;
   AdamVar sv{0.0, 0.0, 0.0}, st{0.0, 0.0, 0.0};
@@ -1985,7 +1981,7 @@ __device__ __forceinline__ void update_slab(const EvalArgs& a, const AdamCtx& ac
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mtiles = Tp / 16;
   const int n0 = blk / mtiles * 16, r0 = blk % mtiles * 16;
-  double* xm = const_cast<double*>(a.x);
+  double* xm = const_cast<double*>(+a.x);
   // everything else of the thread's output first, in flight with the product
   const int j = n0 + (tid & 15), t = r0 + (lane >> 4) + 4 * (tid >> 6);
   const bool out = tid < 256 && t < T && j < G;
