@@ -1443,9 +1443,10 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t v) {
 // R and Q of the wavefront's 64 branches (lane = branch l of period t) from
 // the map-reduce's per-contingency-block sums.  Few branches hold any, and
 // those that do mostly hold one in every block, so each is summed across the
-// lanes (lane = contingency block, one 16-byte load each), eight branches'
-// loads in flight together.  mid() runs while the first branches' loads are
-// in flight.
+// lanes (lane = contingency block, one 16-byte load each), four branches'
+// loads in flight together (eight cost registers and a block per CU: 19.3 us
+// against 17.2 in a batch of twelve grids, 7.1 against 6.5 at 617 buses).  mid()
+// runs while the first branches' loads are in flight.
 // hot: the lane's word of the first 64 contingency blocks (hot_word).
 __device__ __forceinline__ uint64_t hot_word(const EvalArgs& a, int t, int g, int c) {
   const int ng = a.p.Lp >> 6;
@@ -1454,7 +1455,7 @@ __device__ __forceinline__ uint64_t hot_word(const EvalArgs& a, int t, int g, in
 template <class Mid>
 __device__ __forceinline__ void gather_rq(const EvalArgs& a, int t, int g, uint64_t hot, double& r,
                                           double& q, Mid mid) {
-  constexpr int U = 8;
+  constexpr int U = 4;
   const DevProblem& p = a.p;
   const int lane = threadIdx.x & 63;
   bool first = true;
@@ -2318,7 +2319,9 @@ __global__ __launch_bounds__(kBlock) void k_ctg_asm_b(const EvalArgs* __restrict
                      smem);
 }
 
-__global__ __launch_bounds__(kBlock) void k_adjoint_b(const EvalArgs* __restrict__ args,
+// Four blocks per CU (two registers fewer than the compiler would take): 14.7 us
+// against 15.2 for twelve grids; with five it spills, 19.2.
+__global__ __launch_bounds__(kBlock, 4) void k_adjoint_b(const EvalArgs* __restrict__ args,
                                                       const uint32_t* __restrict__ tab) {
   __shared__ double smem[kSlabLds];
   int s, b;
