@@ -330,11 +330,11 @@ struct BatchPlan {
   size_t bytes = 0;            // size of the batch buffer
   int lodf_kind = 0;
   int nsl = 0;                 // most branch slices of a problem (map-reduce LDS)
+  int row_waves = 0;           // wavefronts per block of the map-reduce
 };
 constexpr int kBatchLocBits = 22;                  // block index bits of a table entry
 constexpr int kBatchWl = 4;        // the tile a batch asks of its problems: wavefronts
 constexpr int kBatchTcw = 4;       // and periods per wavefront
-constexpr int kBatchRowWaves = 8;  // wavefronts per block of the batched map-reduce
 // Sizes, validation and (image != nullptr) the host image of a batch buffer
 // for problems whose steps take x[i], m[i], v[i] and workspaces ws[i]; 0 or
 // a message in *err.

@@ -2297,12 +2297,12 @@ __global__ __launch_bounds__(kBlock) void k_forward_b(const EvalArgs* __restrict
   forward_body(args[s], b, smem);
 }
 
-// Batched row-compacted map-reduce: blocks of kBatchRowWaves wavefronts, each
-// taking the slices of its (period, contingency block) in turn; the sums are
-// added in slice order, as in a launch of the problem's own.
+// Batched row-compacted map-reduce: each wavefront takes slices of its block's
+// (period, contingency block) in turn; the sums are added in slice order, as in
+// a launch of the problem's own.
 template <typename LT>
-__global__ __launch_bounds__(kBatchRowWaves * 64) void k_ctg_rows_b(const EvalArgs* __restrict__ args,
-                                                             const uint32_t* __restrict__ tab) {
+__global__ __launch_bounds__(kCtgSlices * 64) void k_ctg_rows_b(const EvalArgs* __restrict__ args,
+                                                                const uint32_t* __restrict__ tab) {
   extern __shared__ double dyn[];
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
@@ -2413,6 +2413,13 @@ int plan_batch(const Problem* const* prs, const DevWork* ws, int n, const double
     }
   }
   for (int i = 0; i < n; ++i) P.nsl = std::max(P.nsl, args[i].nsl);
+  // Four wavefronts a block of the map-reduce, more only while the chip (28 a
+  // CU) has room for them: a block of few hands its place on sooner, and a small
+  // batch needs them to fill the chip.  Twelve grids (4414 blocks): 39 us a step
+  // with 3 or 4, 47 with 2, 5 or 8, 56 with 12.
+  P.row_waves = 4;
+  while (2 * P.row_waves <= kCtgSlices && (int64_t)P.nblk[1] * 2 * P.row_waves <= 28 * 256)
+    P.row_waves *= 2;
   *plan = P;
   return 0;
 }
@@ -2425,7 +2432,7 @@ int launch_eval_batch(const BatchPlan& P, void* d_buf, void* stream) {
   hipLaunchKernelGGL(k_forward_b, dim3(P.nblk[0]), dim3(kBlock), 0, s, args, tab(0));
   if (P.nblk[1] > 0) {
     const size_t lds = (size_t)P.nsl * 128 * sizeof(double);
-    const dim3 g(P.nblk[1]), blk(kBatchRowWaves * 64);
+    const dim3 g(P.nblk[1]), blk(P.row_waves * 64);
     if (P.lodf_kind == kLodfF64)
       hipLaunchKernelGGL(k_ctg_rows_b<double>, g, blk, lds, s, args, tab(1));
     else if (P.lodf_kind == kLodfF32)
