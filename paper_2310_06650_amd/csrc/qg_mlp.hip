@@ -165,13 +165,13 @@ struct Tile {
       s.b[buf][e & 63][e >> 6] = rb[d][q];
     }
   }
-  // step(buf): called after the barrier of every k-step with its LDS buffer, before
-  // its products
-  template <class Step>
+  // ahead(): called once the first k-steps' loads are issued; step(buf): after the
+  // barrier of every k-step with its LDS buffer, before its products
+  template <class Ahead, class Step>
   __device__ __forceinline__ void run(const float* __restrict__ A, int lda,
                                       const float* __restrict__ B, int ldb, int M, int N, int kb,
                                       int ke, int m0, int n0, TileLds& s, v4f (&acc)[2],
-                                      Step step) {
+                                      Ahead ahead, Step step) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int wm = (wv >> 2) * 32, wn = (wv & 3) * 16;
 #pragma unroll
@@ -187,6 +187,8 @@ struct Tile {
     };
 #pragma unroll
     for (int d = 0; d < kDepth; ++d) fetch(d, kb + d * kBK);
+    ahead();
+    __builtin_amdgcn_sched_barrier(0);
     // the loads stay ahead of the products, and a k-step's LDS reads ahead of
     // its first product (a wavefront or two per SIMD do not hide them)
     auto step1 = [&](int d, int buf, int k0) {
@@ -215,10 +217,12 @@ struct Tile {
     // two of them would let the compiler move the loads behind it
     static_assert(kDepth == 2, "one LDS buffer per k-step of a round");
     int k0 = kb;
-    do {
+    auto round = [&]() {
 #pragma unroll
       for (int d = 0; d < kDepth; ++d, k0 += kBK) step1(d, d, k0);
-    } while (k0 < ke);
+    };
+    round();  // apart from the loop: its waits do not count ahead()'s loads
+    while (k0 < ke) round();
   }
 };
 
@@ -420,8 +424,8 @@ constexpr int kChain = 8;  // k-steps of one FP32 accumulation chain of a weight
 // Chains of kChain k-steps are added up in a second accumulator, so that the
 // rounding error does not grow with a long batch.
 // Bound by memory: at a batch of 64 the 15.1 M weights of 512 x 29412 (421 MB)
-// take 107 us, 4.0 TB/s (89 us with the product left out), the 5.7 M of
-// 11124 x 512 take 39; as products, column sums and a pass of updates these were
+// take 104 us, 4.1 TB/s (89 us with the product left out), the 5.7 M of
+// 11124 x 512 take 38; as products, column sums and a pass of updates these were
 // 32.7 + 15.8 + 101 us for the whole network.  Stores past the caches (read
 // again only in the next step) and neighbouring tiles on one XCD (rows are
 // not line-aligned, so neighbours share lines) give 4 and 3 us of it.  One kernel is
@@ -457,24 +461,30 @@ __global__ __launch_bounds__(kGemm) void k_dw(const float* __restrict__ in, int 
   const int n = n0 + c;
   const int rows = n < n_out ? min(kT, fan_in - m0) : 0;
   const size_t e0 = (size_t)m0 * n_out + n;
-  // parameters and moments, in flight with the product's operands
+  // parameters and moments, in flight while the product is formed: loads return
+  // in order, so the operands', which come from L2, go first.  Unconditional (past
+  // the matrix they read zeros or the next row, and are not used): a wait
+  // behind a load that may not have been issued waits for all.  104 us where it
+  // was 107 with these loads first.
   float p[R], m[R], v[R];
-  if constexpr (ADAM) {
+  auto params = [&]() {
+    if constexpr (ADAM) {
+      const auto vp = operand<true>(w.pw, n_out, n_out, n0, m0, fan_in);
+      const auto vm = operand<true>(w.mw, n_out, n_out, n0, m0, fan_in);
+      const auto vv = operand<true>(w.vw, n_out, n_out, n0, m0, fan_in);
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int row = q8 + 8 * i;
-      if (row < rows) {
-        const size_t e = e0 + (size_t)row * n_out;
-        p[i] = w.pw[e];
-        m[i] = w.mw[e];
-        v[i] = w.vw[e];
+      for (int i = 0; i < R; ++i) {
+        const unsigned o = ((unsigned)(q8 + 8 * i) * n_out + c) * 4u;
+        p[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vp, o, 0, 0));
+        m[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vm, o, 0, 0));
+        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vv, o, 0, 0));
       }
     }
-  }
+  };
   Tile tile;
   v4f acc[2], done[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
   int left = kChain;
-  tile.run(in, fan_in, dZ, n_out, fan_in, n_out, 0, batch, m0, n0, s.t, acc, [&](int buf) {
+  tile.run(in, fan_in, dZ, n_out, fan_in, n_out, 0, batch, m0, n0, s.t, acc, params, [&](int buf) {
     if (first)
       for (int k = q8; k < kBK; k += 8) cs += s.t.b[buf][c][k];
     if (left-- == 0) {
