@@ -75,24 +75,29 @@ def parse():
     return ap.parse_args()
 
 
-def kernel_work(case, dims):
+def kernel_work(case, dims, factor_bytes=8):
     """Algorithmic work per launch of each kernel: (bound, amount, unit)."""
     T, N, L, G, K = case.n_period, case.n_bus, case.n_branch, case.n_gen, case.n_ctg
     D = 8
     return {
-        # per (t, l): x gathers and 15 doubles out; per (t, j): 4 in, 4 out;
-        # flow product 2 T G L flop (reported as bytes: the product is tiny)
-        "k_forward": ("hbm", D * (2 * T * N + 4 * T * G + T * L * 15 + T * G * 4 + T * L), "byte"),
+        # per (t, l): x gathers, 12 doubles and a byte out; flow product 2 T G L
+        # flop (reported as bytes: the product is tiny)
+        "k_forward": ("hbm", D * (2 * T * N + T * G + T * L * 13) + T * L, "byte"),
         # every (t, l, k) element, forward and reverse in dense form: the
         # post-outage flow and its square (2 FMA), the R and Q row sums (2 add)
         # and the LODF-weighted S column sum (1 FMA): 8 flop
-        "k_ctg_main": ("alu", 8.0 * T * L * K, "flop"),
+        # (branch-stacked tile).  The period-split form decides most elements by a
+        # bound without those: it is priced by what it reads and writes at most
+        # once, the factors, F, thr and q2 per (t, l), F_k and z per (t, k)
+        "k_ctg_main": (("hbm", factor_bytes * L * K + D * (3 * T * L + 2 * T * K), "byte")
+                       if dims["ctg_split"] else ("alu", 8.0 * T * L * K, "flop")),
         # partial sums over l-blocks for every (t, k)
         "k_ctg_zred": ("hbm", D * T * K * (dims["nLb"] * 2 + 2), "byte"),
         # partial sums over k-blocks for every (t, l); balance over bus-sorted ends
         "k_ctg_asm": ("hbm", D * (T * L * (dims["nKb"] * 2 + 6) + T * 2 * L * 2 + 4 * T * N), "byte"),
-        # adjoint product 2 T G L flop; branch reverse reads 9 coefficients, writes 4
-        "k_adjoint": ("hbm", D * (T * L * 13 + 2 * T * N + T * L), "byte"),
+        # adjoint product 2 T G L flop; branch reverse reads 6 coefficients and a
+        # byte, writes 4
+        "k_adjoint": ("hbm", D * (T * L * 10 + 2 * T * N + T * L) + T * L, "byte"),
         # endpoint adjoints, generator assembly and the fused Adam (48 B per entry)
         "k_final": ("hbm", D * (T * 2 * L * 2 + 4 * T * G + 6 * (2 * T * N + 4 * T * G)), "byte"),
     }
@@ -284,7 +289,7 @@ def main():
                                               profile=1, **{**common, "use_graph": 0}))
     torch.cuda.synchronize()
     kms_step = {k: float(ms) for k, ms in zip(qg.KERNEL_NAMES, list(rep_p.kernel_ms))}
-    work = kernel_work(case, prob.dims)
+    work = kernel_work(case, prob.dims, dict(fp64=8, fp32=4, bf16=2)[args.ctg_precision])
     # the dominant kernel: the largest share of a step (the in-step durations;
     # a short kernel's back-to-back mean varies with the clock more than the
     # order of the in-step durations does); its rate over the back-to-back mean
@@ -304,7 +309,9 @@ def main():
     # the map-reduce stage runs k_ctg_rows under a period-split tile
     kname = "k_ctg_rows" if (dom == "k_ctg_main" and prob.dims["ctg_split"]) else dom
     roof = dict(bound=bound, kernel=kname, achieved=achieved, peak=peak, unit=runit,
-                frac=achieved / peak, traffic=stored_traffic(kname, args.config, prob.tile()),
+                frac=achieved / peak,
+                traffic=(stored_traffic(kname, args.config, prob.tile())
+                         if args.ctg_precision == "fp64" else None),
                 per_launch=f"{amount:.4g} {unit} algorithmic, mean {kms[dom] * 1e3:.2f} us/launch")
     out = dict(metric=METRIC, value=steps_per_s, unit="steps/s", n_gpus=1, steps=args.steps,
                warmup=args.warmup, repeats=args.repeats, ms_per_step=1e3 * el / args.steps,

@@ -6,8 +6,8 @@ Builds the scenarios of synth.batch_cases (bus counts 100..2000, 12..48
 periods, every non-islanding outage), picks each one's contingency tile with
 the autotuner, and measures the same number of Adam steps two ways: each
 scenario solved alone in turn (its own step graphs), and all of them in one
-batched solve (qg_solve_batch: six launches per step for the whole batch,
-the contingency map-reduce persistent over a work list, 16 steps per graph).
+batched solve (qg_solve_batch: five launches per step for the whole batch,
+16 steps per graph).
 Prints one JSON line with scenario-steps per second, contingency elements per
 second and the effective rate of outage-factor bytes.
 """
