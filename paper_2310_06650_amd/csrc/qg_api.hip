@@ -1027,7 +1027,7 @@ qg_status qg_solve_batch(qg_problem* const* probs, int32_t n, double* const* d_x
           "batch upload");
   HIP_TRY(hipStreamSynchronize(ex), "sync");
 
-  // one graph of gsteps batched steps (six launches each)
+  // one graph of gsteps batched steps (five launches each)
   const int gsteps = (int)std::min<int64_t>(16, std::max<int64_t>(1, o->n_steps));
   hipGraphExec_t gexec = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};

@@ -3,7 +3,7 @@
 This module only draws inputs: topology, branch impedances and ratings,
 generator data, load profiles and contingency lists.  It holds none of the
 solver's arithmetic (no power flow, no sensitivities, no objective), so both
-the HIP library and the independent CPU checker can take their inputs from it.
+the HIP library and the independent CPU oracle can take their inputs from it.
 
 The recipe stands in for the GO3 C3E3.1 division-1 cases the paper measures
 on (Section IV, Table 1; Fig. 1 uses a 617-bus, 18-period case with 562 line
