@@ -36,11 +36,6 @@
 
 #include "qg_internal.h"
 
-// Products and sums contract to FMAs inside an expression only: across statements
-// the choice would depend on where a function is inlined, and the kernels of a
-// problem's own step and of a batch, which share functions, would round differently.
-#pragma clang fp contract(on)
-
 namespace qg {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -1648,6 +1643,10 @@ __global__ __launch_bounds__(kBlock) void k_ctg_asm(EvalArgs a) {
 // Adjoints (V, theta) of branch l's two ends in period t, at their bus-sorted
 // slots.
 __device__ __forceinline__ void branch_reverse(const EvalArgs& a, int t, int l, Pair* ge) {
+  // FMAs inside an expression only: across statements the choice would depend on
+  // where the function is inlined, and k_update and k_adjoint_b would round
+  // differently
+#pragma clang fp contract(on)
   const DevProblem& p = a.p;
   const DevWork& w = a.w;
   const int T = p.T, L = p.L, N = p.N;
@@ -1766,6 +1765,7 @@ __device__ __forceinline__ AdamVar adam_load(const double* x, const double* m, c
 __device__ __forceinline__ void adam_store(double* x, double* m, double* v, size_t e,
                                            const AdamVar& s, double g, double lr, double lo,
                                            double hi, const AdamCtx& c) {
+#pragma clang fp contract(on)  // as in branch_reverse
   const double mm = c.b1 * s.m + (1.0 - c.b1) * g;
   const double vv = c.b2 * s.v + (1.0 - c.b2) * g * g;
   const double mh = mm / c.bc1;
