@@ -561,16 +561,23 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     const size_t ep = (size_t)t * p.twoL;
     w.ep[ep + p.slot_fr[l]] = Pair{pf, qf};
     w.ep[ep + p.slot_to[l]] = Pair{pt, qt};
-    // thermal penalty on the larger side (ties: from side), Example 1
+    // thermal penalty on the larger side, Example 1; ties go to the from side,
+    // also where only the rounded roots are equal (squares further apart than
+    // 2^-50 have different roots).  The root is sqrt's: of an infinite square it is
+    // infinite, where x rsqrt_nr(x) is NaN and the penalty would fall to its floor
     const double sf2 = pf * pf + qf * qf, st2 = pt * pt + qt * qt;
-    const bool use_f = sf2 >= st2;
-    const double ss2 = use_f ? sf2 : st2;
-    const double rs = ss2 > 0.0 ? rsqrt_nr(ss2) : 0.0;
-    const double eb = ss2 * rs - p.br_smax[l];
+    bool use_f = sf2 >= st2;
+    if (!use_f && sf2 >= st2 * (1.0 - 0x1p-50)) use_f = sqrt(sf2) >= sqrt(st2);
+    const double ss = sqrt(use_f ? sf2 : st2);
+    const double eb = ss - p.br_smax[l];
     const double kbr = p.dt[t] * p.c_s * sp.beta;
-    double kth;
+    double kth, kp = 0.0, kq = 0.0;
     part[0] = kbr * soft_relu_pair(eb, sp.eps, kth);
-    kth *= kbr * rs;
+    kth *= kbr;
+    if (ss > 0.0) {
+      kp = kth * (use_f ? pf : pt) / ss;
+      kq = kth * (use_f ? qf : qt) / ss;
+    }
     // angle-difference penalty
     const double ea = fabs(d) - p.ang_max;
     const double kang = p.dt[t] * p.c_ang * sp.beta;
@@ -596,7 +603,7 @@ __device__ void branch_forward(const EvalArgs& a, const StepParams& sp, int blk,
     // 8-byte stores took 1.6 us more of 14.7 at 2800 branches and 48 periods, and as
     // much in the reverse pass)
     w.bco[e] = Pair{cs, sn};
-    w.bco[TL + e] = Pair{kth * (use_f ? pf : pt), kth * (use_f ? qf : qt)};
+    w.bco[TL + e] = Pair{kp, kq};
     w.bco[2 * TL + e] = Pair{kd, 2.0 * (qfr ? qf : qt)};
     w.bside[e] = (uint8_t)((use_f ? 0 : kThermalTo) | (qfr ? 0 : kReactiveTo));
   }
