@@ -263,6 +263,11 @@ __device__ __forceinline__ void tile_elements(const v4f (&acc)[2], int m0, int n
 // kernels of their own it took 67.  Its transposed product takes 24 us (32
 // through LDS).  More steps in flight (DEPTH 3, 4 at MI = 4) were 10 % slower.
 constexpr int kStep = 16;
+// Steps of one accumulation chain: 32 of the reduction, added to a wavefront's sum
+// at its end.  With one chain per wavefront (64 at 512 deep) the outputs of
+// 600 -> 3 x 512 -> 600 at 64 rows are off by 3.4e-7, with this by 2.7e-7, and
+// a pass takes 26.6 us where it took 26.4, at 1024 rows 54.9 where it took 50.1.
+constexpr int kChain = 2;
 constexpr int waves_of(int mi) { return mi == 1 ? 8 : 4; }
 constexpr int kCPitch = kT + 4;
 template <int DEPTH, int MI, int TB>
@@ -271,16 +276,17 @@ __global__ __launch_bounds__(waves_of(MI) * 64) void k_product(const float* __re
                                                          float* __restrict__ C, int M, int N, int K,
                                                          int kslice, int split, EpiArgs ep) {
   constexpr int kWaves = waves_of(MI);
+  constexpr bool kOne = DEPTH == 1 || (MI == 1 && DEPTH <= kChain);  // a wavefront's steps: one chain
   __shared__ alignas(16) float s[kWaves][16 * MI][kCPitch];
   const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m0 = blockIdx.y * 16 * MI, n0 = blockIdx.x * kT;
   const int kb = blockIdx.z * kslice, ke = min(K, kb + kslice);
-  v4f acc[MI][4];
+  v4f acc[MI][4], done[MI][4];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 4; ++j) acc[i][j] = done[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
   v4f a[DEPTH][MI], b[DEPTH][4];
   unsigned oa[MI], ob[4];  // byte offsets in the operands' views
 #pragma unroll
@@ -329,8 +335,23 @@ __global__ __launch_bounds__(waves_of(MI) * 64) void k_product(const float* __re
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
                 a[d][i][q], TB ? b[d][j][q] : b[d][q][j], acc[i][j], 0, 0, 0);
       fetch(d, k0 + DEPTH * kWaves * kStep);
+      if (!kOne && d % kChain == kChain - 1) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            done[i][j] += acc[i][j];
+            acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+          }
+      }
     }
   } while (k0 - wv * kStep < ke);
+  if (kOne) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) done[i][j] = acc[i][j];
+  }
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -338,10 +359,10 @@ __global__ __launch_bounds__(waves_of(MI) * 64) void k_product(const float* __re
       float* row = s[wv][16 * i + 4 * kq + q];
       if (TB) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) row[16 * j + r] = acc[i][j][q];
+        for (int j = 0; j < 4; ++j) row[16 * j + r] = done[i][j][q];
       } else {
         *reinterpret_cast<v4f*>(row + 4 * r) =
-            v4f{acc[i][0][q], acc[i][1][q], acc[i][2][q], acc[i][3][q]};
+            v4f{done[i][0][q], done[i][1][q], done[i][2][q], done[i][3][q]};
       }
     }
   __syncthreads();
@@ -410,7 +431,9 @@ __device__ __forceinline__ int2 xcd_tile() {
   return {(int)(t % gridDim.x), (int)(t / gridDim.x)};
 }
 
-constexpr int kChain = 8;  // k-steps of one FP32 accumulation chain of a weight gradient
+// Sums of a weight gradient's chains, of eight terms each but the last.
+constexpr int kDwLevels = 4;
+constexpr int kDwShort = 8 * kBK;  // longest batch for which one sum is enough
 
 // Weight and bias gradient of one layer, dW [M = fan_in][N = n_out] = in^T dZ
 // and db = column sums of dZ [K = batch][N], and with ADAM the update of the
@@ -421,8 +444,10 @@ constexpr int kChain = 8;  // k-steps of one FP32 accumulation chain of a weight
 // column sums are formed by the blocks of the first row of tiles from the
 // staged operand, each column's rows in eight interleaved parts that are then
 // added in order.
-// Chains of kChain k-steps are added up in a second accumulator, so that the
-// rounding error does not grow with a long batch.
+// Chains of one k-step (32 rows) are added up eight at a time, those sums eight at
+// a time, and so on: with longer chains, or all of them in one sum, the rounding
+// error grows with the batch (65536 rows of 40 -> 2 x 32 -> 40: 2.3e-7 of the gradient
+// with chains of 256 in one sum).
 // Bound by memory: at a batch of 64 the 15.1 M weights of 512 x 29412 (421 MB)
 // take 104 us, 4.1 TB/s (89 us with the product left out), the 5.7 M of
 // 11124 x 512 take 38; as products, column sums and a pass of updates these were
@@ -443,8 +468,8 @@ struct DwArgs {
   float* loss;
 };
 
-template <bool ADAM>
-__global__ __launch_bounds__(kGemm) void k_dw(const float* __restrict__ in, int fan_in,
+template <bool ADAM, int kLevels>
+__global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, int fan_in,
                                                  const float* __restrict__ dZ, int n_out, int batch,
                                                  DwArgs w) {
   __shared__ union alignas(16) {
@@ -482,22 +507,35 @@ __global__ __launch_bounds__(kGemm) void k_dw(const float* __restrict__ in, int 
     }
   };
   Tile tile;
-  v4f acc[2], done[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
-  int left = kChain;
+  v4f acc[2], sum[kLevels][2];
+#pragma unroll
+  for (int j = 0; j < kLevels; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) sum[j][i] = v4f{0.f, 0.f, 0.f, 0.f};
+  int chains = 0;  // in the sums
   tile.run(in, fan_in, dZ, n_out, fan_in, n_out, 0, batch, m0, n0, s.t, acc, params, [&](int buf) {
     if (first)
       for (int k = q8; k < kBK; k += 8) cs += s.t.b[buf][c][k];
-    if (left-- == 0) {
-      left = kChain - 1;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        done[i] += acc[i];
-        acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
-      }
+    for (int i = 0; i < 2; ++i) {
+      sum[0][i] += acc[i];
+      acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
     }
+#pragma unroll
+    for (int j = 1, n = 8; j < kLevels; ++j, n *= 8)
+      if (chains > 0 && chains % n == 0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          sum[j][i] += sum[j - 1][i];
+          sum[j - 1][i] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    ++chains;
   });
-  acc[0] += done[0];
-  acc[1] += done[1];
+#pragma unroll
+  for (int j = 0; j < kLevels; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[i] += sum[j][i];
   __syncthreads();
   tile_elements(acc, 0, 0, kT, kT, [&](int row, int col, float v) { s.c[row][col] = v; });
   __syncthreads();
@@ -1018,10 +1056,14 @@ hipError_t grad_step(hipStream_t s, const qg_mlp_desc* d, const qg_mlp_layout& L
       a.pw = u->p + wo; a.mw = u->m + wo; a.vw = u->v + wo;
       a.pb = u->p + bo; a.mb = u->m + bo; a.vb = u->v + bo;
       a.adam = u->adam;
-      hipLaunchKernelGGL(k_dw<true>, grid, dim3(kGemm), 0, s, in, fan_in, dcur, n_out, B, a);
-    } else {
-      hipLaunchKernelGGL(k_dw<false>, grid, dim3(kGemm), 0, s, in, fan_in, dcur, n_out, B, a);
     }
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kGemm), 0, s, in, fan_in, dcur, n_out, B, a);
+    };
+    if (u && B <= kDwShort) go(k_dw<true, 1>);
+    else if (u) go(k_dw<true, kDwLevels>);
+    else if (B <= kDwShort) go(k_dw<false, 1>);
+    else go(k_dw<false, kDwLevels>);
     dcur = dst;
     n_out = W;
   }
