@@ -582,15 +582,19 @@ __global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, i
 // flight (a slice of one, of a multiple of three, or of another number).
 // APAIR, PAIR: two neighbouring elements of A, B per load (their rows' length and
 // base even).  Every output's products are added in the order of one accumulator
-// per slice.  Bound by the weights' first read: at 64 rows 512 x 29412 (30 MB) with
+// per slice.  CHAIN: one launch keeps the sums of slices that were not launched,
+// chains of chain k-steps added as k_reduce_epi adds slices; 1: up to eight, in
+// order; 2: sixteen of one or two k-steps, c and c + 8 first.
+// Bound by the weights' first read: at 64 rows 512 x 29412 (30 MB) with
 // its biases takes 13.7 us and 11124 x 512 11.9; the whole forward pass of
 // 11124 -> 3 x 512 -> 29412 takes 42 us, and 83 with conversions, copies and an
 // unpipelined loop.
-template <int DEPTH, bool A32, bool APAIR, bool PAIR>
+template <int DEPTH, bool A32, bool APAIR, bool PAIR, int CHAIN>
 __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av, int lda,
                                                        const uint16_t* __restrict__ B, int ldb,
                                                        float* __restrict__ C, int M, int N, int K,
-                                                       int kslice, int split, EpiArgs ep) {
+                                                       int kslice, int split, int chain,
+                                                       EpiArgs ep) {
   __shared__ alignas(16) uint16_t As[2][kT][kBK + 8];  // [m][k], 16-byte rows of 8 k
   __shared__ alignas(16) uint16_t Bs[2][kT][kBK + 4];  // [n][k] (transposed), 8-byte halves
   const float* __restrict__ Af = static_cast<const float*>(Av);
@@ -599,7 +603,8 @@ __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av
   const int m0 = blockIdx.y * kT, n0 = blockIdx.x * kT;
   const int kb = blockIdx.z * kslice, ke = min(K, kb + kslice);
   const int wm = (wv >> 2) * 32, wn = (wv & 3) * 16;
-  v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+  const v4f zero = v4f{0.f, 0.f, 0.f, 0.f};
+  v4f acc[2] = {zero, zero}, part[2] = {zero, zero}, done[2] = {zero, zero};
   // A: FP32 element by element, BF16 in pairs of k where its rows are even;
   // B: pairs (n, n + 1) of one k
   float rf[DEPTH][kEl];
@@ -655,14 +660,23 @@ __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av
       Bs[buf][n + 1][k] = (uint16_t)(rb[d][q] >> 16);
     }
   };
-  if (kb < ke) {
+  // k of the n-th k-step: in order, or the chains' in pairs c, c + 8; past the last
+  // one nothing but zeros
+  const int steps = CHAIN == 2 ? 16 * chain : (ke - kb + kBK - 1) / kBK;
+  auto at = [&](int n) {
+    if (CHAIN != 2) return kb + n * kBK;
+    const int c = n >> (chain - 1);
+    return n < steps ? (n + ((c & 1) * 8 + (c >> 1) - c) * chain) * kBK : ke;
+  };
+  if (steps > 0) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) load(d, kb + d * kBK);
+    for (int d = 0; d < DEPTH; ++d) load(d, at(d));
   }
-  auto step1 = [&](int d, int buf, int k0) {
-    put(d, buf, ke - k0);
+  int left = chain, c = 0;
+  auto step1 = [&](int d, int buf, int n) {
+    put(d, buf, ke - at(n));
     __syncthreads();
-    load(d, k0 + DEPTH * kBK);
+    load(d, at(n + DEPTH));
     v8bf a[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -676,12 +690,30 @@ __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av
 #pragma unroll
     for (int i = 0; i < 2; ++i)
       acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i], 0, 0, 0);
+    if (CHAIN > 0 && --left == 0) {
+      left = chain;
+      const bool hold = CHAIN == 2 && (c++ & 1) == 0;  // the pair's first
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (CHAIN == 2) {
+          part[i] = hold ? acc[i] : part[i] + acc[i];
+          if (!hold) done[i] += part[i];
+        } else {
+          done[i] += acc[i];
+        }
+        acc[i] = zero;
+      }
+    }
   };
   // whole rounds of DEPTH k-steps, as in the FP32 tile
   int buf = 0;
-  for (int k0 = kb; k0 < ke;) {
+  for (int n = 0; n < steps;) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d, k0 += kBK, buf ^= 1) step1(d, buf, k0);
+    for (int d = 0; d < DEPTH; ++d, ++n, buf ^= 1) step1(d, buf, n);
+  }
+  if (CHAIN > 0) {  // with what is left of a chain that the reduction's end cuts short
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[i] += done[i];
   }
   if (split) {
     float* Cz = C + (size_t)blockIdx.z * M * N;
@@ -929,31 +961,44 @@ hipError_t product(hipStream_t s, int tb, const float* A, int lda, const float* 
   return hipGetLastError();
 }
 
-// A B with BF16 operands (a32: A in FP32)
+// A B with BF16 operands (a32: A in FP32) and the sums of sl slices; whole: in one
+// launch all the same (K <= 1024, BF16 A).
 hipError_t product16(hipStream_t s, const void* A, bool a32, int lda, const uint16_t* B, int M,
-                     int N, int K, int sl, const EpiArgs& ep, const Ws& w) {
-  const int kslice = ((K + sl - 1) / sl + kBK - 1) / kBK * kBK;
+                     int N, int K, int sl, bool whole, const EpiArgs& ep, const Ws& w) {
+  int kslice = ((K + sl - 1) / sl + kBK - 1) / kBK * kBK;
+  const int chain = kslice / kBK, chains = whole ? sl : 1;
+  if (chains > 1) {
+    kslice *= chains;  // the whole reduction
+    sl = 1;
+  }
   const int split = sl > 1;
   const dim3 grid((N + kT - 1) / kT, (M + kT - 1) / kT, sl);
   const bool pair = N % 2 == 0 && (reinterpret_cast<uintptr_t>(B) & 3u) == 0;
   const bool apair = lda % 2 == 0;  // A is the workspace's
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(kGemm), 0, s, A, lda, B, N, w.part, M, N, K, kslice,
-                       split, ep);
+                       split, chain, ep);
   };
-  auto depth = [&](auto d) {
-    constexpr int D = decltype(d)::value;
-    if (a32 && pair) go(k_gemm_bf16<D, true, false, true>);
-    else if (a32) go(k_gemm_bf16<D, true, false, false>);
-    else if (apair && pair) go(k_gemm_bf16<D, false, true, true>);
-    else if (apair) go(k_gemm_bf16<D, false, true, false>);
-    else if (pair) go(k_gemm_bf16<D, false, false, true>);
-    else go(k_gemm_bf16<D, false, false, false>);
+  auto depth = [&](auto d, auto ch) {
+    constexpr int D = decltype(d)::value, C = decltype(ch)::value;
+    if (C == 0 && a32 && pair) go(k_gemm_bf16<D, true, false, true, 0>);
+    else if (C == 0 && a32) go(k_gemm_bf16<D, true, false, false, 0>);
+    else if (apair && pair) go(k_gemm_bf16<D, false, true, true, C>);
+    else if (apair) go(k_gemm_bf16<D, false, true, false, C>);
+    else if (pair) go(k_gemm_bf16<D, false, false, true, C>);
+    else go(k_gemm_bf16<D, false, false, false, C>);
   };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
   const int steps = kslice / kBK;
-  if (steps == 1) depth(std::integral_constant<int, 1>{});
-  else if (steps % 3 == 0) depth(std::integral_constant<int, 3>{});
-  else depth(std::integral_constant<int, 2>{});
+  if (chains > 8) depth(I2{}, I2{});
+  else if (chains > 1 && steps % 3 == 0) depth(I3{}, I1{});
+  else if (chains > 1) depth(I2{}, I1{});
+  else if (steps == 1) depth(I1{}, I0{});
+  else if (steps % 3 == 0) depth(I3{}, I0{});
+  else depth(I2{}, I0{});
   if (split) reduce_epi(s, w, sl, M, N, ep);
   return hipGetLastError();
 }
@@ -1164,8 +1209,8 @@ qg_status qg_mlp_forward_bf16(const qg_mlp_desc* desc, const uint16_t* d_params1
     ep.bias16 = d_params16 + L.b_off[i];
     ep.out16 = w.a16[i & 1];
     const int sl = fit_slices(slices_bf16(B, desc->width, fan_in), B, desc->width, w);
-    e = product16(s, in, i == 0, fan_in, d_params16 + L.w_off[i], B, desc->width, fan_in, sl, ep,
-                  w);
+    e = product16(s, in, i == 0, fan_in, d_params16 + L.w_off[i], B, desc->width, fan_in, sl, false,
+                  ep, w);
     in = w.a16[i & 1];
     fan_in = desc->width;
   }
@@ -1174,12 +1219,11 @@ qg_status qg_mlp_forward_bf16(const qg_mlp_desc* desc, const uint16_t* d_params1
     ep.kind = kBias;
     ep.bias16 = d_params16 + L.b_off[desc->depth];
     ep.out = d_y;
-    // one slice where the output has tiles enough: no second kernel
-    const int sl = tiles_of(B, desc->d_out) >= 64 && fan_in <= 1024
-                       ? 1
-                       : fit_slices(slices_bf16(B, desc->d_out, fan_in), B, desc->d_out, w);
+    // one launch where the output has tiles enough: no second kernel
+    const bool whole = tiles_of(B, desc->d_out) >= 64 && fan_in <= 1024;
+    const int sl = fit_slices(slices_bf16(B, desc->d_out, fan_in), B, desc->d_out, w);
     e = product16(s, in, false, fan_in, d_params16 + L.w_off[desc->depth], B, desc->d_out, fan_in,
-                  sl, ep, w);
+                  sl, whole, ep, w);
   }
   if (e == hipSuccess) e = hipGetLastError();
   return e == hipSuccess ? QG_OK : dev_fail(e, "mlp bf16 forward");

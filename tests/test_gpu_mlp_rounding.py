@@ -1,5 +1,6 @@
-"""Rounding of the network's FP32 sums: no more than 32 terms are added one
-after another before a sum joins others like it."""
+"""Order and rounding of the network's sums: in FP32 no more than 32 terms are added
+one after another before a sum joins others like it; in BF16 an output's sum has
+one order however the product is launched."""
 import math
 
 import numpy as np
@@ -76,3 +77,25 @@ def test_long_batch(qg):
     wo = net.offsets(1)[0]
     bound = 2.0 ** -24 / math.sqrt(3) * math.sqrt(32 / 6144 + 8 / 768 + 8 / 96 + 8 / 12 + 4 / 3)
     assert rms(g[wo:wo + dw_ref.size].reshape(dw_ref.shape), dw_ref) <= 2 * bound
+
+
+@pytest.mark.parametrize("width", [64, 97, 128, 200, 301, 512, 1000])
+def test_bf16_outputs_do_not_depend_on_how_many_there_are(qg, width):
+    """An output's sum has one order whether the output layer takes one launch
+    (64 tiles and more) or slices (fewer), bit for bit: 4,096 outputs and the
+    first 2,048 of them."""
+    import torch
+    wide, params, x, _, xd, _ = make(qg, 8, width, 1, 4096, 50, seed=width)
+    few = qg.MLP(8, width, 1, 2048, max_batch=50)
+    flat = np.zeros(few.n_params, dtype=np.float32)
+    for i, (W, b) in enumerate(params):
+        W, b = (W, b) if i == 0 else (W[:, :2048], b[:2048])
+        wo, bo = few.offsets(i)
+        flat[wo:wo + W.size], flat[bo:bo + b.size] = W.reshape(-1), b
+    few.set_params(flat)
+    for net in (wide, few):
+        net.to_bf16()
+    a = wide.forward_bf16(xd).cpu().numpy()
+    b = few.forward_bf16(xd).cpu().numpy()
+    torch.cuda.synchronize()
+    assert np.array_equal(a[:, :2048], b)
