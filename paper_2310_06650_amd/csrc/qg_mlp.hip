@@ -579,7 +579,7 @@ __global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, i
 
 // BF16 operands (A32: A in FP32, rounded as it is staged), row-major A [M][K]
 // and B [K][N], FP32 sums; pipelined like the FP32 tile with DEPTH k-steps in
-// flight (a slice of one, of a multiple of three, or of another number).
+// flight.
 // APAIR, PAIR: two neighbouring elements of A, B per load (their rows' length and
 // base even).  Every output's products are added in the order of one accumulator
 // per slice.  CHAIN: one launch keeps the sums of slices that were not launched,
@@ -993,11 +993,13 @@ hipError_t product16(hipStream_t s, const void* A, bool a32, int lda, const uint
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
   const int steps = kslice / kBK;
+  // as many k-steps in flight as a slice has, two in longer ones (with three a pass
+  // of 11124 -> 2048 -> 3000 at 2048 rows takes 489 us, with two 456; with two in slices
+  // of three that of 11124 -> 3 x 512 -> 29412 at 64 rows takes 42.5, with three 42.3)
   if (chains > 8) depth(I2{}, I2{});
-  else if (chains > 1 && steps % 3 == 0) depth(I3{}, I1{});
   else if (chains > 1) depth(I2{}, I1{});
   else if (steps == 1) depth(I1{}, I0{});
-  else if (steps % 3 == 0) depth(I3{}, I0{});
+  else if (steps == 3) depth(I3{}, I0{});
   else depth(I2{}, I0{});
   if (split) reduce_epi(s, w, sl, M, N, ep);
   return hipGetLastError();
