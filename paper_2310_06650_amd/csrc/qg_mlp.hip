@@ -737,8 +737,9 @@ __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av
 
 // out = epilogue(sum over slices of P[s][m][n]) for an M x N matrix (ld N).
 // The slices of 32 elements are summed by 8 groups of threads (group g takes
-// slices g, g + 8, ..., eight loads in flight), the group sums then added in
+// slices g, g + 8, ..., U loads in flight), the group sums then added in
 // group order: a fixed order.
+template <int U>
 __global__ __launch_bounds__(kThreads) void k_reduce_epi(const float* __restrict__ P, int slices,
                                                          int M, int N, EpiArgs ep) {
   __shared__ float red[8][33];
@@ -749,12 +750,12 @@ __global__ __launch_bounds__(kThreads) void k_reduce_epi(const float* __restrict
     Aux x{0.f, 0.f};
     if (g == 0) x = epi_aux(ep, ec, (int)(ec % N));
     float part = 0.f;
-    for (int q0 = g; q0 < slices; q0 += 64) {
-      float v[8];
+    for (int q0 = g; q0 < slices; q0 += 8 * U) {
+      float v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = P[(size_t)min(q0 + 8 * u, slices - 1) * MN + ec];
+      for (int u = 0; u < U; ++u) v[u] = P[(size_t)min(q0 + 8 * u, slices - 1) * MN + ec];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < U; ++u)
         if (q0 + 8 * u < slices) part += v[u];
     }
     red[g][c] = part;
@@ -922,10 +923,18 @@ int blocks_of(const Plan& p, int M, int N) {
   return ((M + 16 * p.mi - 1) / (16 * p.mi)) * ((N + kT - 1) / kT);
 }
 
-// The slices' sums of an M x N product in w.part through the epilogue.
+// The slices' sums of an M x N product in w.part through the epilogue, with the
+// loads that a group has: eight for eight slices (seven of them for nothing) took 27 us
+// where one takes 14 (300 x 2048).
 void reduce_epi(hipStream_t s, const Ws& w, int slices, int M, int N, const EpiArgs& ep) {
-  hipLaunchKernelGGL(k_reduce_epi, dim3(grid_red((size_t)M * N)), dim3(kThreads), 0, s, w.part,
-                     slices, M, N, ep);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid_red((size_t)M * N)), dim3(kThreads), 0, s, w.part, slices,
+                       M, N, ep);
+  };
+  if (slices <= 8) go(k_reduce_epi<1>);
+  else if (slices <= 16) go(k_reduce_epi<2>);
+  else if (slices <= 32) go(k_reduce_epi<4>);
+  else go(k_reduce_epi<8>);
 }
 
 // A op(B) with epilogue as planned; slices go through ws.part
