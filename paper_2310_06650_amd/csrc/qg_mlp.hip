@@ -106,23 +106,61 @@ __device__ __forceinline__ float block_tree(float v, float* red) {
   return red[0];
 }
 
-// Raw buffer view of the bytes of a matrix from base on: the address of a load
-// is base + the lane's 32-bit offset, and loads at or past the end return 0.
-// The view of an operand moves with the k-step, so that the lanes' offsets are
-// the same in every step and the loop needs no address arithmetic.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t view(const void* base, int64_t bytes) {
-  const int hi = (int)(bytes >> 32);
-  const uint32_t n = hi < 0 ? 0u : hi > 0 ? 0xFFFFFFFFu : (uint32_t)bytes;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, 0x00020000);
-}
+// The bytes of a matrix from base on; loads at or past the end return 0.  As a raw
+// buffer the address of a load is base + the lane's 32-bit offset; the view of an
+// operand moves with the k-step, so that the lanes' offsets are the same in every step
+// and the loop needs no address arithmetic.  FAR: for tiles whose rows span more
+// than the 4 GiB of such an offset (rows_far), with 64-bit offsets.
+template <bool FAR>
+struct View {
+  typedef unsigned Off;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ View(const void* base, int64_t bytes) {
+    const int hi = (int)(bytes >> 32);
+    const uint32_t n = hi < 0 ? 0u : hi > 0 ? 0xFFFFFFFFu : (uint32_t)bytes;
+    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, 0x00020000);
+  }
+  __device__ __forceinline__ float f32(Off o) const {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0));
+  }
+  __device__ __forceinline__ v4f f32x4(Off o) const {
+    return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0));
+  }
+  __device__ __forceinline__ unsigned u32(Off o) const {
+    return __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0);
+  }
+  __device__ __forceinline__ unsigned u16(Off o) const {
+    return __builtin_amdgcn_raw_buffer_load_b16(r, o, 0, 0);
+  }
+};
+template <>
+struct View<true> {
+  typedef uint64_t Off;
+  const char* base;
+  int64_t bytes;
+  __device__ __forceinline__ View(const void* b, int64_t n)
+      : base(static_cast<const char*>(b)), bytes(n) {}
+  template <typename T>
+  __device__ __forceinline__ T get(Off o) const {
+    return (int64_t)(o + sizeof(T)) <= bytes ? *reinterpret_cast<const T*>(base + o) : T(0);
+  }
+  __device__ __forceinline__ float f32(Off o) const { return get<float>(o); }
+  __device__ __forceinline__ v4f f32x4(Off o) const {
+    return v4f{f32(o), f32(o + 4), f32(o + 8), f32(o + 12)};
+  }
+  __device__ __forceinline__ unsigned u32(Off o) const { return get<unsigned>(o); }
+  __device__ __forceinline__ unsigned u16(Off o) const { return get<uint16_t>(o); }
+};
 // View of the k-step at k0 of an operand X[r][k] (rows of ld elements, r from
 // r0 of R, k contiguous) or X[k][r] (k < ke; ROWK).
-template <bool ROWK, typename T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand(const T* X, int ld, int R, int r0, int k0,
-                                                          int ke) {
+template <bool ROWK, bool FAR, typename T>
+__device__ __forceinline__ View<FAR> operand(const T* X, int ld, int R, int r0, int k0, int ke) {
   const int64_t at = ROWK ? (int64_t)k0 * ld + r0 : (int64_t)r0 * ld + k0;
-  return view(X + at, ((ROWK ? (int64_t)ke * ld : (int64_t)R * ld) - at) * (int64_t)sizeof(T));
+  return View<FAR>(X + at, ((ROWK ? (int64_t)ke * ld : (int64_t)R * ld) - at) * (int64_t)sizeof(T));
 }
+// Whether a tile of rows rows of ld elements of 4 bytes (less is on the safe side)
+// has offsets past 32 bits.
+inline bool rows_far(int rows, int ld) { return (int64_t)rows * ld > (int64_t)1 << 30; }
 
 // FP32 tile product with the reduction over the operands' rows: acc = the
 // 64 x 64 tile at (m0, n0) of A^T B, A [K][M] and B [K][N], over the range [kb, ke).
@@ -144,18 +182,17 @@ struct alignas(16) TileLds {
   float b[2][kT][kPitch];  // [n][k]
 };
 
+template <bool FAR>
 struct Tile {
+  typedef typename View<FAR>::Off Off;
   float ra[kDepth][kEl], rb[kDepth][kEl];
-  unsigned oa[kEl], ob[kEl];  // byte offsets in the operands' views
+  Off oa[kEl], ob[kEl];  // byte offsets in the operands' views
   // element e of a k-step's operand: row (or column) e % 64, k = e / 64
-  __device__ __forceinline__ void load(int d, __amdgpu_buffer_rsrc_t va,
-                                       __amdgpu_buffer_rsrc_t vb) {
+  __device__ __forceinline__ void load(int d, const View<FAR>& va, const View<FAR>& vb) {
 #pragma unroll
-    for (int q = 0; q < kEl; ++q)
-      ra[d][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(va, oa[q], 0, 0));
+    for (int q = 0; q < kEl; ++q) ra[d][q] = va.f32(oa[q]);
 #pragma unroll
-    for (int q = 0; q < kEl; ++q)
-      rb[d][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vb, ob[q], 0, 0));
+    for (int q = 0; q < kEl; ++q) rb[d][q] = vb.f32(ob[q]);
   }
   __device__ __forceinline__ void put(int d, TileLds& s, int buf) {
 #pragma unroll
@@ -179,11 +216,11 @@ struct Tile {
 #pragma unroll
     for (int q = 0; q < kEl; ++q) {
       const int e = threadIdx.x + q * kGemm;
-      oa[q] = ((unsigned)(e >> 6) * lda + (e & 63)) * 4u;
-      ob[q] = ((unsigned)(e >> 6) * ldb + (e & 63)) * 4u;
+      oa[q] = ((Off)(e >> 6) * lda + (e & 63)) * 4u;
+      ob[q] = ((Off)(e >> 6) * ldb + (e & 63)) * 4u;
     }
     auto fetch = [&](int d, int k0) {
-      load(d, operand<true>(A, lda, M, m0, k0, ke), operand<true>(B, ldb, N, n0, k0, ke));
+      load(d, operand<true, FAR>(A, lda, M, m0, k0, ke), operand<true, FAR>(B, ldb, N, n0, k0, ke));
     };
 #pragma unroll
     for (int d = 0; d < kDepth; ++d) fetch(d, kb + d * kBK);
@@ -270,7 +307,7 @@ constexpr int kStep = 16;
 constexpr int kChain = 2;
 constexpr int waves_of(int mi) { return mi == 1 ? 8 : 4; }
 constexpr int kCPitch = kT + 4;
-template <int DEPTH, int MI, int TB>
+template <int DEPTH, int MI, int TB, bool FAR>
 __global__ __launch_bounds__(waves_of(MI) * 64) void k_product(const float* __restrict__ A, int lda,
                                                          const float* __restrict__ B, int ldb,
                                                          float* __restrict__ C, int M, int N, int K,
@@ -288,22 +325,20 @@ __global__ __launch_bounds__(waves_of(MI) * 64) void k_product(const float* __re
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = done[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
   v4f a[DEPTH][MI], b[DEPTH][4];
-  unsigned oa[MI], ob[4];  // byte offsets in the operands' views
+  typedef typename View<FAR>::Off Off;
+  Off oa[MI], ob[4];  // byte offsets in the operands' views
 #pragma unroll
-  for (int i = 0; i < MI; ++i) oa[i] = ((unsigned)(16 * i + r) * lda + 4 * kq) * 4u;
+  for (int i = 0; i < MI; ++i) oa[i] = ((Off)(16 * i + r) * lda + 4 * kq) * 4u;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    ob[j] =
-        (TB ? (unsigned)(16 * j + r) * ldb + 4 * kq : (unsigned)(4 * kq + j) * ldb + 4 * r) * 4u;
+    ob[j] = (TB ? (Off)(16 * j + r) * ldb + 4 * kq : (Off)(4 * kq + j) * ldb + 4 * r) * 4u;
   auto fetch = [&](int d, int k0) {
-    const __amdgpu_buffer_rsrc_t va = operand<false>(A, lda, M, m0, k0, ke);
-    const __amdgpu_buffer_rsrc_t vb = operand<TB == 0>(B, ldb, N, n0, k0, ke);
+    const View<FAR> va = operand<false, FAR>(A, lda, M, m0, k0, ke);
+    const View<FAR> vb = operand<TB == 0, FAR>(B, ldb, N, n0, k0, ke);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      b[d][j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(vb, ob[j], 0, 0));
+    for (int j = 0; j < 4; ++j) b[d][j] = vb.f32x4(ob[j]);
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-      a[d][i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(va, oa[i], 0, 0));
+    for (int i = 0; i < MI; ++i) a[d][i] = va.f32x4(oa[i]);
   };
   int k0 = kb + wv * kStep;
 #pragma unroll
@@ -468,7 +503,7 @@ struct DwArgs {
   float* loss;
 };
 
-template <bool ADAM, int kLevels>
+template <bool ADAM, int kLevels, bool FAR>
 __global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, int fan_in,
                                                  const float* __restrict__ dZ, int n_out, int batch,
                                                  DwArgs w) {
@@ -494,19 +529,20 @@ __global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, i
   float p[R], m[R], v[R];
   auto params = [&]() {
     if constexpr (ADAM) {
-      const auto vp = operand<true>(w.pw, n_out, n_out, n0, m0, fan_in);
-      const auto vm = operand<true>(w.mw, n_out, n_out, n0, m0, fan_in);
-      const auto vv = operand<true>(w.vw, n_out, n_out, n0, m0, fan_in);
+      const auto vp = operand<true, FAR>(w.pw, n_out, n_out, n0, m0, fan_in);
+      const auto vm = operand<true, FAR>(w.mw, n_out, n_out, n0, m0, fan_in);
+      const auto vv = operand<true, FAR>(w.vw, n_out, n_out, n0, m0, fan_in);
 #pragma unroll
       for (int i = 0; i < R; ++i) {
-        const unsigned o = ((unsigned)(q8 + 8 * i) * n_out + c) * 4u;
-        p[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vp, o, 0, 0));
-        m[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vm, o, 0, 0));
-        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vv, o, 0, 0));
+        const typename View<FAR>::Off o =
+            ((typename View<FAR>::Off)(q8 + 8 * i) * n_out + c) * 4u;
+        p[i] = vp.f32(o);
+        m[i] = vm.f32(o);
+        v[i] = vv.f32(o);
       }
     }
   };
-  Tile tile;
+  Tile<FAR> tile;
   v4f acc[2], sum[kLevels][2];
 #pragma unroll
   for (int j = 0; j < kLevels; ++j)
@@ -589,7 +625,7 @@ __global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, i
 // its biases takes 13.7 us and 11124 x 512 11.9; the whole forward pass of
 // 11124 -> 3 x 512 -> 29412 takes 42 us, and 83 with conversions, copies and an
 // unpipelined loop.
-template <int DEPTH, bool A32, bool APAIR, bool PAIR, int CHAIN>
+template <int DEPTH, bool A32, bool APAIR, bool PAIR, int CHAIN, bool FAR>
 __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av, int lda,
                                                        const uint16_t* __restrict__ B, int ldb,
                                                        float* __restrict__ C, int M, int N, int K,
@@ -609,31 +645,28 @@ __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av
   // B: pairs (n, n + 1) of one k
   float rf[DEPTH][kEl];
   unsigned ra[DEPTH][kEl / 2], rb[DEPTH][kEl / 2];
-  unsigned oa[kEl], ob[kEl / 2];
+  typedef typename View<FAR>::Off Off;
+  Off oa[kEl], ob[kEl / 2];
 #pragma unroll
   for (int q = 0; q < kEl; ++q) {
     const int e = tid + q * kGemm;
-    oa[q] = A32 ? ((unsigned)(e >> 5) * lda + (e & 31)) * 4u
-                : ((unsigned)(e >> 4) * lda + 2 * (e & 15)) * 2u;
-    if (q < kEl / 2) ob[q] = ((unsigned)(e >> 5) * ldb + 2 * (e & 31)) * 2u;
+    oa[q] = A32 ? ((Off)(e >> 5) * lda + (e & 31)) * 4u : ((Off)(e >> 4) * lda + 2 * (e & 15)) * 2u;
+    if (q < kEl / 2) ob[q] = ((Off)(e >> 5) * ldb + 2 * (e & 31)) * 2u;
   }
-  auto pair = [](__amdgpu_buffer_rsrc_t v, unsigned o, bool whole) -> unsigned {
-    if (whole) return __builtin_amdgcn_raw_buffer_load_b32(v, o, 0, 0);
-    return (unsigned)__builtin_amdgcn_raw_buffer_load_b16(v, o, 0, 0) |
-           (unsigned)__builtin_amdgcn_raw_buffer_load_b16(v, o + 2, 0, 0) << 16;
+  auto pair = [](const View<FAR>& v, Off o, bool whole) -> unsigned {
+    return whole ? v.u32(o) : v.u16(o) | v.u16(o + 2) << 16;
   };
   auto load = [&](int d, int k0) {
     if constexpr (A32) {
-      const __amdgpu_buffer_rsrc_t va = operand<false>(Af, lda, M, m0, k0, ke);
+      const View<FAR> va = operand<false, FAR>(Af, lda, M, m0, k0, ke);
 #pragma unroll
-      for (int q = 0; q < kEl; ++q)
-        rf[d][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(va, oa[q], 0, 0));
+      for (int q = 0; q < kEl; ++q) rf[d][q] = va.f32(oa[q]);
     } else {
-      const __amdgpu_buffer_rsrc_t va = operand<false>(Ah, lda, M, m0, k0, ke);
+      const View<FAR> va = operand<false, FAR>(Ah, lda, M, m0, k0, ke);
 #pragma unroll
       for (int q = 0; q < kEl / 2; ++q) ra[d][q] = pair(va, oa[q], APAIR);
     }
-    const __amdgpu_buffer_rsrc_t vb = operand<true>(B, ldb, N, n0, k0, ke);
+    const View<FAR> vb = operand<true, FAR>(B, ldb, N, n0, k0, ke);
 #pragma unroll
     for (int q = 0; q < kEl / 2; ++q) rb[d][q] = pair(vb, ob[q], PAIR);
   };
@@ -913,11 +946,15 @@ int fit_slices(int sl, int M, int N, const Ws& w) {
 // with 128.
 struct Plan {
   int mi, sl;
+  bool far;
 };
 Plan plan_f32(int tb, int M, int N, int K, const Ws& w) {
+  // A has rows of K; op(B) is read in 64 rows of K or 16 of N
+  if (rows_far(kT, K) || (!tb && rows_far(kStep, N)))
+    return {4, fit_slices(slices_f32(M, N, K), M, N, w), true};
   const int64_t t16 = (int64_t)((M + 15) / 16) * ((N + kT - 1) / kT);
-  if (K <= (tb ? 256 : 1024) && t16 <= kOneSlice) return {1, 1};
-  return {M <= 16 ? 1 : M <= 32 ? 2 : 4, fit_slices(slices_f32(M, N, K), M, N, w)};
+  if (K <= (tb ? 256 : 1024) && t16 <= kOneSlice) return {1, 1, false};
+  return {M <= 16 ? 1 : M <= 32 ? 2 : 4, fit_slices(slices_f32(M, N, K), M, N, w), false};
 }
 int blocks_of(const Plan& p, int M, int N) {
   return ((M + 16 * p.mi - 1) / (16 * p.mi)) * ((N + kT - 1) / kT);
@@ -952,16 +989,18 @@ hipError_t product(hipStream_t s, int tb, const float* A, int lda, const float* 
   auto rows = [&](auto t) {
     constexpr int T = decltype(t)::value;
     const int steps = kslice / kRound;  // of a wavefront
-    if (p.mi == 1) {
-      if (steps == 1) go(k_product<1, 1, T>);
-      else if (steps == 2) go(k_product<2, 1, T>);
-      else go(k_product<4, 1, T>);
+    if (p.far) {
+      go(k_product<2, 4, T, true>);
+    } else if (p.mi == 1) {
+      if (steps == 1) go(k_product<1, 1, T, false>);
+      else if (steps == 2) go(k_product<2, 1, T, false>);
+      else go(k_product<4, 1, T, false>);
     } else if (p.mi == 2) {
-      if (steps == 1) go(k_product<1, 2, T>);
-      else go(k_product<2, 2, T>);
+      if (steps == 1) go(k_product<1, 2, T, false>);
+      else go(k_product<2, 2, T, false>);
     } else {
-      if (steps == 1) go(k_product<1, 4, T>);
-      else go(k_product<2, 4, T>);
+      if (steps == 1) go(k_product<1, 4, T, false>);
+      else go(k_product<2, 4, T, false>);
     }
   };
   if (tb) rows(std::integral_constant<int, 1>{});
@@ -990,12 +1029,12 @@ hipError_t product16(hipStream_t s, const void* A, bool a32, int lda, const uint
   };
   auto depth = [&](auto d, auto ch) {
     constexpr int D = decltype(d)::value, C = decltype(ch)::value;
-    if (C == 0 && a32 && pair) go(k_gemm_bf16<D, true, false, true, 0>);
-    else if (C == 0 && a32) go(k_gemm_bf16<D, true, false, false, 0>);
-    else if (apair && pair) go(k_gemm_bf16<D, false, true, true, C>);
-    else if (apair) go(k_gemm_bf16<D, false, true, false, C>);
-    else if (pair) go(k_gemm_bf16<D, false, false, true, C>);
-    else go(k_gemm_bf16<D, false, false, false, C>);
+    if (C == 0 && a32 && pair) go(k_gemm_bf16<D, true, false, true, 0, false>);
+    else if (C == 0 && a32) go(k_gemm_bf16<D, true, false, false, 0, false>);
+    else if (apair && pair) go(k_gemm_bf16<D, false, true, true, C, false>);
+    else if (apair) go(k_gemm_bf16<D, false, true, false, C, false>);
+    else if (pair) go(k_gemm_bf16<D, false, false, true, C, false>);
+    else go(k_gemm_bf16<D, false, false, false, C, false>);
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -1005,7 +1044,12 @@ hipError_t product16(hipStream_t s, const void* A, bool a32, int lda, const uint
   // as many k-steps in flight as a slice has, two in longer ones (with three a pass
   // of 11124 -> 2048 -> 3000 at 2048 rows takes 489 us, with two 456; with two in slices
   // of three that of 11124 -> 3 x 512 -> 29412 at 64 rows takes 42.5, with three 42.3)
-  if (chains > 8) depth(I2{}, I2{});
+  if (rows_far(kT, K) || rows_far(kBK, N)) {
+    if (chains > 8) go(k_gemm_bf16<2, false, false, false, 2, true>);
+    else if (chains > 1) go(k_gemm_bf16<2, false, false, false, 1, true>);
+    else if (a32) go(k_gemm_bf16<2, true, false, false, 0, true>);
+    else go(k_gemm_bf16<2, false, false, false, 0, true>);
+  } else if (chains > 8) depth(I2{}, I2{});
   else if (chains > 1) depth(I2{}, I1{});
   else if (steps == 1) depth(I1{}, I0{});
   else if (steps == 3) depth(I3{}, I0{});
@@ -1116,10 +1160,13 @@ hipError_t grad_step(hipStream_t s, const qg_mlp_desc* d, const qg_mlp_layout& L
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, grid, dim3(kGemm), 0, s, in, fan_in, dcur, n_out, B, a);
     };
-    if (u && B <= kDwShort) go(k_dw<true, 1>);
-    else if (u) go(k_dw<true, kDwLevels>);
-    else if (B <= kDwShort) go(k_dw<false, 1>);
-    else go(k_dw<false, kDwLevels>);
+    const bool far = rows_far(kBK, fan_in) || rows_far(kT, n_out);
+    if (u && far) go(k_dw<true, kDwLevels, true>);
+    else if (far) go(k_dw<false, kDwLevels, true>);
+    else if (u && B <= kDwShort) go(k_dw<true, 1, false>);
+    else if (u) go(k_dw<true, kDwLevels, false>);
+    else if (B <= kDwShort) go(k_dw<false, 1, false>);
+    else go(k_dw<false, kDwLevels, false>);
     dcur = dst;
     n_out = W;
   }
