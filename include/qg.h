@@ -383,11 +383,12 @@ qg_status qg_set_ctg_tile(qg_problem* prob, int32_t bl, int32_t wl, int32_t tc);
  * Branch tiles (of wl * bl branches; of 8 branches for a period-split tile)
  * that one block of the contingency map-reduce covers (a wavefront of one,
  * for a period-split tile), lt in [1, 64] (at least 2 for a period-split
- * tile), or 0 for the default (doubling from 1, or 2, while at least 2048
- * blocks remain, at most 8; a period-split tile at its default takes as many
- * wavefronts per block as keep every block resident).  More tiles spread the
- * fixed costs; fewer leave more blocks or wavefronts.  qg_set_ctg_tile resets it to the
- * default; qg_set_ctg_tile_split sets it (0: the default).
+ * tile), or 0 for the library's choice: doubling from 1 while at least 2048
+ * blocks remain, at most 8; for a period-split tile as many wavefronts per
+ * block as keep every block resident, whatever number qg_problem_dims then
+ * reports.  More tiles spread the fixed costs; fewer leave more blocks or
+ * wavefronts.  qg_set_ctg_tile resets it to the library's choice;
+ * qg_set_ctg_tile_split sets it.
  * Results depend on it only through the order of floating-point sums.  A
  * step graph cached by qg_solve is re-captured after a change.  Errors: ARG.
  */
@@ -397,10 +398,10 @@ qg_status qg_set_ctg_ltiles(qg_problem* prob, int32_t lt);
  * Period-split tile of the contingency map-reduce (the default form): a
  * block covers one period and 64 contingencies over every branch, its
  * wavefronts split the branches in slices of at least lt tiles of 8 (lt in
- * [2, 64], or 0 for the default of qg_set_ctg_ltiles; whole 64-branch groups,
- * at most 16 slices).  wl (1..8) and tcw (1..8) describe a period chunk of wl *
- * tcw periods and enter the default lt and the tile a batched solve asks for;
- * they do not change the results.
+ * [2, 64], or 0 for the library's choice; whole 64-branch groups, at most 16
+ * slices).  wl (1..8) and tcw (1..8) name a period chunk of wl * tcw periods:
+ * they enter the lt that qg_problem_dims reports for the library's choice and
+ * the tile a batched solve asks for, and change neither launch nor results.
  * Results depend on the tile only through the order of floating-point sums.
  * qg_set_ctg_tile returns to the branch-stacked form.  A step graph cached by
  * qg_solve is re-captured after a change.  Errors: ARG.

@@ -1,10 +1,11 @@
 """Tile autotuner of the contingency map-reduce.
 
-The tile (period-split: wavefronts per block, periods per wavefront, branch
-tiles per block; branch-stacked: branches per wavefront, wavefronts per
+The tile (period-split: branch tiles per slice, that is how many wavefronts
+share a block's branches; branch-stacked: branches per wavefront, wavefronts per
 block, periods per block, branch tiles per block) trades the re-reads of the
 outage factors, the partial sums and the per-block fixed costs against the
-number of blocks in flight; the best choice depends on the grid's shape.
+number of blocks and wavefronts in flight; the best choice depends on the grid's
+shape.
 Tiles are named by their text form (``Problem.tile``).  ``tune`` times, for
 each candidate, a short graph-replayed solve from a copy of the given point
 (the whole step: the tile also changes how much the reductions after the
@@ -21,13 +22,14 @@ import os
 
 from . import qg
 
-# text forms; a missing lt: the library's default for the rest of the tile
-CANDIDATES = ["s4x2", "s4x4", "s2x2", "s3x2", "s8x2", "s4x3", "s4x6", "s8x6", "s4x4x16",
-              "s4x2x4", "s1x4", "s1x4x8", "s1x4x12", "s2x4x8", "s3x4x8", "s4x2x16",
+# text forms; a missing lt: the library's choice.  Of a period-split tile only lt
+# changes the launch: the library's own slices, or 1, 2 or 4 groups of 64 branches
+# a slice (7, not 8: no default is reported as 7)
+CANDIDATES = ["s4x4", "s4x4x7", "s4x4x16", "s4x4x32",
               "8x8x4", "8x4x4", "8x8x7", "16x4x4", "8x8x4x1", "8x8x7x4", "8x4x8x8"]
-# the tiles a batched solve takes (4 wavefronts of 4 periods; branch tiles
-# per slice free), timed through the batched path
-BATCH_CANDIDATES = ["s4x4x8", "s4x4x16", "s4x4x32"]
+# the tiles a batched solve takes, timed through the batched path
+BATCH_CANDIDATES = ["s4x4", "s4x4x7", "s4x4x16", "s4x4x32"]
+CACHE_VERSION = 2  # of what a tile's text means
 
 
 def cache_path():
@@ -90,10 +92,11 @@ def tune(prob, x, reps=30, eps=1e-2, candidates=None, use_cache=True, measure="s
         candidates = BATCH_CANDIDATES
     cache = _load() if use_cache else {}
     hit = cache.get(key)
-    if use_cache and hit and isinstance(hit.get("tile"), str) and hit.get("measure") == measure:
-        prob.set_tile(hit["tile"])
+    if (use_cache and hit and hit.get("version") == CACHE_VERSION
+            and isinstance(hit.get("tile"), str) and hit.get("measure") == measure):
+        prob.set_tile(hit["given"])
         return hit["tile"], hit["times"]
-    times = {}
+    times, given = {}, {}  # by the tile in full; the candidate that gave it
     for cand in (candidates or CANDIDATES):
         try:
             prob.set_tile(cand)
@@ -104,9 +107,11 @@ def tune(prob, x, reps=30, eps=1e-2, candidates=None, use_cache=True, measure="s
         else:
             us = sum(prob.time_stage(x, s, reps, eps) for s in (1, 2, 3))
         times[prob.tile()] = us
+        given[prob.tile()] = cand
     tile = min(times, key=times.get)
-    prob.set_tile(tile)
+    prob.set_tile(given[tile])
     if use_cache:
-        cache[key] = dict(tile=tile, times=times, measure=measure)
+        cache[key] = dict(version=CACHE_VERSION, tile=tile, given=given[tile], times=times,
+                          measure=measure)
         _save(cache)
     return tile, times

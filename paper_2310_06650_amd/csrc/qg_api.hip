@@ -430,6 +430,7 @@ qg_status qg_set_ctg_tile_split(qg_problem* pr, int32_t wl, int32_t tcw, int32_t
     return fail(QG_ERR_ARG, "split tile needs wl in [1, 8], tcw in [1, 8], lt 0 or in [2, 64]");
   qg::CtgTile t{8, wl, tcw, lt};
   t.split = 1;
+  t.lt_auto = lt == 0;
   if (lt == 0) t.lt = qg::default_ctg_lt(pr->p, t);
   qg::apply_ctg_tile(&pr->p, t);
   return QG_OK;
@@ -442,6 +443,7 @@ qg_status qg_set_ctg_ltiles(qg_problem* pr, int32_t lt) {
   qg::Problem& p = pr->p;
   qg::CtgTile t = p.tile;
   if (t.split && lt == 1) return fail(QG_ERR_ARG, "a period-split tile needs lt >= 2");
+  t.lt_auto = lt == 0;
   t.lt = lt > 0 ? lt : qg::default_ctg_lt(p, t);
   qg::apply_ctg_tile(&p, t);
   return QG_OK;
@@ -752,7 +754,7 @@ qg_status qg_solve(qg_problem* pr, double* d_x, double* d_m, double* d_v,
     // and so is the contingency tile (grid and LDS size of the map-reduce)
     const qg::CtgTile& gt = pr->p.graph_tile;
     if (hit && (gt.bl != p.tile.bl || gt.wl != p.tile.wl || gt.tc != p.tile.tc ||
-                gt.lt != p.tile.lt || gt.split != p.tile.split))
+                gt.lt != p.tile.lt || gt.lt_auto != p.tile.lt_auto || gt.split != p.tile.split))
       hit = false;
     if (!hit) {
       drop_graph(pr->p);

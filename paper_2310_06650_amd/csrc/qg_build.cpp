@@ -222,15 +222,12 @@ int default_ctg_lt(const Problem& p, const CtgTile& t) {
 }
 
 CtgTile default_ctg_tile(const Problem& p) {
-  // period-split blocks: below 32 periods four, three or two wavefronts of
-  // two periods, whichever leaves the fewest padded periods in the last
-  // period chunk (ties to more wavefronts); from 32 periods one wavefront
-  // of four.  Branch tiles per block by the rule of default_ctg_lt.
-  // Measured as whole graph-replayed steps: against the best branch-stacked
-  // tile 4.8 % faster at 18 periods, 1.6x at 48; at 18 periods (617 buses)
-  // three wavefronts run 31.1k steps/s against 30.8k for four (whose last
-  // chunk holds 2 of 8 periods); at 48 periods (2000 buses) one wavefront
-  // runs 10.15k against 9.99k for two and 9.72k for four.
+  // period-split blocks, slices by ctg_slices.  wl and tc do not reach the
+  // kernel: they name the tile (a batched solve asks for 4 x 4) and enter the
+  // reported default lt.  Below 32 periods they are four, three or two
+  // wavefronts of two periods, whichever leaves the fewest padded periods in the
+  // last period chunk (ties to more wavefronts); from 32 periods one wavefront
+  // of four.
   int wl = 1, tc = 4;
   if (p.T < 32) {
     tc = 2;
@@ -244,7 +241,7 @@ CtgTile default_ctg_tile(const Problem& p) {
     }
   }
   CtgTile t{8, wl, tc, 2};
-  t.split = 1;
+  t.split = t.lt_auto = 1;
   t.lt = default_ctg_lt(p, t);
   return t;
 }
@@ -259,7 +256,7 @@ int ctg_slices(const Problem& p, int nkb) {
   if (!p.tile.split) return 0;
   const int ng = p.Lp / 64;
   int most;  // 64-branch groups of a slice
-  if (p.tile.lt != default_ctg_lt(p, p.tile)) {
+  if (!p.tile.lt_auto) {
     most = (p.tile.lt + 7) / 8;
   } else {
     // the most wavefronts per block with which every block is resident at

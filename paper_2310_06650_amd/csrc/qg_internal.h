@@ -169,6 +169,7 @@ struct CtgTile {
   int lt;   // consecutive tiles of wl * bl branches per block (split: of 8
             // branches per wavefront, see ctg_slices)
   int split = 0;  // 1: period-split blocks, one period each (k_ctg_rows)
+  int lt_auto = 0;  // 1: lt is the default, not the caller's
 };
 
 // Homotopy source of one evaluation.

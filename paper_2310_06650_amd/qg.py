@@ -421,7 +421,8 @@ class Problem:
 
     def set_tile(self, text):
         """Set a tile given in the text form of tile(); lt may be left out or
-        0 (the default)."""
+        0 (the library's choice, of which tile() shows the number: given
+        back, that number is the caller's)."""
         if text.startswith("s"):
             v = [int(u) for u in text[1:].split("x")]
             self.set_ctg_tile_split(v[0], v[1], v[2] if len(v) > 2 else 0)

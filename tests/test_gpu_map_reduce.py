@@ -63,3 +63,23 @@ def test_edges_match_oracle_with_and_without_skip(qg, shape, prec, tol):
         t, g = evaluate(prob, x)
         prob.close()
         close(c, qg, t, g, ob.evaluate(m, x, 1e-2, 0.9, 0.8, active=A), tol)
+
+
+def test_split_tile_names_change_nothing(qg):
+    """Wavefronts and periods of a period-split tile name it; the launch follows
+    from lt alone, whether given or left to the library: bitwise equal results of
+    a grid for which eight tiles are the default of one name and not of another."""
+    c = synth.make_case(seed=3, n_bus=2000, n_branch=2800, n_gen=300, n_period=48, n_ctg=None,
+                        tree="prufer", mesh=3.0)
+    x = synth.random_point(c, 17, spread=0.05)
+    prob = qg.Problem(c)
+    for lt in ("", "x8"):
+        got = []
+        for name in ("s4x4", "s8x8", "s1x4"):
+            prob.set_tile(name + lt)
+            got.append((prob.dims["ctg_lt"],) + evaluate(prob, x))
+        if lt == "":
+            assert len({g[0] for g in got}) > 1  # the defaults do differ
+        for g in got[1:]:
+            assert np.array_equal(got[0][1], g[1]) and np.array_equal(got[0][2], g[2]), lt
+    prob.close()
