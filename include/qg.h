@@ -99,7 +99,8 @@ enum { QG_CTG_ALL_NONBRIDGE = 0, QG_CTG_LIST = 1 };
  * test radius, the factors' maximum taken as stored (FP64, FP32 or BF16) and
  * with margins that cover the rounding of the exact test of that precision,
  * so the results are bitwise those of testing every element.  With this flag
- * every element is tested (a reference for that claim). */
+ * every element is tested (a reference for that claim), by a kernel launched
+ * before the map-reduce. */
 #define QG_FLAG_CTG_NO_SKIP 0x10u
 
 /* Grid description: host arrays, all FP64 per unit (100 MVA base) unless
@@ -192,7 +193,8 @@ typedef struct {
   double terms[QG_NTERMS];   /* score-point terms at the end */
   /* mean duration per launch when profile = 1, in stream order: k_forward,
    * k_ctg_main, k_ctg_zred, k_ctg_asm, k_adjoint, k_final (slots 6, 7 unused);
-   * under a period-split tile k_ctg_rows runs in k_ctg_main's place and does
+   * under a period-split tile k_ctg_rows runs in k_ctg_main's place (after
+   * k_ctg_test with QG_FLAG_CTG_NO_SKIP, in the same slot) and does
    * k_ctg_zred's work, whose slot then shows only the events' distance; grids
    * of up to 768 branches run k_update, shown in k_final's slot, for k_adjoint
    * and k_final */
@@ -327,7 +329,8 @@ qg_status qg_solve(qg_problem* prob, double* d_x, double* d_m, double* d_v,
  * Batched solve of independent scenarios (problems built separately, of any
  * sizes; the scenario batching of the many-problem workload): the same
  * schedule and Adam constants for all, n_steps steps each.  A step is five
- * launches for the whole batch, one per kernel of the single-problem step
+ * launches for the whole batch, one per kernel of the single-problem step (and
+ * k_ctg_test, if a problem has QG_FLAG_CTG_NO_SKIP)
  * (Section II-C to II-G; Alg. 3), each covering every scenario's blocks;
  * the contingency map-reduce (eqs. (rank_correct), (sfr_pen)-(zctg)) finishes
  * the penalties too.  Steps are replayed from one HIP graph per 16 steps.  Every scenario gets the

@@ -331,6 +331,7 @@ struct BatchPlan {
   size_t bytes = 0;            // size of the batch buffer
   int lodf_kind = 0;
   int nsl = 0;                 // most branch slices of a problem (map-reduce LDS)
+  bool test_wide = false;      // form of k_ctg_test
   int row_waves = 0;           // wavefronts per block of the map-reduce
 };
 constexpr int kBatchLocBits = 22;                  // block index bits of a table entry

@@ -7,7 +7,8 @@
 //   k_ctg_rows      per-(t, l, k) outage flows F_l + LODF_lk F_k, their (eqs. (rank_correct),
 //                     penalties and reductions, per-(t, k) penalties z_tk, (sfr_pen)-(zctg), (2nd_lin_sys))
 //                     per-chunk worst and sum (branch-stacked tile: k_ctg_main
-//                     and k_ctg_zred instead)
+//                     and k_ctg_zred instead; QG_FLAG_CTG_NO_SKIP: k_ctg_test
+//                     before it)
 //   k_ctg_asm       per-(t, l) dL/dF and dL/dqmax2 (mean + worst-contingency weights)
 //                   + per-(t, bus) power balance from bus-sorted endpoint flows
 //                     (LDS-staged segmented sums)                      (Ex. 4)
@@ -56,6 +57,7 @@ struct EvalArgs {
   // period-split tile: branch slices of a map-reduce block (0: branch-stacked
   // tile) and the contingency-block stride of w.rq and w.hot
   int nsl, rqs;
+  int ntest;  // blocks of k_ctg_test
   TermOffsets toff;
   // contingencies scored this step (Alg. 2): slot s of the map-reduce holds
   // contingency act_k[s] (the identity when act_k is null), na slots in use,
@@ -1109,7 +1111,8 @@ __global__ __launch_bounds__(512) void k_ctg_main(EvalArgs a, const LT* __restri
 // 64-bit word of row flags per group; the readers consult the word first.
 // Neither the pairing of rows nor the bound changes any sum's order, so
 // testing every row (lmax null) gives bitwise the same results, as does a
-// block of fewer wavefronts than slices.
+// block of fewer wavefronts than slices.  ALL: every row was tested by
+// k_ctg_test, and the flagged rows come from its words.
 //
 // FP64 tests |P| > thr_tl with thr_tl from k_forward, a radius a little below
 // sqrt(s_ctg^2 - qmax2_tl), so that every element the exact test
@@ -1237,7 +1240,7 @@ __device__ __forceinline__ void ctg_finish_s(const EvalArgs& a, int kc, int t, d
 }
 
 // LT: storage type of the outage factors; lds: a.nsl x 128 doubles.
-template <typename LT>
+template <typename LT, bool ALL>
 __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* lds) {
   typedef typename std::conditional<std::is_same<LT, double>::value, double, float>::type R;
   constexpr bool kF64 = std::is_same<R, double>::value;
@@ -1251,16 +1254,21 @@ __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* 
   const unsigned k = (unsigned)(kb * 64 + lane);  // slot of the lane
   const double* __restrict__ Ft = w.F + (size_t)t * Lp;
   const double* __restrict__ Ht = (kF64 ? w.thr : w.q2) + (size_t)t * Lp;  // thr, or qmax2
-  const double* __restrict__ lmax = a.lmax ? a.lmax + (size_t)kb * Lp : nullptr;
+  const double* __restrict__ lmax = ALL ? nullptr : a.lmax + (size_t)kb * Lp;
   // F, thr and the largest factor of a lane's branch in the first group, in
   // flight with the outaged branches' flows; later groups' one group ahead
   double Fn = 0.0, Hn = 0.0, Mn = 0.0;
+  uint64_t flags = 0;
+  uint64_t* __restrict__ words = w.hot + (size_t)t * ng * a.rqs + kb;
   auto prefetch = [&](int g) {
     if (g < ng) {
       const int l = g * 64 + lane;
       Fn = Ft[l];
       Hn = Ht[l];
-      if (lmax) Mn = lmax[l];
+      if constexpr (ALL)
+        flags = words[(size_t)g * a.rqs];
+      else
+        Mn = lmax[l];
     }
   };
   prefetch(wv);
@@ -1310,19 +1318,20 @@ __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* 
     for (int g = s; g < ng; g += a.nsl) {
       const int l = g * 64 + lane;
       const double F = Fn, H = Hn, M = Mn;
+      const uint64_t known = flags;
       const double smx = p.ctg_smax[l];
       double q2 = H;
       if constexpr (kF64) q2 = w.q2[(size_t)t * Lp + l];
       prefetch(g + a.nsl);
       bool cold = false;
-      if (lmax) {
-        if constexpr (kF64) {
-          const double e = fabs(F) * (1.0 + 0x1p-40) - H * (1.0 - 0x1p-40);
-          cold = fma(M, fkm, e) <= 0.0;
-        } else {
-          const double e = fma(M, fkm, fabs(F));
-          cold = (e * e + q2) * (1.0 + 0x1p-18) <= smx * smx * (1.0 - 0x1p-18);
-        }
+      if constexpr (ALL) {
+        cold = !((known >> lane) & 1);
+      } else if constexpr (kF64) {
+        const double e = fabs(F) * (1.0 + 0x1p-40) - H * (1.0 - 0x1p-40);
+        cold = fma(M, fkm, e) <= 0.0;
+      } else {
+        const double e = fma(M, fkm, fabs(F));
+        cold = (e * e + q2) * (1.0 + 0x1p-18) <= smx * smx * (1.0 - 0x1p-18);
       }
       uint64_t und = __builtin_amdgcn_ballot_w64(l < L && !cold), hot = 0;
       while (und) {
@@ -1349,7 +1358,7 @@ __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* 
             h.smx2 = (R)(m * m);
             over = fma(h.P, h.P, h.q2) > h.smx2;
           }
-          if (__builtin_amdgcn_ballot_w64(over) == 0) continue;
+          if (!ALL && __builtin_amdgcn_ballot_w64(over) == 0) continue;
           hot |= (uint64_t)1 << r[u];
           const double m = readlane_f64(smx, r[u]);
           h.smx = (R)m;
@@ -1367,7 +1376,7 @@ __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* 
           }
         }
       }
-      if (lane == 0) w.hot[((size_t)t * ng + g) * a.rqs + kb] = hot;
+      if (!ALL && lane == 0) words[(size_t)g * a.rqs] = hot;
     }
     if (pend.l >= 0) {
       HotRow<R> none;
@@ -1391,10 +1400,115 @@ __device__ __forceinline__ void ctg_rows_body(const EvalArgs& a, int b, double* 
 
 // Blocks (contingency block, period), XCD-grouped: the periods of one
 // contingency block read the same factor rows through one L2.
-template <typename LT>
+template <typename LT, bool ALL>
 __global__ __launch_bounds__(1024) void k_ctg_rows(EvalArgs a) {
   extern __shared__ double dyn[];
-  ctg_rows_body<LT>(a, xcd_group(blockIdx.x, gridDim.x), dyn);
+  ctg_rows_body<LT, ALL>(a, xcd_group(blockIdx.x, gridDim.x), dyn);
+}
+
+// The test of every row, where no bound is to decide any (lmax null): a block tests a
+// group of 64 branches against 64 contingencies in several periods and stores the
+// group's flags a period.  The factors are turned over through LDS, so that a lane
+// holds a branch: it keeps the largest |P| of its row (NaN dropped), an FMA and a
+// maximum an element with F_k by v_readlane, and the lanes' tests of that largest flow
+// are the word.  With FP32 the test fl(P^2 + qmax2) > s_ctg^2 grows with |P|: the
+// largest flow passes it if any does.
+// WIDE: each wavefront takes kTestTp periods of its own; otherwise all take the same
+// ones and a quarter of the contingencies each, for grids of few blocks or periods
+// (2800 branches x 2 periods: a step of 43.0 us, 54.3 in wide blocks).
+// Bound by the vector instructions.  With 2800 branches, 2432 contingencies and 48
+// periods it takes 68 us (FP32 41), and k_ctg_rows then 21 (17); testing the rows one
+// period and four rows at a time in k_ctg_rows took 190 (210).  Slower: F and radius
+// by scalar loads and a lane a contingency, a compare and its ballot an element (70;
+// FP32 by v_readlane 90).
+constexpr int kTestTp = 4;     // periods of a wavefront
+constexpr int kTestWaves = 4;  // wavefronts of a block
+constexpr int test_periods(bool wide) { return wide ? kTestTp * kTestWaves : kTestTp; }
+
+template <typename LT, bool WIDE>
+__device__ __forceinline__ void ctg_test_block(const EvalArgs& a, int q, double* lds) {
+  typedef typename std::conditional<std::is_same<LT, double>::value, double, float>::type R;
+  constexpr bool kF64 = std::is_same<R, double>::value;
+  constexpr int TP = kTestTp, kRow = 65;
+  const DevProblem& p = a.p;
+  const DevWork& w = a.w;
+  const LT* __restrict__ lodf = DevPtr<const LT>(static_cast<const LT*>(a.lodf_sel));
+  const int lane = threadIdx.x & 63, T = p.T, Lp = p.Lp, ng = Lp >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ntc = (T + test_periods(WIDE) - 1) / test_periods(WIDE);
+  // period chunks of one tile side by side: they read the same factors
+  const int kg = q / ntc, kb = kg / ng, g = kg - kb * ng;
+  const int t0 = (q - kg * ntc) * test_periods(WIDE) + (WIDE ? wv * TP : 0);
+  const unsigned k = (unsigned)(kb * 64 + lane);  // slot of the lane while loading
+  R* tile = reinterpret_cast<R*>(lds);            // [64 branches][kRow]
+  const LT* __restrict__ row = lodf + (size_t)(g * 64 + wv * 16) * a.kst;
+  R in[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) in[j] = lodf_load(row + (size_t)j * a.kst, k);
+  const int l = g * 64 + lane;  // branch of the lane
+  const int kc = a.act_k ? a.act_k[k] : (int)k;
+  R fk[TP], F[TP], m[TP];
+  double H[TP];  // thr, or qmax2
+#pragma unroll
+  for (int i = 0; i < TP; ++i) {
+    const size_t t = min(t0 + i, T - 1);  // periods past the last store nothing
+    fk[i] = (R)w.Fk[t * p.Kp + kc];
+    F[i] = (R)w.F[t * Lp + l];
+    H[i] = (kF64 ? w.thr : w.q2)[t * Lp + l];
+    m[i] = R(-1);
+  }
+#pragma unroll
+  for (int j = 0; j < 16; ++j) tile[(wv * 16 + j) * kRow + lane] = in[j];
+  __syncthreads();
+  const R* mine = tile + lane * kRow;
+  const int k0 = WIDE ? 0 : wv * 16, k1 = WIDE ? 64 : k0 + 16;
+#pragma unroll 8
+  for (int kk = k0; kk < k1; ++kk) {
+    const R lod = mine[kk];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) m[i] = fmax(m[i], fabs(fma(lod, readlane_any(fk[i], kk), F[i])));
+  }
+  __syncthreads();
+  if constexpr (!WIDE) {
+    R* part = tile;  // [wavefront][TP][64]
+#pragma unroll
+    for (int i = 0; i < TP; ++i) part[(wv * TP + i) * 64 + lane] = m[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+      for (int u = 0; u < kTestWaves; ++u) m[i] = fmax(m[i], part[(u * TP + i) * 64 + lane]);
+    __syncthreads();  // the next tile's factors overwrite them
+  }
+  float s2 = 0.f;
+  if constexpr (!kF64) {
+    const double r = p.ctg_smax[l];
+    s2 = (float)(r * r);
+  }
+#pragma unroll
+  for (int i = 0; i < TP; ++i) {
+    bool over;
+    if constexpr (kF64)
+      over = m[i] > H[i];
+    else
+      over = m[i] >= 0.f && fmaf(m[i], m[i], (float)H[i]) > s2;
+    const uint64_t word = __builtin_amdgcn_ballot_w64(over);
+    if (t0 + i < T && lane == 0 && (WIDE || wv == 0))
+      w.hot[((size_t)(t0 + i) * ng + g) * a.rqs + kb] = word;
+  }
+}
+
+// lds: 64 x 65 factors.
+template <typename LT, bool WIDE>
+__device__ __forceinline__ void ctg_test_body(const EvalArgs& a, int b, double* lds) {
+  const int n = a.nKb * (a.p.Lp >> 6) * ((a.p.T + test_periods(WIDE) - 1) / test_periods(WIDE));
+  for (int q = b; q < n; q += a.ntest) ctg_test_block<LT, WIDE>(a, q, lds);
+}
+
+template <typename LT, bool WIDE>
+__global__ __launch_bounds__(kTestWaves * 64) void k_ctg_test(EvalArgs a) {
+  __shared__ double lds[64 * 65 * (std::is_same<LT, double>::value ? 2 : 1) / 2];
+  ctg_test_body<LT, WIDE>(a, xcd_group(blockIdx.x, gridDim.x), lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -2139,11 +2253,32 @@ void launch_ctg_main(int bl, dim3 grid, dim3 block, hipStream_t s, const EvalArg
   }
 }
 
+// Blocks of k_ctg_test (which loop past 2^20 of them).
+static int test_blocks(const Problem* pr, const EvalArgs& a, bool wide) {
+  const int n = test_periods(wide);
+  const int64_t tiles = (int64_t)a.nKb * (pr->Lp / 64) * ((pr->T + n - 1) / n);
+  return (int)std::min<int64_t>(tiles, 1 << 20);
+}
+// Blocks that count for its wide form (half its wavefronts have a period), and whether
+// they are four a CU.
+static int wide_blocks(const Problem* pr, const EvalArgs& a) {
+  return pr->T > test_periods(true) / 2 ? test_blocks(pr, a, true) : 0;
+}
+static bool test_wide(int64_t blocks) { return blocks >= 4 * 256; }
+
 template <typename LT>
 void launch_ctg(const Problem* pr, hipStream_t s, const EvalArgs& a, const LT* lodf) {
   const CtgTile& t = pr->tile;
   if (t.split) {
-    hipLaunchKernelGGL(k_ctg_rows<LT>, dim3(a.nKb * pr->T), dim3(64 * a.nsl),
+    if (!a.lmax) {
+      EvalArgs b = a;
+      const bool wide = test_wide(wide_blocks(pr, a));
+      b.ntest = test_blocks(pr, a, wide);
+      auto test = wide ? k_ctg_test<LT, true> : k_ctg_test<LT, false>;
+      hipLaunchKernelGGL(test, dim3(b.ntest), dim3(kTestWaves * 64), 0, s, b);
+    }
+    auto rows = a.lmax ? k_ctg_rows<LT, false> : k_ctg_rows<LT, true>;
+    hipLaunchKernelGGL(rows, dim3(a.nKb * pr->T), dim3(64 * a.nsl),
                        (size_t)a.nsl * 128 * sizeof(double), s, a);
     return;
   }
@@ -2197,6 +2332,7 @@ static EvalArgs make_args(const Problem* pr, const DevWork& w, const double* x, 
     a.lmax = dp.lmax;
   }
   a.nsl = ctg_slices(*pr, a.nKb);
+  a.ntest = 0;
   return a;
 }
 
@@ -2307,13 +2443,28 @@ __global__ __launch_bounds__(kBlock) void k_forward_b(const EvalArgs* __restrict
 // Batched row-compacted map-reduce: each wavefront takes slices of its block's
 // (period, contingency block) in turn; the sums are added in slice order, as in
 // a launch of the problem's own.
-template <typename LT>
+// ALL: a problem of the batch has every row tested.
+template <typename LT, bool ALL>
 __global__ __launch_bounds__(kCtgSlices * 64) void k_ctg_rows_b(const EvalArgs* __restrict__ args,
                                                                 const uint32_t* __restrict__ tab) {
   extern __shared__ double dyn[];
   int s, b;
   batch_entry(tab, blockIdx.x, s, b);
-  ctg_rows_body<LT>(args[s], xcd_group(b, args[s].nKb * args[s].p.T), dyn);
+  const EvalArgs& a = args[s];
+  b = xcd_group(b, a.nKb * a.p.T);
+  if (ALL && !a.lmax)
+    ctg_rows_body<LT, true>(a, b, dyn);
+  else
+    ctg_rows_body<LT, false>(a, b, dyn);
+}
+
+template <typename LT, bool WIDE>
+__global__ __launch_bounds__(kTestWaves * 64) void k_ctg_test_b(const EvalArgs* __restrict__ args,
+                                                                const uint32_t* __restrict__ tab) {
+  __shared__ double lds[64 * 65 * (std::is_same<LT, double>::value ? 2 : 1) / 2];
+  int s, b;
+  batch_entry(tab, blockIdx.x, s, b);
+  ctg_test_body<LT, WIDE>(args[s], b, lds);
 }
 
 __global__ __launch_bounds__(kBlock) void k_ctg_asm_b(const EvalArgs* __restrict__ args,
@@ -2348,7 +2499,7 @@ __global__ __launch_bounds__(kBlock) void k_final_b(const EvalArgs* __restrict__
 static void stage_blocks(const Problem* pr, const EvalArgs& a, int out[kStages]) {
   out[0] = pr->nb_br + pr->T + pr->Lp / 16 * (pr->Tp / 16);
   out[1] = pr->K > 0 ? a.nKb * pr->T : 0;
-  out[2] = 0;  // the map-reduce finishes z itself
+  out[2] = a.ntest;  // k_ctg_test, before stage 1 (k_ctg_rows finishes z itself)
   out[3] = asm_blocks(pr);
   out[4] = pr->G16 / 16 * pr->nsplit + pr->nb_br + (pr->T * pr->G16 + kBlock - 1) / kBlock;
   out[5] = pr->nb_bus + 4 * pr->nb_gen + 1;
@@ -2363,6 +2514,12 @@ int plan_batch(const Problem* const* prs, const DevWork* ws, int n, const double
   P.n = n;
   std::vector<EvalArgs> args((size_t)n);
   std::vector<std::array<int, kStages>> nb((size_t)n);
+  int64_t wide = 0;  // blocks of k_ctg_test's wide form
+  for (int i = 0; i < n; ++i) {
+    const EvalArgs a = make_args(prs[i], ws[i], x[i], nullptr, nullptr, mode, 1, m[i], v[i]);
+    if (prs[i]->K > 0 && !a.lmax) wide += wide_blocks(prs[i], a);
+  }
+  P.test_wide = test_wide(wide);
   for (int i = 0; i < n; ++i) {
     const Problem* pr = prs[i];
     const CtgTile& t = pr->tile;
@@ -2380,6 +2537,7 @@ int plan_batch(const Problem* const* prs, const DevWork* ws, int n, const double
       return 1;
     }
     args[i] = make_args(pr, ws[i], x[i], nullptr, nullptr, mode, 1, m[i], v[i]);
+    if (pr->K > 0 && !args[i].lmax) args[i].ntest = test_blocks(pr, args[i], P.test_wide);
     int b[kStages];
     stage_blocks(pr, args[i], b);
     for (int q = 0; q < kStages; ++q) {
@@ -2440,12 +2598,20 @@ int launch_eval_batch(const BatchPlan& P, void* d_buf, void* stream) {
   if (P.nblk[1] > 0) {
     const size_t lds = (size_t)P.nsl * 128 * sizeof(double);
     const dim3 g(P.nblk[1]), blk(P.row_waves * 64);
+    auto go = [&](auto test, auto all, auto rows) {
+      if (P.nblk[2] > 0)
+        hipLaunchKernelGGL(test, dim3(P.nblk[2]), dim3(kTestWaves * 64), 0, s, args, tab(2));
+      hipLaunchKernelGGL(P.nblk[2] > 0 ? all : rows, g, blk, lds, s, args, tab(1));
+    };
     if (P.lodf_kind == kLodfF64)
-      hipLaunchKernelGGL(k_ctg_rows_b<double>, g, blk, lds, s, args, tab(1));
+      go(P.test_wide ? k_ctg_test_b<double, true> : k_ctg_test_b<double, false>,
+         k_ctg_rows_b<double, true>, k_ctg_rows_b<double, false>);
     else if (P.lodf_kind == kLodfF32)
-      hipLaunchKernelGGL(k_ctg_rows_b<float>, g, blk, lds, s, args, tab(1));
+      go(P.test_wide ? k_ctg_test_b<float, true> : k_ctg_test_b<float, false>,
+         k_ctg_rows_b<float, true>, k_ctg_rows_b<float, false>);
     else
-      hipLaunchKernelGGL(k_ctg_rows_b<uint16_t>, g, blk, lds, s, args, tab(1));
+      go(P.test_wide ? k_ctg_test_b<uint16_t, true> : k_ctg_test_b<uint16_t, false>,
+         k_ctg_rows_b<uint16_t, true>, k_ctg_rows_b<uint16_t, false>);
   }
   hipLaunchKernelGGL(k_ctg_asm_b, dim3(P.nblk[3]), dim3(kBlock), 0, s, args, tab(3));
   hipLaunchKernelGGL(k_adjoint_b, dim3(P.nblk[4]), dim3(kBlock), 0, s, args, tab(4));

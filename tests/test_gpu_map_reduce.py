@@ -83,3 +83,131 @@ def test_split_tile_names_change_nothing(qg):
         for g in got[1:]:
             assert np.array_equal(got[0][1], g[1]) and np.array_equal(got[0][2], g[2]), lt
     prob.close()
+
+
+def pair(qg, c, flags=0):
+    """The problem with the bound and with every element tested."""
+    return [qg.Problem(c, flags=flags | extra) for extra in (0, qg.QG_FLAG_CTG_NO_SKIP)]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("shape", [(500, 1100, 17), (900, 2000, 17), (900, 2000, 8)])
+def test_testing_every_element_in_both_forms(qg, prec, shape):
+    """Without the bound the rows are tested by a kernel of their own, in blocks of
+    sixteen periods (grids of a thousand such blocks, more than eight periods) or
+    of four: bitwise the results with the bound, of every contingency and of a
+    screened set, with a period more than whole blocks and with half of one."""
+    n, nb, T = shape
+    flag = {"fp64": 0, "fp32": qg.QG_FLAG_CTG_FP32, "bf16": qg.QG_FLAG_CTG_BF16}[prec]
+    c = synth.make_case(seed=n + T, n_bus=n, n_branch=nb, n_gen=40, n_period=T, n_ctg=None,
+                        mesh=2.0)
+    x = synth.random_point(c, 9, spread=0.2)
+    A = np.sort(np.random.default_rng(3).choice(c.n_ctg, size=c.n_ctg // 3, replace=False))
+    got = []
+    for prob in pair(qg, c, flag):
+        full = evaluate(prob, x)
+        prob.set_screening(top_frac=len(A) / c.n_ctg)
+        prob.set_active_contingencies(A)
+        got.append(full + evaluate(prob, x))
+        prob.close()
+    assert got[0][0][qg.TERM_NAMES.index("ctg_max")] > 0.0
+    for a, b in zip(*got):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_batch_of_problems_with_and_without_the_bound(qg, wide):
+    """A batch in which some problems have every element tested, in the small and the
+    wide form of that kernel, ends where each problem solved alone ends."""
+    import torch
+    shapes = [(60, 90, 9), (131, 183, 7)] + ([(900, 2000, 20)] if wide else [])
+    probs, cases = [], []
+    for i, (n, nb, T) in enumerate(shapes):
+        c = synth.make_case(seed=40 + i, n_bus=n, n_branch=nb, n_gen=12, n_period=T, n_ctg=None,
+                            mesh=2.0)
+        for p in pair(qg, c)[:: 1 if i else -1]:
+            p.set_tile("s4x4")
+            probs.append(p)
+            cases.append(c)
+    opts = qg.solve_opts(4, 1e-3, eps0=1e-1, epsf=1e-3)
+    ends = []
+    for batched in (True, False):
+        vs = [[p.new_vector(synth.flat_start(c)), p.new_vector(), p.new_vector()]
+              for p, c in zip(probs, cases)]
+        if batched:
+            qg.solve_batch(probs, *zip(*vs), opts)
+        else:
+            for p, v in zip(probs, vs):
+                p.solve(*v, opts)
+        torch.cuda.synchronize()
+        ends.append([v[0].cpu().numpy() for v in vs])
+    for p in probs:
+        p.close()
+    for i, (a, b) in enumerate(zip(*ends)):
+        assert np.isfinite(a).all() and np.array_equal(a, b), i
+        assert np.array_equal(a, ends[0][i ^ 1]), i  # nor does the bound matter
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf, 1e200])
+def test_bound_with_flows_that_are_no_numbers(qg, prec, value):
+    """A row whose flow or whose outages' flows are NaN or infinite is tested, not
+    passed over: the same results, NaN where there is NaN, as testing every element;
+    the other periods' gradient entries are untouched."""
+    flag = {"fp64": 0, "fp32": qg.QG_FLAG_CTG_FP32, "bf16": qg.QG_FLAG_CTG_BF16}[prec]
+    c = synth.make_case(seed=21, n_bus=90, n_branch=150, n_gen=12, n_period=5, n_ctg=None,
+                        mesh=0.7)
+    x = synth.random_point(c, 5, spread=0.3)
+    bad = x.copy()
+    P = c.block_slices()[2]
+    bad[P.start + 2 * c.n_gen + 3] = value  # the third period's
+    got = []
+    for prob in pair(qg, c, flag):
+        got.append(evaluate(prob, x) + evaluate(prob, bad))
+        prob.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=True)
+    good, spoilt = got[0][1], got[0][3]
+    th = c.block_slices()[1]
+    for t in (0, 4):
+        s = slice(th.start + t * c.n_bus, th.start + (t + 1) * c.n_bus)
+        assert np.array_equal(good[s], spoilt[s]), t
+
+
+def test_rows_the_bound_decides(qg):
+    """At a state 1,500 steps into a solve of the 2,000-bus grid the bound |F_tl| + max
+    |LODF| max |F_tk| <= radius (of one branch, one period, 64 contingencies; here
+    from the oracle's flows and factors) decides nine rows in ten and some element
+    is overloaded; the results are those of testing every element for every number
+    of slices."""
+    from tests.test_gpu_parity import _solved_point
+    c = synth.config_case("c3")
+    x = _solved_point(qg, c, 1500)
+    mdl = ob.make_model(c)
+    V, TH, P, Q, R, U = ob.unpack(c, x)
+    q2, _ = ob.qmax2(ob.branch_flows(mdl, V, TH))
+    F = ob.balanced_injection(c, P) @ mdl.isf.T
+    K = len(mdl.ctg)
+    Kp = -(-K // 64) * 64
+    smax2 = np.asarray(c.br_smax_ctg, dtype=np.float64) ** 2
+    thr = np.sqrt(np.maximum(smax2[None, :] - q2, 0.0))
+    lod = np.zeros((c.n_branch, Kp))
+    lod[:, :K] = np.abs(mdl.lodf)
+    lod[mdl.ctg, np.arange(K)] = 0.0
+    lm = lod.reshape(c.n_branch, Kp // 64, 64).max(axis=2)
+    fk = np.zeros((c.n_period, Kp))
+    fk[:, :K] = np.abs(F[:, mdl.ctg])
+    fkm = fk.reshape(c.n_period, Kp // 64, 64).max(axis=2)
+    cold = (np.abs(F) - thr)[:, :, None] + lm[None] * fkm[:, None, :] <= 0.0
+    assert 0.9 < cold.mean() < 1.0
+    Pk = F[0][:, None] + mdl.lodf * F[0, mdl.ctg][None, :]
+    assert np.nansum(Pk * Pk + q2[0][:, None] > smax2[:, None]) > 0
+    probs = pair(qg, c)
+    for tile in ("s4x4", "s4x4x7", "s4x4x16", "s4x4x24", "s4x4x32", "s4x4x64"):
+        got = []
+        for prob in probs:
+            prob.set_tile(tile)
+            got.append(evaluate(prob, x))
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1]), tile
+    for prob in probs:
+        prob.close()
