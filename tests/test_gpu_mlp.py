@@ -154,10 +154,9 @@ def test_deterministic(qg):
     assert np.array_equal(a, b) and np.array_equal(g1, g2)
 
 
-# edges of the products: reduction tails, odd row lengths, one to four blocks
-# of 16 batch rows and the first of a second tile, an output layer with tiles
-# enough for one slice (its loss comes from the product), a batch past which the
-# weight gradient is a product of its own
+# edges of the products in tiles of 16 rows: reduction tails, odd row lengths, one
+# to four blocks of 16 batch rows and more, an output layer whose loss comes from
+# the product, a weight gradient of more than eight chains of 32 rows
 EDGE_SHAPES = [(33, 65, 1, 67, 1), (130, 63, 2, 4200, 16), (257, 97, 1, 4161, 33),
                (64, 32, 2, 40, 65), (50, 41, 1, 61, 257)]
 
