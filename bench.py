@@ -39,6 +39,7 @@ METRIC = "grad+Adam steps/s at 617-bus×18T×all ctg; learned vs plain time-to-1
 PEAK_HBM_GBS = 8000.0
 PEAK_FP64_TFLOPS = 78.6       # vector and matrix (dense)
 PEAK_FP32_TFLOPS = 157.3      # vector
+UPDATE_MAX_BRANCH = 768       # grids of up to this many branches run k_update
 
 
 def parse():
@@ -79,6 +80,14 @@ def kernel_work(case, dims, factor_bytes=8):
     """Algorithmic work per launch of each kernel: (bound, amount, unit)."""
     T, N, L, G, K = case.n_period, case.n_bus, case.n_branch, case.n_gen, case.n_ctg
     D = 8
+    # 16 generators' slabs, reverse pass of the branches: 6 coefficients and a byte in,
+    # 4 end adjoints out
+    adjoint = D * (T * L * 6 + 2 * T * N + T * L) + T * L
+    ends = D * T * 2 * L * 2
+    # generator assembly and the fused Adam (48 B per entry)
+    final = D * (4 * T * G + 6 * (2 * T * N + 4 * T * G))
+    # end flows and balance; device terms (8 doubles per device-period)
+    rest = D * (T * 2 * L * 2 + 4 * T * N + 8 * T * G)
     return {
         # per (t, l): x gathers, 12 doubles and a byte out; flow product 2 T G L
         # flop (reported as bytes: the product is tiny)
@@ -93,13 +102,15 @@ def kernel_work(case, dims, factor_bytes=8):
                        if dims["ctg_split"] else ("alu", 8.0 * T * L * K, "flop")),
         # partial sums over l-blocks for every (t, k)
         "k_ctg_zred": ("hbm", D * T * K * (dims["nLb"] * 2 + 2), "byte"),
-        # partial sums over k-blocks for every (t, l); balance over bus-sorted ends
-        "k_ctg_asm": ("hbm", D * (T * L * (dims["nKb"] * 2 + 6) + T * 2 * L * 2 + 4 * T * N), "byte"),
-        # adjoint product 2 T G L flop; branch reverse reads 6 coefficients and a
-        # byte, writes 4
-        "k_adjoint": ("hbm", D * (T * L * 10 + 2 * T * N + T * L) + T * L, "byte"),
-        # endpoint adjoints, generator assembly and the fused Adam (48 B per entry)
-        "k_final": ("hbm", D * (T * 2 * L * 2 + 4 * T * G + 6 * (2 * T * N + 4 * T * G)), "byte"),
+        # flow adjoints, F, qmax2 and their ends; the sums over k-blocks of every (t, l),
+        # or (period-split form, which stores them for overloaded rows only, not
+        # counted) a flag per (t, branch, k-block)
+        "k_ctg_asm": ("hbm", rest + D * T * L * 4 + (T * L * dims["nKb"] / 8 if dims["ctg_split"]
+                                                    else D * T * L * dims["nKb"] * 2), "byte"),
+        # k_update: both kernels' work, the end adjoints kept in LDS
+        "k_adjoint": ("hbm", adjoint + ends, "byte"),
+        "k_update": ("hbm", adjoint + final, "byte"),
+        "k_final": ("hbm", ends + final, "byte"),
     }
 
 
@@ -294,7 +305,12 @@ def main():
     # a short kernel's back-to-back mean varies with the clock more than the
     # order of the in-step durations does); its rate over the back-to-back mean
     dom = max(kms_step, key=lambda k: kms_step[k])
-    bound, amount, unit = work[dom]
+    # what runs in a stage's place: k_ctg_rows under a period-split tile, k_update (for
+    # k_adjoint and k_final) on small grids
+    kname = "k_ctg_rows" if (dom == "k_ctg_main" and prob.dims["ctg_split"]) else dom
+    if dom == "k_final" and case.n_branch <= UPDATE_MAX_BRANCH:
+        kname = "k_update"
+    bound, amount, unit = work[kname if kname in work else dom]
     sec = kms[dom] * 1e-3
     if bound == "hbm":
         achieved = amount / sec / 1e9
@@ -306,8 +322,6 @@ def main():
         peak = (PEAK_FP32_TFLOPS if (dom == "k_ctg_main" and args.ctg_precision != "fp64")
                 else PEAK_FP64_TFLOPS)
         runit = "TFLOP/s"
-    # the map-reduce stage runs k_ctg_rows under a period-split tile
-    kname = "k_ctg_rows" if (dom == "k_ctg_main" and prob.dims["ctg_split"]) else dom
     roof = dict(bound=bound, kernel=kname, achieved=achieved, peak=peak, unit=runit,
                 frac=achieved / peak,
                 traffic=(stored_traffic(kname, args.config, prob.tile())
