@@ -263,9 +263,9 @@ int ctg_slices(const Problem& p, int nkb) {
     // once (28 wavefronts of k_ctg_rows fit a CU), but 8 at least: a block's
     // wavefronts wait for each other twice, so where the blocks come in
     // several rounds smaller blocks that overlap do better.  us of the
-    // map-reduce with 16 / 11 / 8 slices: 162 blocks of 14 groups 7.5 (14
-    // slices) / - / 8.7 (7), 456 of 44 16.6 / 13.3 / 13.8, 589 of 23 15.4 /
-    // 13.3 (12) / 12.7, 1824 of 44 49 / 42 / 36.
+    // map-reduce at the end of a solve with 16 / 11 / 8 slices: 162 blocks of 14
+    // groups 6.4 (14 slices) / - / 7.1 (7), 456 of 44 12.3 (15) / 10.4 / 10.5, 589
+    // of 23 11.5 / 11.7 (12) / 9.9, 1824 of 44 39.6 (15) / 31.0 / 28.2.
     const int per_cu = (nkb * p.T + 255) / 256;
     const int wl = std::max(8, std::min(kCtgSlices, 28 / per_cu));
     most = (ng + wl - 1) / wl;

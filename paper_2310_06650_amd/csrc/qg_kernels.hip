@@ -1127,18 +1127,19 @@ __global__ __launch_bounds__(512) void k_ctg_main(EvalArgs a, const LT* __restri
 //
 // What it measured, against a tile of eight branches and four periods per
 // wavefront whose half rows (four branches) were skipped together and whose
-// z and S went through memory to a reduction kernel (us in the step,
-// map-reduce + reduction before, this kernel now): 2000 buses x 48 periods
-// 55.6 + 10.0 -> 36, 617 x 18 9.4 + 4.8 -> 7.4, twelve grids of 100-1000 buses in a
-// batch 262 + 17 -> 48.  There 2.1 % of the rows at 2000 buses are hot, and most
+// z and S went through memory to a reduction kernel (us in the steps of solves a
+// fifth under way, map-reduce + reduction before, this kernel now): 2000 buses x 48
+// periods 55.6 + 10.0 -> 34, 617 x 18 9.4 + 4.8 -> 7.2, twelve grids of 100-1000 buses
+// in a batch 262 + 17 -> 39 (along the benchmark's solves from the flat start 29 and 7.2 in
+// the two grids).  There 2.1 % of the rows at 2000 buses are hot, and most
 // of them in all 64 lanes (the branch is overloaded before the outage); 3.8 %
 // remain after the bound (13 % of half rows did).  At 2000 buses the vector
 // instructions bound it (they issue in about three quarters of the SIMD cycles,
 // half of them for the hot rows); at 617 buses its chain of four memory round
 // trips does.  Slower: the slices' hot rows spread evenly over the wavefronts
-// after the test (two more barriers and a lookup: 48 us, 10 us at 617 buses),
-// one list of undecided rows for four groups with F and thr by scalar loads
-// (44 us), R and Q staged in LDS (44 us).
+// after the test (two more barriers and a lookup: 48 us where it took 36, 10 us
+// at 617 buses), one list of undecided rows for four groups with F and thr by
+// scalar loads (44 us), R and Q staged in LDS (44 us).
 
 // A hot row (one with a flagged lane): the lane's post-outage flow and factor,
 // the branch (-1: none), its qmax2 and rating.

@@ -295,9 +295,9 @@ __device__ __forceinline__ void tile_elements(const v4f (&acc)[2], int m0, int n
 // split: raw sums to C + z M N, otherwise the epilogue at once.
 //
 // At 64 rows bound by the weights' first read from HBM: 512 x 29412 (60 MB) with
-// the loss and dY takes 31 us, 2.4 TB/s (a streaming sum of 60 MB that no cache
+// the loss and dY takes 32 us, 2.3 TB/s (a streaming sum of 60 MB that no cache
 // holds takes 28); staged through LDS, in two slices, then added up and compared by
-// kernels of their own it took 67.  Its transposed product takes 24 us (32
+// kernels of their own it took 67.  Its transposed product takes 26 us (32
 // through LDS).  More steps in flight (DEPTH 3, 4 at MI = 4) were 10 % slower.
 constexpr int kStep = 16;
 // Steps of one accumulation chain: 32 of the reduction, added to a wavefront's sum
@@ -489,9 +489,11 @@ constexpr int kDwShort = 8 * kBK;  // longest batch for which one sum is enough
 // 32.7 + 15.8 + 101 us for the whole network.  Stores past the caches (read
 // again only in the next step) and neighbouring tiles on one XCD (rows are
 // not line-aligned, so neighbours share lines) give 4 and 3 us of it.  One kernel is
-// the faster at every batch: with sliced products and passes of their own
-// 11124 -> 3 x 512 -> 29412 takes 283 us a step at 64 rows against 264, and
-// 600 -> 3 x 512 -> 600 2597 us at 8192 rows against 1500.
+// the faster at every batch and number of tiles: with sliced products and passes of
+// their own 11124 -> 3 x 512 -> 29412 takes 283 us a step at 64 rows against 264,
+// 600 -> 3 x 512 -> 600 2597 us at 8192 rows against 1500; and one tile a layer walked
+// by one block, 40 -> 2 x 32 -> 40 11.5 ms at 65,536 rows with slices, 6.6 here, 64 -> 16 ->
+// 8 7.3 and 4.4.
 struct DwArgs {
   float *gw, *gb;                        // gradients out
   float *pw, *mw, *vw, *pb, *mb, *vb;    // ADAM: parameters and moments
@@ -622,8 +624,8 @@ __global__ __launch_bounds__(kGemm, 4) void k_dw(const float* __restrict__ in, i
 // chains of chain k-steps added as k_reduce_epi adds slices; 1: up to eight, in
 // order; 2: sixteen of one or two k-steps, c and c + 8 first.
 // Bound by the weights' first read: at 64 rows 512 x 29412 (30 MB) with
-// its biases takes 13.7 us and 11124 x 512 11.9; the whole forward pass of
-// 11124 -> 3 x 512 -> 29412 takes 42 us, and 83 with conversions, copies and an
+// its biases takes 14.3 us and 11124 x 512 12.5; the whole forward pass of
+// 11124 -> 3 x 512 -> 29412 takes 41 us, and 83 with conversions, copies and an
 // unpipelined loop.
 template <int DEPTH, bool A32, bool APAIR, bool PAIR, int CHAIN, bool FAR>
 __global__ __launch_bounds__(kGemm) void k_gemm_bf16(const void* __restrict__ Av, int lda,
@@ -874,9 +876,9 @@ void layout(const qg_mlp_desc* d, qg_mlp_layout* L) {
 int tiles_of(int M, int N) { return ((M + kT - 1) / kT) * ((N + kT - 1) / kT); }
 
 // Slices of a deep FP32 product: about one block per CU, each slice at least 64
-// deep.  At 64 x 512 over 29412 or 11124 (8 tiles) 32 slices take 24.2 and 12.4 us,
-// 16 take 35.5 and 17.3, 64 take 30.6 and 17.7 (more sums to write, fewer rows
-// of the weights in each).
+// deep.  With that (32 slices of 64 x 512 over 29412 and 11124, 8 tiles) a training
+// step of 11124 -> 3 x 512 -> 29412 at 64 rows takes 252 us, with half as many 268, with
+// twice as many 264 (more sums to write, fewer rows of the weights in each).
 int slices_f32(int M, int N, int K) {
   const int tiles = tiles_of(M, N);
   if (tiles >= 64 && K <= 512) return 1;  // no second kernel: 5.8 against 4.6 + 4.8 us (7353 x 200)
@@ -937,13 +939,13 @@ int fit_slices(int sl, int M, int N, const Ws& w) {
 // sl slices.  A product that is not deep and has few tiles is cut into tiles of 16
 // rows, read with eight wavefronts a block, instead of slices: the second kernel
 // costs more than the weights' repeated reads from L2.  One forward pass of
-// 600 -> 3 x 512 -> 600 at 64 rows takes 26.6 us in this way, 35.4 in slices; of
-// 1400 -> 2 x 256 -> 3300 18.1, in slices 30.2.  With more blocks than kOneSlice the
-// repeated reads win (29412 outputs: 79.7 us a pass against 53.7).  The transposed
+// 600 -> 3 x 512 -> 600 at 64 rows takes 26.1 us in this way, 31.0 in slices; of
+// 1400 -> 2 x 256 -> 3300 17.3, in slices 26.7.  With more blocks than kOneSlice the
+// repeated reads win (29412 outputs: 86.0 us a pass against 53.1).  The transposed
 // product reads 64 bytes of each of the weights' rows at a time, which a few
-// blocks do slowly over a long reduction: 600 -> 3 x 512 -> 600 trains in 85.8 us with
-// the limit at 256, in 92.4 with 512, and 1400 -> 2 x 256 -> 3300 in 62.4, in 63.0
-// with 128.
+// blocks do slowly over a long reduction: 600 -> 3 x 512 -> 600 trains in 83.6 us with
+// the limit at 256, in 90.5 with 512 (1400 -> 2 x 256 -> 3300 in 61.4 with 128, 256 or
+// 512).
 struct Plan {
   int mi, sl;
   bool far;
